@@ -782,7 +782,8 @@ int Engine::setup_new(std::vector<Job*>& fresh, hipStream_t st) {
     if (rc) return rc;
     std::vector<CoeffDesc> cd;
     std::vector<ReduceDesc> rd;
-    std::vector<CoarseDesc> co_lds, co_glb;
+    std::vector<CoarseDesc> co;
+    std::vector<mg_hierarchy*> co_big;         // coarsest levels that take several launches each
     std::vector<EltDesc> f32;
     int cblocks = 0, f32blocks = 0, maxlev = 0;
     for (size_t q = 0; q < fresh.size(); ++q) {
@@ -816,8 +817,10 @@ int Engine::setup_new(std::vector<Job*>& fresh, hipStream_t st) {
         rd.push_back(ReduceDesc{H->partials, nb, H->scal + kSlotRhs * kReduceWidth, gdev + q * kReduceWidth});
         maxlev = std::max(maxlev, H->nlev);
         Level& Lc = H->lev[H->nlev - 1];
-        const CoarseDesc c{Lc.nx, Lc.ny, Lc.nz, Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, H->singular ? 1 : 0};
-        (coarse_setup_in_lds(Lc.N) ? co_lds : co_glb).push_back(c);
+        if (coarse_setup_batched(Lc.N))
+            co.push_back(CoarseDesc{Lc.nx, Lc.ny, Lc.nz, Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, H->singular ? 1 : 0});
+        else
+            co_big.push_back(H);
         if (H->p.precision == MG_MIXED) {
             // FP32 coefficient mirrors of the stored levels (the finest FP32
             // level recomputes its coefficients from an FP32 copy of rho)
@@ -853,12 +856,15 @@ int Engine::setup_new(std::vector<Job*>& fresh, hipStream_t st) {
         if ((rc = push_table(staging, av, st, &dav))) return rc;
         BHIP(launch_avg_coeff_multi(dav, (int)av.size(), ab, st));
     }
-    for (int lds = 0; lds < 2; ++lds) {
-        std::vector<CoarseDesc>& v = lds ? co_lds : co_glb;
-        if (v.empty()) continue;
+    if (!co.empty()) {
         const CoarseDesc* dco = nullptr;
-        if ((rc = push_table(staging, v, st, &dco))) return rc;
-        BHIP(launch_coarse_setup_multi(dco, (int)v.size(), lds == 1, st));
+        if ((rc = push_table(staging, co, st, &dco))) return rc;
+        BHIP(launch_coarse_setup_multi(dco, (int)co.size(), st));
+    }
+    for (mg_hierarchy* H : co_big) {            // its partial rows are reduced already: scratch
+        const Level& Lc = H->lev[H->nlev - 1];
+        BHIP(launch_coarse_setup(Shape{Lc.nx, Lc.ny, Lc.nz}, Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, H->partials,
+                                 st, nullptr, H->singular ? 1 : 0));
     }
     if (!f32.empty()) {
         const EltDesc* de = nullptr;

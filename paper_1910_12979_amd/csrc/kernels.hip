@@ -458,71 +458,154 @@ __global__ __launch_bounds__(kBlock) void k_resid_norm(int nx, int ny, int nz, T
 }
 
 // ---------------------------------------------------------------------------
-// Coarsest level.  One workgroup builds M = -A + c 1 1^T (c = mean diagonal
-// of -A) and inverts it in place by Gauss-Jordan elimination (M is SPD, so
-// no pivoting is needed).  The per-cycle solve is then a mat-vec.
+// Coarsest level: M = -A + c 1 1^T (c = mean diagonal of -A; with outflow
+// sides M = -A), inverted once per coefficient set (dense.h).  The per-cycle
+// solve is then a mat-vec.
 // ---------------------------------------------------------------------------
-constexpr int kSetupThreads = 1024;
-constexpr int kSetupLdsN = 128;      // matrices up to this order are inverted in LDS
-
-// The workgroup's build and inversion of one problem's coarsest matrix; Ms
-// (order-kSetupLdsN LDS matrix, used when kLds), fac, prow (kCoarseMax
-// each) and shift are LDS scratch of the calling kernel.
-template <bool kLds>
-__device__ void coarse_setup_body(int nx, int ny, int nz, double h, const double* __restrict__ bx,
-                                  const double* __restrict__ by, const double* __restrict__ bz,
-                                  double* __restrict__ Mg, const Bnd<double>& bnd, int has_bnd, int singular,
-                                  double* Ms, double* fac, double* prow, double& shift) {
-    const int n = nx * ny * nz;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    double* M = kLds ? Ms : Mg;
-    const double ih2 = 1.0 / (h * h);
-    for (int e = tid; e < n * n; e += nt) M[e] = 0.0;
-    __syncthreads();
-    for (int c = tid; c < n; c += nt) {
-        int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
-        int im = i > 0 ? i - 1 : nx - 1, ip = i < nx - 1 ? i + 1 : 0;
-        int jm = j > 0 ? j - 1 : ny - 1, jp = j < ny - 1 ? j + 1 : 0;
-        int km = k > 0 ? k - 1 : nz - 1, kp = k < nz - 1 ? k + 1 : 0;
-        double b[6] = {bx[c], bx[cidx(ip, j, k, nx, ny)], by[c], by[cidx(i, jp, k, nx, ny)],
-                       bz[c], bz[cidx(i, j, kp, nx, ny)]};
-        int nb[6] = {(int)cidx(im, j, k, nx, ny), (int)cidx(ip, j, k, nx, ny), (int)cidx(i, jm, k, nx, ny),
-                     (int)cidx(i, jp, k, nx, ny), (int)cidx(i, j, km, nx, ny), (int)cidx(i, j, kp, nx, ny)};
-        double* row = M + c * n;
+// Off-diagonal entries and diagonal of -A for cell c of the coarsest level.
+struct CoarseRows {
+    int nx, ny, nz;
+    double ih2;
+    const double* bx;
+    const double* by;
+    const double* bz;
+    Bnd<double> bnd;
+    int has_bnd;
+    // face q (x low, x high, y low, ...) of cell c: its coefficient and the cell across it
+    __device__ __forceinline__ double face(int c, int q, int& nb) const {
+        const int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
+        const int ip = i < nx - 1 ? i + 1 : 0, jp = j < ny - 1 ? j + 1 : 0, kp = k < nz - 1 ? k + 1 : 0;
+        switch (q) {
+            case 0: nb = (int)cidx(i > 0 ? i - 1 : nx - 1, j, k, nx, ny); return bx[c];
+            case 1: nb = (int)cidx(ip, j, k, nx, ny); return bx[nb];
+            case 2: nb = (int)cidx(i, j > 0 ? j - 1 : ny - 1, k, nx, ny); return by[c];
+            case 3: nb = (int)cidx(i, jp, k, nx, ny); return by[nb];
+            case 4: nb = (int)cidx(i, j, k > 0 ? k - 1 : nz - 1, nx, ny); return bz[c];
+            default: nb = (int)cidx(i, j, kp, nx, ny); return bz[nb];
+        }
+    }
+    __device__ void operator()(int c, int q, double& val, int& nb) const { val = face(c, q, nb) * ih2; }
+    __device__ double diag(int c) const {
+        double d = 0.0;
         for (int q = 0; q < 6; ++q) {
-            if (b[q] == 0.0) continue;      // wall face: no coupling
-            row[c] += b[q] * ih2;
-            row[nb[q]] -= b[q] * ih2;
+            int nb;
+            d += face(c, q, nb) * ih2;
         }
-        if (has_bnd) row[c] += bnd_diag(bnd, i, j, k, nx, ny, nz) * ih2;   // outflow faces
-    }
-    __syncthreads();
-    if (singular) {      // constant null space: M = -A + c 1 1^T, c the mean diagonal
-        if (tid == 0) {
-            double d = 0.0;
-            for (int c = 0; c < n; ++c) d += M[c * n + c];
-            shift = d / n;
+        if (has_bnd) {
+            const int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
+            d += bnd_diag(bnd, i, j, k, nx, ny, nz) * ih2;
         }
-        __syncthreads();
-        for (int e = tid; e < n * n; e += nt) M[e] += shift;
+        return d;
     }
-    gj_invert(M, n, fac, prow);
-    if (kLds)
-        for (int e = tid; e < n * n; e += nt) Mg[e] = Ms[e];
+};
+
+__device__ __forceinline__ void coarse_setup_body(const CoarseRows& R, double* __restrict__ M, int singular, DenseLds<6>& L) {
+    dense_invert<6>(R.nx * R.ny * R.nz, singular, M, L, R, [&](int c) { return R.diag(c); });
 }
 
-template <bool kLds>
-__global__ __launch_bounds__(kSetupThreads) void k_coarse_setup(int nx, int ny, int nz, double h,
-                                                                const double* __restrict__ bx,
-                                                                const double* __restrict__ by,
-                                                                const double* __restrict__ bz,
-                                                                double* __restrict__ Mg, Bnd<double> bnd,
-                                                                int has_bnd, int singular) {
-    __shared__ double Ms[kLds ? kSetupLdsN * kSetupLdsN : 1];
-    __shared__ double fac[kCoarseMax];      // column p before the elimination step
-    __shared__ double prow[kCoarseMax];     // row p before the elimination step
-    __shared__ double shift;
-    coarse_setup_body<kLds>(nx, ny, nz, h, bx, by, bz, Mg, bnd, has_bnd, singular, Ms, fac, prow, shift);
+__global__ __launch_bounds__(kDenseThreads) void k_coarse_setup(CoarseRows R, double* __restrict__ M, int singular) {
+    __shared__ DenseLds<6> L;
+    coarse_setup_body(R, M, singular, L);
+}
+
+__global__ __launch_bounds__(256) void k_coarse_build(CoarseRows R, double* __restrict__ M, int singular) {
+    dense_build_row<6>(R.nx * R.ny * R.nz, singular, M, R, [&](int c) { return R.diag(c); });
+}
+
+// One block step of the inversion above kDenseReg unknowns, pivots p0 ..
+// p0 + nb - 1 (nb <= kDenseNB; a last, smaller block is padded by the unit
+// matrix).  First W = P^-1 R into scratch, P the pivot block and R its rows
+// (with the unit columns in the block's own columns): thread j loads column j
+// of R while the first wavefront inverts P (its LDS traffic needs no barrier).
+constexpr int kPanelThreads = kCoarseMax;
+__global__ __launch_bounds__(kPanelThreads) void k_dense_panel(const double* __restrict__ M, int n, int p0, int nb,
+                                                               double* __restrict__ W) {
+    constexpr int NB = kDenseNB, G = 64 / NB, E = NB / G;      // lane (g, tj): rows g E .., column tj
+    __shared__ double prow[2][NB], pcol[2][NB];
+    __shared__ __align__(16) double inv[NB][NB];
+    const int tid = threadIdx.x, j = tid;
+    double r[NB];
+    if (j < n) {
+        const bool own = j >= p0 && j < p0 + nb;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) r[k] = k >= nb ? 0.0 : own ? (j - p0 == k ? 1.0 : 0.0) : M[(size_t)(p0 + k) * n + j];
+    }
+    if (tid < 64) {
+        const int g = tid / NB, tj = tid % NB;
+        double a[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = g * E + e;
+            a[e] = (i < nb && tj < nb) ? M[(size_t)(p0 + i) * n + p0 + tj] : (i == tj ? 1.0 : 0.0);
+        }
+        for (int q = 0; q < G; ++q) {
+#pragma unroll
+            for (int e0 = 0; e0 < E; ++e0) {
+                const int p = q * E + e0, b = e0 & 1;
+                if (g == q) prow[b][tj] = a[e0];
+                if (tj == p) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) pcol[b][g * E + e] = a[e];
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const double d = qdiv(1.0, pcol[b][p]);
+                const double np = tj == p ? d : prow[b][tj] * d;
+#pragma unroll
+                for (int e = 0; e < E; ++e) a[e] = fma(-pcol[b][g * E + e], np, tj == p ? 0.0 : a[e]);
+                if (g == q) a[e0] = np;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) inv[g * E + e][tj] = a[e];
+    }
+    __syncthreads();
+    if (j >= n) return;
+    for (int k = 0; k < NB; ++k) {
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < NB; ++m) s = fma(inv[k][m], r[m], s);
+        W[(size_t)k * n + j] = s;
+    }
+}
+
+// Then, one workgroup per strip of kStripRows rows: rows of the pivot block
+// become W, every other row i subtracts sum_k M_i,p0+k W_k (its own block
+// columns counted as 0).  A strip reads and writes only its own rows of M.
+constexpr int kStripRows = 4;
+__global__ __launch_bounds__(kPanelThreads) void k_dense_update(double* __restrict__ M, int n, int p0, int nb,
+                                                                const double* __restrict__ W) {
+    constexpr int NB = kDenseNB;
+    __shared__ __align__(16) double C[kStripRows][NB];
+    const int i0 = blockIdx.x * kStripRows, j = threadIdx.x;
+    double w[NB], v[kStripRows];
+    if (j < n) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) w[k] = W[(size_t)k * n + j];
+#pragma unroll
+        for (int r = 0; r < kStripRows; ++r)
+            v[r] = (i0 + r < n && (j < p0 || j >= p0 + nb)) ? M[(size_t)(i0 + r) * n + j] : 0.0;
+    }
+    if (j < kStripRows * NB) {
+        const int r = j / NB, k = j % NB;
+        C[r][k] = (i0 + r < n && k < nb) ? M[(size_t)(i0 + r) * n + p0 + k] : 0.0;
+    }
+    __syncthreads();                                    // the block's columns are read before any is written
+    if (j >= n) return;
+#pragma unroll
+    for (int r = 0; r < kStripRows; ++r) {
+        const int i = i0 + r;
+        if (i >= n) break;
+        double x = v[r];
+        if (i >= p0 && i < p0 + nb) {
+            x = W[(size_t)(i - p0) * n + j];
+        } else {
+#pragma unroll
+            for (int k = 0; k < NB; ++k) x = fma(-C[r][k], w[k], x);
+        }
+        M[(size_t)i * n + j] = x;
+    }
 }
 
 template <typename T>
@@ -1107,20 +1190,27 @@ hipError_t launch_resid_restrict_rho(const Shape& fine, double h, const RhoArgs&
     return hipGetLastError();
 }
 
-hipError_t launch_coarse_setup(const Shape& s, double h, const double* bx, const double* by,
-                               const double* bz, double* minv, hipStream_t st, const Bnd<double>* bnd,
-                               int singular) {
-    if (s.N() > (size_t)kCoarseMax) return hipErrorInvalidValue;
-    Bnd<double> b;
-    int has = 0;
-    set_bnd(b, has, bnd);
-    if (s.N() <= (size_t)kSetupLdsN)
-        hipLaunchKernelGGL(k_coarse_setup<true>, dim3(1), dim3(kSetupThreads), 0, st, s.nx, s.ny, s.nz, h, bx, by, bz,
-                           minv, b, has, singular);
-    else
-        hipLaunchKernelGGL(k_coarse_setup<false>, dim3(1), dim3(kSetupThreads), 0, st, s.nx, s.ny, s.nz, h, bx, by,
-                           bz, minv, b, has, singular);
+hipError_t launch_dense_blocks(double* M, int n, double* scratch, hipStream_t st) {
+    if (n < 1 || n > kCoarseMax) return hipErrorInvalidValue;
+    for (int p0 = 0; p0 < n; p0 += kDenseNB) {
+        const int nb = std::min(kDenseNB, n - p0);
+        hipLaunchKernelGGL(k_dense_panel, dim3(1), dim3(kPanelThreads), 0, st, M, n, p0, nb, scratch);
+        hipLaunchKernelGGL(k_dense_update, dim3((n + kStripRows - 1) / kStripRows), dim3(kPanelThreads), 0, st, M, n,
+                           p0, nb, (const double*)scratch);
+    }
     return hipGetLastError();
+}
+
+hipError_t launch_coarse_setup(const Shape& s, double h, const double* bx, const double* by, const double* bz,
+                               double* minv, double* scratch, hipStream_t st, const Bnd<double>* bnd, int singular) {
+    const CoarseRows R{s.nx, s.ny, s.nz, 1.0 / (h * h), bx, by, bz, bnd ? *bnd : Bnd<double>{}, bnd ? 1 : 0};
+    const int n = (int)s.N();
+    if (n <= kDenseReg) {
+        hipLaunchKernelGGL(k_coarse_setup, dim3(1), dim3(kDenseThreads), 0, st, R, minv, singular);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_coarse_build, dim3(n), dim3(256), 0, st, R, minv, singular);
+    return launch_dense_blocks(minv, n, scratch, st);
 }
 
 hipError_t launch_coarse_solve(int N, const double* minv, const double* f, double* phi, hipStream_t st,
@@ -1436,17 +1526,12 @@ __global__ __launch_bounds__(256) void k_avg_coeff_multi(const AvgDesc* __restri
     avg_coeff_cell<double>(a.nx, a.ny, I, J, K, cx, cy, a.bx, a.by, a.bz, a.cbx, a.cby, a.cbz);
 }
 
-// one workgroup per problem
-template <bool kLds>
-__global__ __launch_bounds__(kSetupThreads) void k_coarse_setup_multi(const CoarseDesc* __restrict__ d) {
-    __shared__ double Ms[kLds ? kSetupLdsN * kSetupLdsN : 1];
-    __shared__ double fac[kCoarseMax];
-    __shared__ double prow[kCoarseMax];
-    __shared__ double shift;
+// one workgroup per problem (at most kDenseReg unknowns each)
+__global__ __launch_bounds__(kDenseThreads) void k_coarse_setup_multi(const CoarseDesc* __restrict__ d) {
+    __shared__ DenseLds<6> L;
     const CoarseDesc c = d[blockIdx.x];
-    const Bnd<double> none{};
-    coarse_setup_body<kLds>(c.nx, c.ny, c.nz, c.h, c.bx, c.by, c.bz, c.minv, none, 0, c.singular, Ms, fac, prow,
-                            shift);
+    const CoarseRows R{c.nx, c.ny, c.nz, 1.0 / (c.h * c.h), c.bx, c.by, c.bz, Bnd<double>{}, 0};
+    coarse_setup_body(R, c.minv, c.singular, L);
 }
 
 __global__ __launch_bounds__(256) void k_elt_multi(const EltDesc* __restrict__ d, int nprob) {
@@ -1476,7 +1561,7 @@ __global__ __launch_bounds__(256) void k_correct_multi(const CorrectDesc* __rest
 int row_blocks(size_t n) { return partial_blocks(n); }
 int elt_blocks(size_t n) { return (int)((n + 255) / 256); }
 int cell_blocks(size_t n) { return (int)((n + 255) / 256); }
-bool coarse_setup_in_lds(size_t n) { return n <= (size_t)kSetupLdsN; }
+bool coarse_setup_batched(size_t n) { return n <= (size_t)kDenseReg; }
 
 hipError_t launch_coeff_rhs_multi(const CoeffDesc* d, int nprob, int blocks, hipStream_t st) {
     if (nprob <= 0 || blocks <= 0) return hipSuccess;
@@ -1502,10 +1587,9 @@ hipError_t launch_avg_coeff_multi(const AvgDesc* d, int nprob, int blocks, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_coarse_setup_multi(const CoarseDesc* d, int nprob, bool lds, hipStream_t st) {
+hipError_t launch_coarse_setup_multi(const CoarseDesc* d, int nprob, hipStream_t st) {
     if (nprob <= 0) return hipSuccess;
-    if (lds) hipLaunchKernelGGL(k_coarse_setup_multi<true>, dim3(nprob), dim3(kSetupThreads), 0, st, d);
-    else hipLaunchKernelGGL(k_coarse_setup_multi<false>, dim3(nprob), dim3(kSetupThreads), 0, st, d);
+    hipLaunchKernelGGL(k_coarse_setup_multi, dim3(nprob), dim3(kDenseThreads), 0, st, d);
     return hipGetLastError();
 }
 

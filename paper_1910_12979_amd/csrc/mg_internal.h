@@ -270,10 +270,11 @@ hipError_t launch_resid_restrict_rho(const Shape& fine, double h, const RhoArgs&
                                      const double* f, double* fc, double* phic, hipStream_t st,
                                      const Bnd<double>* bnd = nullptr);
 // Coarsest level: build M = -A + c 1 1^T (singular operator) or M = -A
-// (outflow sides, bnd given) from the coefficients and invert it in place
-// (one workgroup).  minv holds N*N doubles.
+// (outflow sides, bnd given) from the coefficients and invert it (dense.h).
+// minv holds N*N doubles; scratch (a hierarchy's partial rows) 16 N doubles,
+// used above 128 unknowns.
 hipError_t launch_coarse_setup(const Shape& s, double h, const double* bx, const double* by,
-                               const double* bz, double* minv, hipStream_t st,
+                               const double* bz, double* minv, double* scratch, hipStream_t st,
                                const Bnd<double>* bnd = nullptr, int singular = 1);
 // Coarsest level: phi = zero-mean solution of L phi = f (f's mean removed
 // first); with singular = 0 plainly phi = M^-1 (-f).
@@ -442,9 +443,9 @@ hipError_t launch_coeff_rhs_multi(const CoeffDesc* d, int nprob, int blocks, hip
 hipError_t launch_shift_norm_multi(const RowDesc* d, int nprob, int blocks, hipStream_t st);
 hipError_t launch_sum_multi(const RowDesc* d, int nprob, int blocks, hipStream_t st);
 hipError_t launch_avg_coeff_multi(const AvgDesc* d, int nprob, int blocks, hipStream_t st);
-// lds: every problem's coarsest level has at most 128 cells (inverted in LDS)
-hipError_t launch_coarse_setup_multi(const CoarseDesc* d, int nprob, bool lds, hipStream_t st);
-bool coarse_setup_in_lds(size_t n);
+// every problem's coarsest level small enough for one workgroup (coarse_setup_batched)
+hipError_t launch_coarse_setup_multi(const CoarseDesc* d, int nprob, hipStream_t st);
+bool coarse_setup_batched(size_t n);
 hipError_t launch_elt_multi(const EltDesc* d, int nprob, int blocks, hipStream_t st);
 hipError_t launch_correct_multi(const CorrectDesc* d, int nprob, int blocks, hipStream_t st);
 // Mixed precision: the scale update of launch_next_scale for many problems.

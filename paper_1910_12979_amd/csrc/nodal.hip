@@ -43,7 +43,6 @@ namespace mg {
 namespace {
 
 constexpr int kNodBlock = 256;
-constexpr int kNodSetupThreads = 1024;
 
 // One level of the nodal hierarchy: cells (nx, ny, nz), nodes (Nx, Ny, Nz);
 // arrays in T (FP64, or FP32 for the inner cycle of a mixed-precision solve).
@@ -793,55 +792,78 @@ __global__ void k_nod_avg_sigma(NodLevel F, NodLevel C) {
     C.sig[cidx3(C, i, j, k)] = 0.125 * s;
 }
 
-// Coarsest level: M = -A + c 1 1^T (c the mean diagonal), inverted in place.
-// Row n of -A: -(1/(12 h^2)) sum_c sigma_c (far corners - 4 e_n).
-__global__ __launch_bounds__(kNodSetupThreads) void k_nod_coarse_setup(NodLevel L, double* __restrict__ M) {
-    __shared__ double fac[kCoarseMax], prow[kCoarseMax];
-    __shared__ double shift;
-    const int n = (int)L.nodes();
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const double s12 = 1.0 / (12.0 * L.h * L.h);
-    for (int e = tid; e < n * n; e += nt) M[e] = 0.0;
-    __syncthreads();
-    for (int r = tid; r < n; r += nt) {
-        const int I = r % L.Nx, J = (r / L.Nx) % L.Ny, K = r / (L.Nx * L.Ny);
-        const int X[3] = {I, J, K};
+// Coarsest level: M = -A + c 1 1^T (c the mean diagonal), inverted (dense.h).
+// Row n of -A: -(1/(12 h^2)) sum_c sigma_c (far corners - 4 e_n).  Entry e of
+// the 20 off-diagonal ones: 0..11 the nodes moved in two directions (the
+// cells on both sides of the plane they lie in), 12..19 the body diagonals.
+struct NodCoarseRows {
+    NodLevel L;
+    double s12;
+    __device__ double sigma(int i, int j, int k) const {
+        return (i < 0 || j < 0 || k < 0) ? 0.0 : L.sig[cidx3(L, i, j, k)];
+    }
+    __device__ void operator()(int r, int e, double& val, int& nb) const {
+        const int X[3] = {r % L.Nx, (r / L.Nx) % L.Ny, r / (L.Nx * L.Ny)};
         const int Nn[3] = {L.Nx, L.Ny, L.Nz}, nc[3] = {L.nx, L.ny, L.nz}, per[3] = {L.px, L.py, L.pz};
-        double* row = M + (size_t)r * n;
-        for (int sz = 0; sz < 2; ++sz)
-            for (int sy = 0; sy < 2; ++sy)
-                for (int sx = 0; sx < 2; ++sx) {
-                    const int S[3] = {sx, sy, sz};
-                    int c[3];
-                    bool ok = true;
-                    for (int d = 0; d < 3; ++d) {
-                        c[d] = nod_cell(X[d], S[d], nc[d], per[d]);
-                        if (c[d] < 0) ok = false;
-                    }
-                    if (!ok) continue;
-                    const double sig = L.sig[cidx3(L, c[0], c[1], c[2])];
-                    row[r] += 4.0 * sig * s12;
-                    for (int mz = 0; mz < 2; ++mz)
-                        for (int my = 0; my < 2; ++my)
-                            for (int mx = 0; mx < 2; ++mx) {
-                                if (mx + my + mz < 2) continue;
-                                const int Mo[3] = {mx, my, mz};
-                                int m[3];
-                                for (int d = 0; d < 3; ++d)
-                                    m[d] = nod_node(X[d], Mo[d] ? (S[d] ? 1 : -1) : 0, Nn[d], per[d]);
-                                row[nidx(L, m[0], m[1], m[2])] -= sig * s12;
-                            }
-                }
+        int side[3], still = 3;                        // side per direction; `still`: the direction not moved in
+        if (e < 12) {
+            still = e >> 2;
+            const int d1 = still == 0 ? 1 : 0, d2 = still == 2 ? 1 : 2;
+            side[d1] = e & 1;
+            side[d2] = (e >> 1) & 1;
+            side[still] = 0;
+        } else {
+            side[0] = e & 1;
+            side[1] = (e >> 1) & 1;
+            side[2] = ((e - 12) >> 2) & 1;
+        }
+        int m[3], c[3];
+        bool ok = true;
+        for (int d = 0; d < 3; ++d) {
+            m[d] = d == still ? X[d] : nod_node(X[d], side[d] ? 1 : -1, Nn[d], per[d]);
+            c[d] = nod_cell(X[d], side[d], nc[d], per[d]);
+            ok = ok && m[d] >= 0;
+        }
+        val = 0.0;
+        nb = 0;
+        if (!ok) return;
+        double s = sigma(c[0], c[1], c[2]);
+        if (still < 3) {
+            c[still] = nod_cell(X[still], 1, nc[still], per[still]);
+            s += sigma(c[0], c[1], c[2]);
+        }
+        val = s * s12;
+        nb = (int)nidx(L, m[0], m[1], m[2]);
     }
-    __syncthreads();
-    if (tid == 0) {
+    __device__ double diag(int r) const {
+        const int X[3] = {r % L.Nx, (r / L.Nx) % L.Ny, r / (L.Nx * L.Ny)};
+        const int nc[3] = {L.nx, L.ny, L.nz}, per[3] = {L.px, L.py, L.pz};
         double d = 0.0;
-        for (int c = 0; c < n; ++c) d += M[(size_t)c * n + c];
-        shift = d / n;
+        for (int q = 0; q < 8; ++q)
+            d += sigma(nod_cell(X[0], q & 1, nc[0], per[0]), nod_cell(X[1], (q >> 1) & 1, nc[1], per[1]),
+                       nod_cell(X[2], q >> 2, nc[2], per[2]));
+        return 4.0 * d * s12;
     }
-    __syncthreads();
-    for (int e = tid; e < n * n; e += nt) M[e] += shift;
-    gj_invert(M, n, fac, prow);
+};
+
+__global__ __launch_bounds__(kDenseThreads) void k_nod_coarse_setup(NodCoarseRows R, double* __restrict__ M) {
+    __shared__ DenseLds<20> S;
+    dense_invert<20>((int)R.L.nodes(), 1, M, S, R, [&](int r) { return R.diag(r); });
+}
+
+__global__ __launch_bounds__(256) void k_nod_coarse_build(NodCoarseRows R, double* __restrict__ M) {
+    dense_build_row<20>((int)R.L.nodes(), 1, M, R, [&](int r) { return R.diag(r); });
+}
+
+hipError_t launch_nod_coarse_setup(const NodLevel& L, double* minv, double* scratch, hipStream_t st) {
+    const NodCoarseRows R{L, 1.0 / (12.0 * L.h * L.h)};
+    const int n = (int)L.nodes();
+    if (n <= kDenseReg) {
+        hipLaunchKernelGGL(k_nod_coarse_setup, dim3(1), dim3(kDenseThreads), 0, st, R, minv);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_nod_coarse_build, dim3(n), dim3(256), 0, st, R, minv);
+    return launch_dense_blocks(minv, n, scratch, st);
 }
 
 // U_c -= (G phi)_c / rho_c with phi - mean (mean = *phi_sum / nodes); phi_out
@@ -1395,8 +1417,7 @@ int nod_coefficients(nodal_hierarchy* H, const double* rho, const double* b0c, c
         const NodLevel& C = H->lev[l + 1];
         hipLaunchKernelGGL(k_nod_avg_sigma, grid3(C.nx, C.ny, C.nz, block), block, 0, st, H->lev[l], C);
     }
-    hipLaunchKernelGGL(k_nod_coarse_setup, dim3(1), dim3(kNodSetupThreads), 0, st, H->lev[H->nlev - 1], H->minv);
-    NHIP(hipGetLastError());
+    NHIP(launch_nod_coarse_setup(H->lev[H->nlev - 1], H->minv, H->partials, st));
     const double* q = H->host + kSlotRhs * kReduceWidth;
     if (q[3] > 0.0) {
         set_error("non-finite value in rho, beta0, U or S");
@@ -1874,8 +1895,7 @@ int nodal_level_step(nodal_handle h, int32_t level, int32_t step, int32_t arg, v
         case MG_STEP_COARSE: {
             if (has_coarse) break;
             const NodLevel& L = h->lev[level];
-            hipLaunchKernelGGL(k_nod_coarse_setup, dim3(1), dim3(kNodSetupThreads), 0, st, L, h->minv);
-            NHIP(hipGetLastError());
+            NHIP(launch_nod_coarse_setup(L, h->minv, h->partials, st));
             NHIP(launch_coarse_solve((int)L.nodes(), h->minv, L.f, L.phi, st, 1));
             return MG_OK;
         }

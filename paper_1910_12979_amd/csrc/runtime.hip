@@ -420,7 +420,7 @@ int build_coefficients(mg_hierarchy* H, const double* rho, const double* b0c, co
     }
     Level& Lc = H->lev[H->nlev - 1];
     const Bnd<double> cb = Lc.bnd64();
-    HIPCHK(launch_coarse_setup(shape_of(Lc), Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, st,
+    HIPCHK(launch_coarse_setup(shape_of(Lc), Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, H->partials, st,
                                Lc.has_bnd ? &cb : nullptr, H->singular ? 1 : 0));
     if (mixed) {
         // FP32 coefficient mirrors of level 0 (the coarse ones came with the
@@ -1447,8 +1447,8 @@ int level_step(mg_hierarchy* H, int l, int step, int arg, hipStream_t st) {
             }
             {
                 const Bnd<double> cb = F.bnd64();
-                HIPCHK(launch_coarse_setup(s, F.h, F.d.bx, F.d.by, F.d.bz, H->minv, st, F.has_bnd ? &cb : nullptr,
-                                           H->singular ? 1 : 0));
+                HIPCHK(launch_coarse_setup(s, F.h, F.d.bx, F.d.by, F.d.bz, H->minv, H->partials, st,
+                                           F.has_bnd ? &cb : nullptr, H->singular ? 1 : 0));
                 HIPCHK(launch_coarse_solve((int)F.N, H->minv, F.d.f, F.d.phi, st, H->singular ? 1 : 0));
             }
             break;
