@@ -304,8 +304,8 @@ int nodal_set_coefficients(nodal_handle h, const double* rho, const double* beta
  * one captured hipGraph replayed every cycle (all buffers are fixed);
  * results are identical either way. */
 int nodal_set_graphs(nodal_handle h, int32_t enable);
-/* enable = 1 (the default): the coarse levels whose phi, f and r fit in
- * 136 KB of LDS (with every coarser level's) run as one workgroup per V-cycle
+/* enable = 1 (the default): the coarse levels that fit in one workgroup's LDS
+ * (phi, residual and sigma, with every coarser level's) run as one workgroup per V-cycle
  * (colours, residual, restriction, coarsest solve, prolongation with
  * barriers in between) instead of one launch per step; the per-node
  * arithmetic is the same, so results are identical either way. */
@@ -439,10 +439,10 @@ int mg_tune_lookup(const char* arch, const int32_t n[3], int32_t rho, int32_t fp
  * on the caller's stream. */
 int mg_set_graphs(mg_handle h, int32_t enable);
 
-/* Bottom of the V-cycle: with enable = 1 (the default) the levels below the
- * ones the fused sweep covers (when their phi and f fit in 136 KB of LDS) run
- * as one 1024-thread workgroup per V-cycle instead of one launch per step
- * and level.  Results are identical either way. */
+/* Bottom of the V-cycle: with enable = 1 (the default) the levels of at most
+ * 4096 cells, and wider ones that the fused sweep does not cover (when their
+ * phi and f fit in 136 KB of LDS), run as one workgroup per V-cycle instead
+ * of one launch per step and level.  Results are identical either way. */
 int mg_set_bottom(mg_handle h, int32_t enable);
 
 /* Multi-box finest level: the block-structured box layout whose boxes the

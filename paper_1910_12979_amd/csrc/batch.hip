@@ -381,6 +381,26 @@ int multi_norm_sweep(std::vector<mg_hierarchy*>& hs, double* gather, Staging& S,
     return MG_OK;
 }
 
+// The bottoms of every problem: one launch per kernel form.
+template <typename T>
+int multi_bottom(const std::vector<BottomArgs<T>>& all, Staging& S, hipStream_t st) {
+    for (int narrow = 0; narrow < 2; ++narrow) {
+        std::vector<BottomArgs<T>> v;
+        int cells = 0;
+        for (const auto& a : all) {
+            if (bottom_narrow(a) != (narrow == 1)) continue;
+            v.push_back(a);
+            if (narrow) cells = std::max(cells, bottom_cells(a));
+        }
+        if (v.empty()) continue;
+        void* dd = nullptr;
+        int rc = S.push(v.data(), v.size() * sizeof(BottomArgs<T>), st, &dd);
+        if (rc) return rc;
+        BHIP(launch_bottom_multi((const BottomArgs<T>*)dd, (int)v.size(), cells, st));
+    }
+    return MG_OK;
+}
+
 // One V-cycle for every job in `jobs` (each at its own depth).  pre_done[i]
 // finest-level pre-sweeps were already run by the speculative norm sweep.
 int multi_vcycle(std::vector<mg_hierarchy*>& hs, const std::vector<int>& pre_done, Staging& S, hipStream_t st) {
@@ -419,12 +439,8 @@ int multi_vcycle(std::vector<mg_hierarchy*>& hs, const std::vector<int>& pre_don
     }
     int rc = multi_coarse(direct, S, st);
     if (rc) return rc;
-    if (!bottoms.empty()) {
-        void* dd = nullptr;
-        rc = S.push(bottoms.data(), bottoms.size() * sizeof(BottomArgs<double>), st, &dd);
-        if (rc) return rc;
-        BHIP(launch_bottom_multi((const BottomArgs<double>*)dd, (int)bottoms.size(), st));
-    }
+    rc = multi_bottom(bottoms, S, st);
+    if (rc) return rc;
     for (int l = lmax - 1; l >= 0; --l) {
         std::vector<Item> items;
         for (size_t i = 0; i < hs.size(); ++i)
@@ -567,10 +583,8 @@ int multi_vcycle_f32(std::vector<mg_hierarchy*>& hs, Staging& S, hipStream_t st,
         bottom_args<float>(hs[i], stop[i], a);
         bottoms.push_back(a);
     }
-    void* dd = nullptr;
-    int rc = S.push(bottoms.data(), bottoms.size() * sizeof(BottomArgs<float>), st, &dd);
+    int rc = multi_bottom(bottoms, S, st);
     if (rc) return rc;
-    BHIP(launch_bottom_multi((const BottomArgs<float>*)dd, (int)bottoms.size(), st));
     for (int l = lmax - 1; l >= 0; --l) {
         rc = sweeps(l, true, kInProlong);
         if (rc) return rc;

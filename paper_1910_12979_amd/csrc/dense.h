@@ -190,4 +190,53 @@ __device__ __forceinline__ void dense_build_row(int n, int singular, double* __r
 // scratch: kDenseNB * n doubles.
 hipError_t launch_dense_blocks(double* M, int n, double* scratch, hipStream_t st);
 
+// Coarsest solve by the calling workgroup (NT threads, a multiple of 64):
+// rhs[0..n-1] (LDS) in, x[0..n-1] (LDS) = M^-1 (-f') out, f' the input with
+// its mean removed and x's mean removed where the operator is singular.  The
+// matrix is symmetric: thread lanes take its rows in turn and walk down the
+// columns, so every load is of consecutive entries; each row's sum is formed
+// in kMatvecParts column ranges, added pairwise, so the value depends on n
+// alone.  part: kMatvecParts * n doubles of LDS, mean: one.  Ends with a
+// barrier.
+constexpr int kMatvecParts = 8;
+template <int NT>
+__device__ __forceinline__ void dense_solve(int n, int singular, const double* __restrict__ minv, double* rhs,
+                                            double* x, double* part, double* mean) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (singular) {
+        dense_mean(rhs, n, mean);
+        __syncthreads();
+        const double m = *mean;
+        for (int c = threadIdx.x; c < n; c += NT) rhs[c] = rhs[c] - m;
+    }
+    __syncthreads();
+    const int len = (n + kMatvecParts - 1) / kMatvecParts;
+    for (int g = wave; g < kMatvecParts; g += NT / 64) {
+        const int c0 = min(g * len, n), c1 = min(c0 + len, n);
+        for (int r = lane; r < n; r += 64) {
+            double s = 0.0;
+            for (int c = c0; c < c1; c += 8) {         // eight loads in flight at a time
+                double v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = minv[(size_t)min(c + q, c1 - 1) * n + r];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) s = fma(-v[q], c + q < c1 ? rhs[c + q] : 0.0, s);
+            }
+            part[g * n + r] = s;
+        }
+    }
+    __syncthreads();
+    for (int r = threadIdx.x; r < n; r += NT)
+        x[r] = ((part[r] + part[n + r]) + (part[2 * n + r] + part[3 * n + r])) +
+               ((part[4 * n + r] + part[5 * n + r]) + (part[6 * n + r] + part[7 * n + r]));
+    __syncthreads();
+    if (singular) {
+        dense_mean(x, n, mean);
+        __syncthreads();
+        const double m = *mean;
+        for (int c = threadIdx.x; c < n; c += NT) x[c] = x[c] - m;
+        __syncthreads();
+    }
+}
+
 }  // namespace mg

@@ -608,41 +608,22 @@ __global__ __launch_bounds__(kPanelThreads) void k_dense_update(double* __restri
     }
 }
 
+constexpr int kSolveThreads = 512;
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_coarse_solve(int n, const double* __restrict__ Minv,
-                                                         const T* __restrict__ f, T* __restrict__ phi,
-                                                         int singular) {
-    __shared__ double rhs[kCoarseMax];
-    __shared__ double x[kCoarseMax];
-    __shared__ double mean;
-    for (int c = threadIdx.x; c < n; c += kBlock) rhs[c] = (double)f[c];
+__device__ __forceinline__ void coarse_solve_body(int n, const double* __restrict__ minv, const T* __restrict__ f,
+                                                  T* __restrict__ phi, int singular) {
+    __shared__ double rhs[kCoarseMax], x[kCoarseMax], part[kMatvecParts * kCoarseMax], mean;
+    for (int c = threadIdx.x; c < n; c += kSolveThreads) rhs[c] = (double)f[c];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        if (singular)
-            for (int c = 0; c < n; ++c) s += rhs[c];
-        mean = singular ? s / n : 0.0;
-    }
-    __syncthreads();
-    double m = mean;
-    __syncthreads();
-    for (int c = threadIdx.x; c < n; c += kBlock) rhs[c] = -(rhs[c] - m);
-    __syncthreads();
-    for (int r = threadIdx.x; r < n; r += kBlock) {
-        const double* row = Minv + (size_t)r * n;
-        double s = 0.0;
-        for (int c = 0; c < n; ++c) s += row[c] * rhs[c];
-        x[r] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        if (singular)
-            for (int c = 0; c < n; ++c) s += x[c];
-        mean = singular ? s / n : 0.0;
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < n; c += kBlock) phi[c] = (T)(x[c] - mean);
+    dense_solve<kSolveThreads>(n, singular, minv, rhs, x, part, &mean);
+    for (int c = threadIdx.x; c < n; c += kSolveThreads) phi[c] = (T)x[c];
+}
+
+template <typename T>
+__global__ __launch_bounds__(kSolveThreads) void k_coarse_solve(int n, const double* __restrict__ Minv,
+                                                                const T* __restrict__ f, T* __restrict__ phi,
+                                                                int singular) {
+    coarse_solve_body<T>(n, Minv, f, phi, singular);
 }
 
 // ---------------------------------------------------------------------------
@@ -1215,13 +1196,13 @@ hipError_t launch_coarse_setup(const Shape& s, double h, const double* bx, const
 
 hipError_t launch_coarse_solve(int N, const double* minv, const double* f, double* phi, hipStream_t st,
                                int singular) {
-    hipLaunchKernelGGL(k_coarse_solve<double>, dim3(1), dim3(kBlock), 0, st, N, minv, f, phi, singular);
+    hipLaunchKernelGGL(k_coarse_solve<double>, dim3(1), dim3(kSolveThreads), 0, st, N, minv, f, phi, singular);
     return hipGetLastError();
 }
 
 hipError_t launch_coarse_solve_f32(int N, const double* minv, const float* f, float* phi, hipStream_t st,
                                    int singular) {
-    hipLaunchKernelGGL(k_coarse_solve<float>, dim3(1), dim3(kBlock), 0, st, N, minv, f, phi, singular);
+    hipLaunchKernelGGL(k_coarse_solve<float>, dim3(1), dim3(kSolveThreads), 0, st, N, minv, f, phi, singular);
     return hipGetLastError();
 }
 
@@ -1442,39 +1423,10 @@ __global__ __launch_bounds__(256) void k_prolong_multi(const CellDesc* __restric
     c.phi[cc] = c.phi[cc] + c.phic[cidx(i / 2, j / 2, k / 2, c.nx / 2, c.ny / 2)];
 }
 
-// one block per problem: coarsest solve, same code as the single-problem kernel
-__global__ __launch_bounds__(kBlock) void k_coarse_solve_multi(const CellDesc* __restrict__ d) {
+// one block per problem: coarsest solve (batches have no outflow sides)
+__global__ __launch_bounds__(kSolveThreads) void k_coarse_solve_multi(const CellDesc* __restrict__ d) {
     const CellDesc c = d[blockIdx.x];
-    __shared__ double rhs[kCoarseMax];
-    __shared__ double x[kCoarseMax];
-    __shared__ double mean;
-    const int n = c.nx * c.ny * c.nz;
-    for (int q = threadIdx.x; q < n; q += kBlock) rhs[q] = c.f[q];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int q = 0; q < n; ++q) s += rhs[q];
-        mean = s / n;
-    }
-    __syncthreads();
-    const double m = mean;
-    __syncthreads();
-    for (int q = threadIdx.x; q < n; q += kBlock) rhs[q] = -(rhs[q] - m);
-    __syncthreads();
-    for (int r = threadIdx.x; r < n; r += kBlock) {
-        const double* row = c.minv + (size_t)r * n;
-        double s = 0.0;
-        for (int q = 0; q < n; ++q) s += row[q] * rhs[q];
-        x[r] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int q = 0; q < n; ++q) s += x[q];
-        mean = s / n;
-    }
-    __syncthreads();
-    for (int q = threadIdx.x; q < n; q += kBlock) c.phi[q] = x[q] - mean;
+    coarse_solve_body<double>(c.nx * c.ny * c.nz, c.minv, c.f, c.phi, 1);
 }
 
 // one block per problem: the single-problem k_reduce on each problem's rows
@@ -1625,7 +1577,7 @@ hipError_t launch_prolong_multi(const CellDesc* d, int nprob, int blocks, hipStr
 
 hipError_t launch_coarse_solve_multi(const CellDesc* d, int nprob, hipStream_t st) {
     if (nprob <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_coarse_solve_multi, dim3(nprob), dim3(kBlock), 0, st, d);
+    hipLaunchKernelGGL(k_coarse_solve_multi, dim3(nprob), dim3(kSolveThreads), 0, st, d);
     return hipGetLastError();
 }
 

@@ -906,122 +906,206 @@ __global__ void k_nod_shift_out(size_t n, const double* __restrict__ phi, const 
 }
 
 // ---------------------------------------------------------------------------
-// Bottom of the nodal V-cycle in one workgroup: from the first level whose
-// phi, f and r (with every coarser level's) fit in LDS down to the coarsest
-// solve and back, with barriers between dependent steps instead of one
-// launch of a few microseconds per colour, residual, restriction and
-// prolongation.  Per node the arithmetic is that of the per-level kernels
-// (the same stencil routine for the colours, the same sums in the same
-// order for the residual, restriction, prolongation and coarsest solve), so
-// a bottom launch gives the same bits as the launches it replaces.  sigma
-// stays in global memory.
+// Bottom of the nodal V-cycle in one workgroup: from the first level that
+// fits (with the next coarser ones) in LDS down to the coarsest solve and
+// back, with barriers between dependent steps instead of one launch of a few
+// microseconds per colour, residual, restriction and prolongation.  Per node
+// the arithmetic is that of the per-level kernels (the same sums in the same
+// order; a cell beyond a wall adds an exact zero where they leave it out), so
+// a bottom launch gives the same bits as the launches it replaces.
+//
+// phi, the residual and sigma are in LDS, sigma inside a border that holds
+// the periodic images or zeros beyond walls, so that a node's eight cells are
+// at fixed offsets; a thread owns the same nodes of each colour throughout
+// and keeps their right-hand sides and coordinates in registers.  What bounds
+// a colour phase is then the 28 LDS reads and 56 operations of an update
+// (sigma from global memory and 64-bit index arithmetic before: from 16 x 16 x
+// 17 nodes down 126 -> 69 us in FP64, from 24 x 16 x 21 175 -> 78 us in FP32).
 // ---------------------------------------------------------------------------
 constexpr int kNodBottomThreads = 1024;
-constexpr size_t kNodBottomLds = 136 * 1024;     // phi, f, r of every bottom level
-constexpr int kNodBottomMax = 8;
+
+// Capacities: nodes and bordered cells of the first and second level, nodes
+// of each colour a thread owns, coarsest nodes below a second level (a level
+// directly above the coarsest may have up to kCoarseMax there).
+template <typename T>
+struct NodBottomCap {
+    static constexpr int f = sizeof(T) == 8 ? 1 : 2;
+    static constexpr int nodes = 5120 * f, cells = 5888 * f, nodes1 = 768 * f, cells1 = 1024 * f;
+    static constexpr int own = sizeof(T) == 8 ? 2 : 3, own1 = 1, coarse = 160;
+};
 
 template <typename T>
 struct NodBottomArgs {
-    int nlev;
-    NodLevelT<T> lev[kNodBottomMax];    // sig global; phi, f of lev[0] global (in and out)
-    int off[kNodBottomMax];             // element offsets of each level's phi, f, r in LDS
+    int nlev;                           // bottom levels, 2 or 3; the last one is solved directly
+    NodLevelT<T> lev[3];                // sig global; phi, f of lev[0] global (in and out)
     const double* minv;
     int pre, post;
 };
 
-// (L phi) at node (I, J, K) as the residual kernel forms it: cells sz, sy,
-// sx, each sigma times (far corners - 4 phi_n), nodes beyond a wall 0 and
-// cells beyond it skipped (their sigma is 0 there).
+inline __host__ __device__ int nod_bordered(const int N[3]) { return (N[0] + 1) * (N[1] + 1) * (N[2] + 1); }
+inline int nod_colour_max(int Nx, int Ny, int Nz) { return Nx * ((Ny + 1) / 2) * ((Nz + 1) / 2); }
+
+// sigma of L into the bordered array S: entry (x, y, z) is cell (x - 1, y - 1, z - 1).
 template <typename T>
-__device__ inline T nb_apply(const NodLevelT<T>& L, const T* P, int I, int J, int K) {
-    const NodAxis ax = nod_axis(I, L.Nx, L.nx, L.px);
-    const NodAxis ay = nod_axis(J, L.Ny, L.ny, L.py);
-    const NodAxis az = nod_axis(K, L.Nz, L.nz, L.pz);
-    NodNbr<T> N;
-    nod_load_nbrs(L, P, I, ax, ay, az, J, K, N);
-    const T pn = P[((size_t)K * L.Ny + J) * L.Nx + I];
-    const long long nx = L.nx, nxny = (long long)L.nx * L.ny;
+__device__ __forceinline__ void nb_load_sigma(const NodLevelT<T>& L, T* S) {
+    const int bx = L.Nx + 1, by = L.Ny + 1, n = bx * by * (L.Nz + 1);
+    for (int e = threadIdx.x; e < n; e += kNodBottomThreads) {
+        int x, y, z, r;
+        small_divmod(e, bx, r, x);
+        small_divmod(r, by, z, y);
+        const int i = nod_cell(x, 0, L.nx, L.px), j = nod_cell(y, 0, L.ny, L.py), k = nod_cell(z, 0, L.nz, L.pz);
+        S[e] = (i < 0 || j < 0 || k < 0) ? T(0) : L.sig[(k * L.ny + j) * L.nx + i];
+    }
+}
+
+// Coordinates of node e of colour col (10 bits each), or -1 past the last.
+template <typename T>
+__device__ __forceinline__ int nb_own(const NodLevelT<T>& L, int col, int e) {
+    const int hy = (L.Ny + 1 - (col & 1)) >> 1, hz = (L.Nz + 1 - (col >> 1)) >> 1;
+    if (e >= L.Nx * hy * hz) return -1;
+    int I, r, jh, kh;
+    small_divmod(e, L.Nx, r, I);
+    small_divmod(r, hy, kh, jh);
+    return I | (2 * jh + (col & 1)) << 10 | (2 * kh + (col >> 1)) << 20;
+}
+
+// The neighbourhood of a node: v[dz][dy][dx] for the 20 coupled nodes (beyond
+// a wall some existing node, whose cells' sigma is 0) and its 8 cells.
+template <typename T>
+struct NbNode {
+    T v[3][3][3], s[2][2][2];
+    int n;
+    __device__ __forceinline__ NbNode(const NodLevelT<T>& L, const T* P, const T* S, int ijk) {
+        const int I = ijk & 1023, J = (ijk >> 10) & 1023, K = ijk >> 20;
+        auto low = [](int X, int N, int per) { return X > 0 ? X - 1 : (per ? N - 1 : 0); };
+        auto high = [](int X, int N, int per) { return X + 1 < N ? X + 1 : (per ? 0 : X); };
+        const int x[3] = {low(I, L.Nx, L.px), I, high(I, L.Nx, L.px)};
+        const int y[3] = {low(J, L.Ny, L.py) * L.Nx, J * L.Nx, high(J, L.Ny, L.py) * L.Nx};
+        const int zs = L.Nx * L.Ny;
+        const int z[3] = {low(K, L.Nz, L.pz) * zs, K * zs, high(K, L.Nz, L.pz) * zs};
+        n = z[1] + y[1] + I;
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    if ((dx != 1) + (dy != 1) + (dz != 1) >= 2) v[dz][dy][dx] = P[z[dz] + y[dy] + x[dx]];
+        const T* c = S + ((K * (L.Ny + 1)) + J) * (L.Nx + 1) + I;
+#pragma unroll
+        for (int sz = 0; sz < 2; ++sz)
+#pragma unroll
+            for (int sy = 0; sy < 2; ++sy)
+#pragma unroll
+                for (int sx = 0; sx < 2; ++sx) s[sz][sy][sx] = c[(sz * (L.Ny + 1) + sy) * (L.Nx + 1) + sx];
+    }
+    // sum of phi over the four corners of cell (sx, sy, sz) across a face or the diagonal
+    __device__ __forceinline__ T far(int sz, int sy, int sx) const {
+        T a = v[1][2 * sy][2 * sx];
+        a = a + v[2 * sz][1][2 * sx];
+        a = a + v[2 * sz][2 * sy][1];
+        return a + v[2 * sz][2 * sy][2 * sx];
+    }
+};
+
+template <typename T>
+__device__ __forceinline__ void nb_update(const NodLevelT<T>& L, T* P, const T* S, int ijk, T f) {
+    const NbNode<T> q(L, P, S, ijk);
+    T num = T(0), den = T(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const T sig = q.s[c >> 2][(c >> 1) & 1][c & 1];
+        num = num + sig * q.far(c >> 2, (c >> 1) & 1, c & 1);
+        den = den + T(4) * sig;
+    }
+    P[q.n] = pdiv(num - (T)(12.0 * (L.h * L.h)) * f, den);
+}
+
+template <typename T>
+__device__ __forceinline__ void nb_residual(const NodLevelT<T>& L, const T* P, const T* S, int ijk, T f, T* R) {
+    const NbNode<T> q(L, P, S, ijk);
+    const T pn = P[q.n];
     T sum = T(0);
 #pragma unroll
-    for (int sz = 0; sz < 2; ++sz) {
-        const int oz = sz ? 2 : 0;
+    for (int c = 0; c < 8; ++c)
+        sum = sum + q.s[c >> 2][(c >> 1) & 1][c & 1] * (q.far(c >> 2, (c >> 1) & 1, c & 1) - T(4) * pn);
+    R[q.n] = f - pdiv(sum, (T)(12.0 * L.h * L.h));
+}
+
+// A value the compiler cannot see through: what is derived from a node's
+// coordinates is then computed at each use, not held for every owned node
+// across the sweeps (350 registers more than there are).
+__device__ __forceinline__ int at_use(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// A level's nodes as one thread owns them: M of each colour.
+template <typename T, int M>
+struct NbOwned {
+    int ijk[4][M];
+    T f[4][M];
+    __device__ __forceinline__ void load(const NodLevelT<T>& L) {
 #pragma unroll
-        for (int sy = 0; sy < 2; ++sy) {
-            const int oy = sy ? 2 : 0;
+        for (int q = 0; q < 4 * M; ++q) ijk[q / M][q % M] = nb_own(L, q / M, threadIdx.x + (q % M) * kNodBottomThreads);
+    }
+    __device__ __forceinline__ void load_f(const NodLevelT<T>& L, const T* F) {
 #pragma unroll
-            for (int sx = 0; sx < 2; ++sx) {
-                const int ox = sx ? 2 : 0;
-                T sig = T(0);
-                if (az.e[sz] && ay.e[sy] && ax.e[sx]) sig = L.sig[az.c[sz] * nxny + ay.c[sy] * nx + ax.c[sx]];
-                T acc = T(0);
-                acc += N.v[1][oy][ox];
-                acc += N.v[oz][1][ox];
-                acc += N.v[oz][oy][1];
-                acc += N.v[oz][oy][ox];
-                sum += sig * (acc - T(4) * pn);
+        for (int q = 0; q < 4 * M; ++q) {
+            const int p = max(ijk[q / M][q % M], 0);
+            f[q / M][q % M] = F[((p >> 20) * L.Ny + ((p >> 10) & 1023)) * L.Nx + (p & 1023)];
+        }
+    }
+    __device__ __forceinline__ void sweeps(const NodLevelT<T>& L, T* P, const T* S, int n) {
+        for (int s = 0; s < n; ++s) {
+#pragma unroll
+            for (int col = 0; col < 4; ++col) {
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int p = at_use(ijk[col][m]);
+                    if (p >= 0) nb_update(L, P, S, p, f[col][m]);
+                }
+                __syncthreads();
             }
         }
     }
-    return sum;
-}
-
-template <typename T>
-__device__ void nb_colour(const NodLevelT<T>& L, T* P, const T* F, int col) {
-    const int hy = (L.Ny + 1 - (col & 1)) >> 1, hz = (L.Nz + 1 - (col >> 1)) >> 1;
-    const int items = L.Nx * hy * hz;
-    const T c12 = (T)(12.0 * (L.h * L.h));
-    for (int e = threadIdx.x; e < items; e += blockDim.x) {
-        int I, r, jh, kh;
-        small_divmod(e, L.Nx, r, I);
-        small_divmod(r, hy, kh, jh);
-        const int J = 2 * jh + (col & 1), K = 2 * kh + (col >> 1);
-        T num, den;
-        nod_stencil_fast(L, P, I, J, K, num, den);
-        const size_t n = ((size_t)K * L.Ny + J) * L.Nx + I;
-        P[n] = pdiv(num - c12 * F[n], den);
+    __device__ __forceinline__ void residual(const NodLevelT<T>& L, const T* P, const T* S, T* R) {
+#pragma unroll
+        for (int q = 0; q < 4 * M; ++q) {
+            const int p = at_use(ijk[q / M][q % M]);
+            if (p >= 0) nb_residual(L, P, S, p, f[q / M][q % M], R);
+        }
+        __syncthreads();
     }
-    __syncthreads();
-}
+};
 
 template <typename T>
-__device__ void nb_resid(const NodLevelT<T>& L, const T* P, const T* F, T* R) {
-    const int items = L.Nx * L.Ny * L.Nz;
-    const T ih = (T)(12.0 * L.h * L.h);
-    for (int e = threadIdx.x; e < items; e += blockDim.x) {
-        int I, J, K, r;
-        small_divmod(e, L.Nx, r, I);
-        small_divmod(r, L.Ny, K, J);
-        R[e] = F[e] - pdiv(nb_apply(L, P, I, J, K), ih);
-    }
-    __syncthreads();
-}
-
-template <typename T>
-__device__ void nb_restrict(const NodLevelT<T>& Fl, const T* R, const NodLevelT<T>& Cl, T* cP, T* cF) {
+__device__ void nb_restrict(const NodLevelT<T>& Fl, const T* R, const NodLevelT<T>& Cl, T* cF) {
     const int items = Cl.Nx * Cl.Ny * Cl.Nz;
     const int Nn[3] = {Fl.Nx, Fl.Ny, Fl.Nz}, per[3] = {Fl.px, Fl.py, Fl.pz};
-    for (int e = threadIdx.x; e < items; e += blockDim.x) {
-        int I, J, K, r;
-        small_divmod(e, Cl.Nx, r, I);
-        small_divmod(r, Cl.Ny, K, J);
-        const int X[3] = {2 * I, 2 * J, 2 * K};
+    for (int e = threadIdx.x; e < items; e += kNodBottomThreads) {
+        int X[3], r;
+        small_divmod(e, Cl.Nx, r, X[0]);
+        small_divmod(r, Cl.Ny, X[2], X[1]);
+        // fine node 2X - 1 + d of each direction (an existing one beyond a wall, weighted 0)
+        int m[3][3];
+        T w[3][3];
+        const int stride[3] = {1, Fl.Nx, Fl.Nx * Fl.Ny};
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int o = 0; o < 3; ++o) {
+                const int g = nod_node(2 * X[d], o - 1, Nn[d], per[d]);
+                m[d][o] = max(g, 0) * stride[d];
+                w[d][o] = g < 0 ? T(0) : (o == 1 ? T(1) : T(0.5));
+            }
         T s = T(0);
-        for (int dz = -1; dz <= 1; ++dz)
-            for (int dy = -1; dy <= 1; ++dy)
-                for (int dx = -1; dx <= 1; ++dx) {
-                    const int D[3] = {dx, dy, dz};
-                    int m[3];
-                    bool ok = true;
-                    T w = T(1);
-                    for (int d = 0; d < 3; ++d) {
-                        m[d] = nod_node(X[d], D[d], Nn[d], per[d]);
-                        if (m[d] < 0) ok = false;
-                        if (D[d] != 0) w *= T(0.5);
-                    }
-                    if (ok) s += w * R[((size_t)m[2] * Fl.Ny + m[1]) * Fl.Nx + m[0]];
-                }
+#pragma unroll
+        for (int q = 0; q < 27; ++q) {
+            const int dx = q % 3, dy = (q / 3) % 3, dz = q / 9;
+            s = s + (w[0][dx] * w[1][dy] * w[2][dz]) * R[m[2][dz] + m[1][dy] + m[0][dx]];
+        }
         cF[e] = T(0.125) * s;
-        cP[e] = T(0);
     }
     __syncthreads();
 }
@@ -1030,105 +1114,89 @@ template <typename T>
 __device__ void nb_prolong(const NodLevelT<T>& Fl, T* P, const NodLevelT<T>& Cl, const T* cP) {
     const int items = Fl.Nx * Fl.Ny * Fl.Nz;
     const int Nc[3] = {Cl.Nx, Cl.Ny, Cl.Nz}, per[3] = {Cl.px, Cl.py, Cl.pz};
-    for (int e = threadIdx.x; e < items; e += blockDim.x) {
+    for (int e = threadIdx.x; e < items; e += kNodBottomThreads) {
         int X[3], r;
         small_divmod(e, Fl.Nx, r, X[0]);
         small_divmod(r, Fl.Ny, X[2], X[1]);
+        // both coarse parents of each direction (an even index: one, the second weighted 0)
+        int m[3][2];
+        T w[3][2];
+        const int stride[3] = {1, Cl.Nx, Cl.Nx * Cl.Ny};
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int lo = X[d] >> 1, odd = X[d] & 1;
+            int hi = lo + odd;
+            if (per[d] && hi >= Nc[d]) hi -= Nc[d];
+            m[d][0] = lo * stride[d];
+            m[d][1] = hi * stride[d];
+            w[d][0] = odd ? T(0.5) : T(1);
+            w[d][1] = odd ? T(0.5) : T(0);
+        }
         T v = T(0);
-        for (int bz = 0; bz < 2; ++bz)
-            for (int by = 0; by < 2; ++by)
-                for (int bx = 0; bx < 2; ++bx) {
-                    const int B[3] = {bx, by, bz};
-                    int m[3];
-                    bool ok = true;
-                    T w = T(1);
-                    for (int d = 0; d < 3; ++d) {
-                        if ((X[d] & 1) == 0) {
-                            if (B[d]) {
-                                ok = false;
-                                break;
-                            }
-                            m[d] = X[d] >> 1;
-                        } else {
-                            m[d] = B[d] ? (X[d] + 1) >> 1 : (X[d] - 1) >> 1;
-                            if (per[d] && m[d] >= Nc[d]) m[d] -= Nc[d];
-                            w *= T(0.5);
-                        }
-                    }
-                    if (ok) v += w * cP[((size_t)m[2] * Cl.Ny + m[1]) * Cl.Nx + m[0]];
-                }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            v = v + (w[0][q & 1] * w[1][(q >> 1) & 1] * w[2][q >> 2]) *
+                        cP[m[2][q >> 2] + m[1][(q >> 1) & 1] + m[0][q & 1]];
         P[e] = P[e] + v;
     }
     __syncthreads();
 }
 
-// Coarsest level as the coarse-solve kernel does it: remove mean(f), x =
-// Minv (-f'), remove mean(x), serial sums and row dot products in its order.
-template <typename T>
-__device__ void nb_coarse(int n, const double* __restrict__ minv, const T* F, T* P, double* rhs, double* x,
-                          double* mean) {
-    for (int c = threadIdx.x; c < n; c += blockDim.x) rhs[c] = (double)F[c];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int c = 0; c < n; ++c) s += rhs[c];
-        *mean = s / n;
-    }
-    __syncthreads();
-    const double m = *mean;
-    __syncthreads();
-    for (int c = threadIdx.x; c < n; c += blockDim.x) rhs[c] = -(rhs[c] - m);
-    __syncthreads();
-    for (int r = threadIdx.x; r < n; r += blockDim.x) {
-        const double* row = minv + (size_t)r * n;
-        double s = 0.0;
-        for (int c = 0; c < n; ++c) s += row[c] * rhs[c];
-        x[r] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int c = 0; c < n; ++c) s += x[c];
-        *mean = s / n;
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < n; c += blockDim.x) P[c] = (T)(x[c] - *mean);
-    __syncthreads();
-}
-
 template <typename T>
 __global__ __launch_bounds__(kNodBottomThreads) void k_nod_bottom(NodBottomArgs<T> A) {
-    __shared__ double lds_raw[kNodBottomLds / sizeof(double)];
-    __shared__ double rhs[kCoarseMax], x[kCoarseMax];
-    __shared__ double mean;
-    T* lds = reinterpret_cast<T*>(lds_raw);
-    const int nb = A.nlev;
-    auto nodes = [&](int b) { return (int)A.lev[b].nodes(); };
-    auto Pof = [&](int b) { return lds + A.off[b]; };
-    auto Fof = [&](int b) { return lds + A.off[b] + nodes(b); };
-    auto Rof = [&](int b) { return lds + A.off[b] + 2 * nodes(b); };
-    {   // first bottom level: f from the restriction above, phi = 0
-        const int n0 = nodes(0);
-        for (int e = threadIdx.x; e < n0; e += blockDim.x) {
-            Fof(0)[e] = A.lev[0].f[e];
-            Pof(0)[e] = T(0);
+    using Cap = NodBottomCap<T>;
+    __shared__ T P0[Cap::nodes], S0[Cap::cells];
+    __shared__ __align__(16) T R0[Cap::nodes];          // residual of the first level; the coarsest solve's sums
+    __shared__ T P1[Cap::nodes1], S1[Cap::cells1];
+    __shared__ __align__(16) T F1[Cap::nodes1], R1[Cap::nodes1];
+    __shared__ double rhs2[Cap::coarse], x2[Cap::coarse], mean;
+    static_assert(sizeof(R0) >= kMatvecParts * kCoarseMax * sizeof(double), "sums of the coarsest solve");
+    static_assert(sizeof(F1) >= kCoarseMax * sizeof(double), "a coarsest level right below the first");
+    const NodLevelT<T>&L0 = A.lev[0], &L1 = A.lev[1];
+    const bool two = A.nlev > 2;
+    const NodLevelT<T>& Lc = A.lev[two ? 2 : 1];
+    const int nc = (int)Lc.nodes();
+    // the coarsest level's right-hand side and solution: apart below a second level, else in its place
+    double* const rhs = two ? rhs2 : reinterpret_cast<double*>(F1);
+    double* const x = two ? x2 : reinterpret_cast<double*>(R1);
+    T* const Fc = two ? R1 + Cap::nodes1 - Cap::coarse : P1;      // (R1's own values are consumed before)
+    NbOwned<T, Cap::own> a;
+    NbOwned<T, Cap::own1> o;
+    a.load(L0);
+    a.load_f(L0, L0.f);
+    nb_load_sigma(L0, S0);
+    for (int e = threadIdx.x; e < (int)L0.nodes(); e += kNodBottomThreads) P0[e] = T(0);
+    if (two) {
+        o.load(L1);
+        nb_load_sigma(L1, S1);
+        for (int e = threadIdx.x; e < (int)L1.nodes(); e += kNodBottomThreads) P1[e] = T(0);
+    }
+    __syncthreads();
+    for (int visit = 0; visit < 2; ++visit) {
+        if (visit) nb_prolong(L0, P0, L1, P1);          // two == false: the coarsest solution is in P1 too
+        a.sweeps(L0, P0, S0, visit ? A.post : A.pre);
+        if (visit) break;
+        a.residual(L0, P0, S0, R0);
+        nb_restrict(L0, R0, L1, two ? F1 : Fc);
+        for (int v1 = 0; v1 < 2; ++v1) {
+            if (two && v1) nb_prolong(L1, P1, Lc, Fc);
+            if (two) {
+                if (!v1) o.load_f(L1, F1);
+                o.sweeps(L1, P1, S1, v1 ? A.post : A.pre);
+            }
+            if (v1) break;
+            if (two) {
+                o.residual(L1, P1, S1, F1);             // its right-hand side is in registers
+                nb_restrict(L1, F1, Lc, Fc);
+            }
+            for (int c = threadIdx.x; c < nc; c += kNodBottomThreads) rhs[c] = (double)Fc[c];
+            __syncthreads();
+            dense_solve<kNodBottomThreads>(nc, 1, A.minv, rhs, x, reinterpret_cast<double*>(R0), &mean);
+            for (int c = threadIdx.x; c < nc; c += kNodBottomThreads) Fc[c] = (T)x[c];
+            __syncthreads();
         }
-        __syncthreads();
     }
-    for (int b = 0; b + 1 < nb; ++b) {
-        for (int s = 0; s < A.pre; ++s)
-            for (int col = 0; col < 4; ++col) nb_colour(A.lev[b], Pof(b), Fof(b), col);
-        nb_resid(A.lev[b], Pof(b), Fof(b), Rof(b));
-        nb_restrict(A.lev[b], Rof(b), A.lev[b + 1], Pof(b + 1), Fof(b + 1));
-    }
-    nb_coarse(nodes(nb - 1), A.minv, Fof(nb - 1), Pof(nb - 1), rhs, x, &mean);
-    for (int b = nb - 2; b >= 0; --b) {
-        nb_prolong(A.lev[b], Pof(b), A.lev[b + 1], Pof(b + 1));
-        for (int s = 0; s < A.post; ++s)
-            for (int col = 0; col < 4; ++col) nb_colour(A.lev[b], Pof(b), Fof(b), col);
-    }
-    const int n0 = nodes(0);
-    for (int e = threadIdx.x; e < n0; e += blockDim.x) A.lev[0].phi[e] = Pof(0)[e];
+    for (int e = threadIdx.x; e < (int)L0.nodes(); e += kNodBottomThreads) L0.phi[e] = P0[e];
 }
 
 // Grid of a point loop over an X x Y x Z box: at most 2048 workgroups (the
@@ -1351,19 +1419,25 @@ hipError_t nod_coarse_solve(int n, const double* minv, const float* f, float* ph
     return launch_coarse_solve_f32(n, minv, f, phi, st, 1);
 }
 
-// First level (>= 1) from which every level's phi, f and r fit in the
-// bottom kernel's LDS, or -1 (no level above the coarsest qualifies).
+// First level (>= 1, above the coarsest) that the bottom kernel takes with
+// every coarser one, or -1.
 template <typename T>
 int nod_bottom_start(const nodal_hierarchy* H) {
+    using Cap = NodBottomCap<T>;
     const NodLevelT<T>* lev = nod_levels<T>(const_cast<nodal_hierarchy*>(H));
-    size_t bytes = 0;
-    int start = -1;
-    for (int l = H->nlev - 1; l >= 1; --l) {
-        bytes += 3 * lev[l].nodes() * sizeof(T);
-        if (bytes > kNodBottomLds || H->nlev - l > kNodBottomMax) break;
-        start = l;
+    auto fits = [](const NodLevelT<T>& L, int nodes, int cells, int own) {
+        const int N[3] = {L.Nx, L.Ny, L.Nz};
+        return std::max({L.Nx, L.Ny, L.Nz}) < 1024 && L.nodes() <= (size_t)nodes && nod_bordered(N) <= cells &&
+               nod_colour_max(L.Nx, L.Ny, L.Nz) <= own * kNodBottomThreads;
+    };
+    for (int l = std::max(1, H->nlev - 3); l + 1 < H->nlev; ++l) {
+        if (!fits(lev[l], Cap::nodes, Cap::cells, Cap::own)) continue;
+        if (H->nlev - l == 3 && (!fits(lev[l + 1], Cap::nodes1, Cap::cells1, Cap::own1) ||
+                                 lev[l + 2].nodes() > (size_t)Cap::coarse))
+            continue;
+        return l;
     }
-    return start < H->nlev - 1 ? start : -1;
+    return -1;
 }
 
 // V-cycle from level l in T (the coarsest solve applies the FP64 inverse).
@@ -1372,12 +1446,7 @@ int nod_vcycle(nodal_hierarchy* H, int l, hipStream_t st) {
     if (H->bottom_on && l > 0 && l == nod_bottom_start<T>(H)) {
         NodBottomArgs<T> a{};
         a.nlev = H->nlev - l;
-        size_t off = 0;
-        for (int b = 0; b < a.nlev; ++b) {
-            a.lev[b] = nod_levels<T>(H)[l + b];
-            a.off[b] = (int)off;
-            off += 3 * a.lev[b].nodes();
-        }
+        for (int b = 0; b < a.nlev; ++b) a.lev[b] = nod_levels<T>(H)[l + b];
         a.minv = H->minv;
         a.pre = H->p.pre_sweeps;
         a.post = H->p.post_sweeps;

@@ -598,16 +598,19 @@ int bottom_start(const mg_hierarchy* H) {
     int L = -1;
     for (int l = 1; l + 1 < H->nlev; ++l) {
         const Level& F = H->lev[l];
+        if (F.N <= (size_t)kBottomCells) return l;
         if (!sweep_fusable<T>(F.nx, F.ny, F.nz)) {
             L = l;
             break;
         }
     }
     if (L < 0) return -1;
-    // the first level from there down whose phi and f, with every coarser
-    // level's, fit in the workgroup's LDS (a 24^3 level in FP64 does not:
-    // it keeps one launch per step, and the bottom takes 12^3 and below)
+    // a wider level that the fused sweep does not take: the first level from
+    // there down whose phi and f, with every coarser level's, fit in the
+    // workgroup's LDS (a 24^3 level in FP64 does not: it keeps one launch per
+    // step, and the bottom takes 12^3 and below)
     for (int b = L; b + 1 < H->nlev; ++b) {
+        if (H->lev[b].N <= (size_t)kBottomCells) return b;
         if (H->nlev - b > kMaxBottomLevels) continue;
         size_t bytes = 0;
         for (int l = b; l < H->nlev; ++l) bytes += 2 * H->lev[l].N * sizeof(T);
@@ -636,6 +639,7 @@ void bottom_args(mg_hierarchy* H, int l, BottomArgs<T>& a) {
         v.ny = F.ny;
         v.nz = F.nz;
         v.off = off;
+        v.fused_div = sweep_fusable<T>(F.nx, F.ny, F.nz) ? 1 : 0;
         v.h2 = (T)(F.h * F.h);
         v.bx = A->bx;
         v.by = A->by;
