@@ -152,7 +152,7 @@ SweepArgs<double> sweep_args(mg_hierarchy* H, int l) {
 bool multi_tile_shape(int cfg) {
     const SweepCfg& c = kSweepCfgs[cfg];
     return (c.tx == 32 && c.ty == 8) || (c.tx == 64 && c.ty == 8) || (c.tx == 32 && c.ty == 4) ||
-           (c.tx == 64 && c.ty == 16);
+           (c.tx == 64 && c.ty == 16) || cfg == kTileCfg;
 }
 
 // One batched launch of the fused sweep kernel (op) over `grp`, grouped by
@@ -162,7 +162,7 @@ int launch_fused(std::vector<Item>& grp, bool use_rho, int in_mode, int op, Stag
     std::map<int, std::vector<Item*>> by_cfg;
     for (auto& it : grp) {
         Level& F = it.H->lev[it.l];
-        by_cfg[sweep_config_for(F.nx, F.ny, F.nz, use_rho)].push_back(&it);
+        by_cfg[sweep_config_for(F.nx, F.ny, F.nz, use_rho, true, false, op != kOpSweepNorm)].push_back(&it);
     }
     for (auto& kv : by_cfg) {
         const int cfg = kv.first;
@@ -254,7 +254,7 @@ int multi_smooth(std::vector<Item>& items, int first, Staging& S, hipStream_t st
     int maxk = 0;
     for (auto& it : items) {
         Level& F = it.H->lev[it.l];
-        if (!sweep_fusable<double>(F.nx, F.ny, F.nz)) small.push_back(&it);
+        if (!sweep_fusable(F.nx, F.ny, F.nz)) small.push_back(&it);
         maxk = std::max(maxk, it.nsweeps);
     }
     // prolongation alone (no sweep to fold it into)
@@ -308,7 +308,7 @@ int multi_smooth(std::vector<Item>& items, int first, Staging& S, hipStream_t st
             std::vector<Item> grp;
             for (auto& it : items) {
                 Level& F = it.H->lev[it.l];
-                if (k >= it.nsweeps || !sweep_fusable<double>(F.nx, F.ny, F.nz)) continue;
+                if (k >= it.nsweeps || !sweep_fusable(F.nx, F.ny, F.nz)) continue;
                 if (rho_level(it.H, it.l) != (rho == 1)) continue;
                 grp.push_back(it);
             }
@@ -323,24 +323,24 @@ int multi_smooth(std::vector<Item>& items, int first, Staging& S, hipStream_t st
 
 // r_l = f_l - L phi_l restricted into f_{l+1}; phi_{l+1} = 0 (batched form).
 int multi_resid_restrict(std::vector<Item>& items, Staging& S, hipStream_t st) {
-    std::vector<Item> tiled;
+    std::vector<Item> fused[2];                  // stored coefficients, coefficients from rho
     std::vector<Item*> cells;
     for (auto& it : items) {
         Level& F = it.H->lev[it.l];
-        if (rho_level(it.H, it.l)) {
-            if (sweep_fusable<double>(F.nx, F.ny, F.nz)) {
-                tiled.push_back(it);
-            } else {
-                Level& C = it.H->lev[it.l + 1];
-                BHIP(launch_resid_restrict_rho(Shape{F.nx, F.ny, F.nz}, F.h, it.H->rho, F.d.phi, F.d.f, C.d.f, C.d.phi,
-                                               st));
-            }
+        const bool rho = rho_level(it.H, it.l);
+        if (sweep_fusable(F.nx, F.ny, F.nz)) {
+            fused[rho].push_back(it);
+        } else if (rho) {
+            Level& C = it.H->lev[it.l + 1];
+            BHIP(launch_resid_restrict_rho(Shape{F.nx, F.ny, F.nz}, F.h, it.H->rho, F.d.phi, F.d.f, C.d.f, C.d.phi,
+                                           st));
         } else {
             cells.push_back(&it);
         }
     }
-    if (!tiled.empty()) {
-        int rc = launch_fused(tiled, true, kInPlain, kOpResidRestrict, S, st);
+    for (int rho = 0; rho < 2; ++rho) {
+        if (fused[rho].empty()) continue;
+        int rc = launch_fused(fused[rho], rho == 1, kInPlain, kOpResidRestrict, S, st);
         if (rc) return rc;
     }
     return launch_cells(cells, coarse_cells,
@@ -381,23 +381,16 @@ int multi_norm_sweep(std::vector<mg_hierarchy*>& hs, double* gather, Staging& S,
     return MG_OK;
 }
 
-// The bottoms of every problem: one launch per kernel form.
+// The bottoms of every problem in one launch.
 template <typename T>
-int multi_bottom(const std::vector<BottomArgs<T>>& all, Staging& S, hipStream_t st) {
-    for (int narrow = 0; narrow < 2; ++narrow) {
-        std::vector<BottomArgs<T>> v;
-        int cells = 0;
-        for (const auto& a : all) {
-            if (bottom_narrow(a) != (narrow == 1)) continue;
-            v.push_back(a);
-            if (narrow) cells = std::max(cells, bottom_cells(a));
-        }
-        if (v.empty()) continue;
-        void* dd = nullptr;
-        int rc = S.push(v.data(), v.size() * sizeof(BottomArgs<T>), st, &dd);
-        if (rc) return rc;
-        BHIP(launch_bottom_multi((const BottomArgs<T>*)dd, (int)v.size(), cells, st));
-    }
+int multi_bottom(const std::vector<BottomArgs<T>>& v, Staging& S, hipStream_t st) {
+    if (v.empty()) return MG_OK;
+    int cells = 0;
+    for (const auto& a : v) cells = std::max(cells, bottom_cells(a));
+    void* dd = nullptr;
+    int rc = S.push(v.data(), v.size() * sizeof(BottomArgs<T>), st, &dd);
+    if (rc) return rc;
+    BHIP(launch_bottom_multi((const BottomArgs<T>*)dd, (int)v.size(), cells, st));
     return MG_OK;
 }
 
@@ -409,7 +402,7 @@ int multi_vcycle(std::vector<mg_hierarchy*>& hs, const std::vector<int>& pre_don
     std::vector<int> stop(hs.size());
     int lmax = 0;
     for (size_t i = 0; i < hs.size(); ++i) {
-        const int b = bottom_start<double>(hs[i]);
+        const int b = bottom_start(hs[i]);
         stop[i] = b > 0 ? b : hs[i]->nlev - 1;
         lmax = std::max(lmax, stop[i]);
     }
@@ -476,6 +469,7 @@ SweepArgs<float> sweep_args_f32(mg_hierarchy* H, int l) {
     a.by = F.s.by;
     a.bz = F.s.bz;
     a.rho = l == 0 ? H->rho32 : nullptr;
+    a.march_div = sweep_marchable(F.nx, F.ny, F.nz) ? 1 : 0;
     a.b0c = H->rho.b0c;
     a.b0e = H->rho.b0e;
     if (l + 1 < H->nlev) {
@@ -537,7 +531,7 @@ int multi_vcycle_f32(std::vector<mg_hierarchy*>& hs, Staging& S, hipStream_t st,
     std::vector<int> stop(hs.size());
     int lmax = 0;
     for (size_t i = 0; i < hs.size(); ++i) {
-        stop[i] = bottom_start<float>(hs[i]);
+        stop[i] = bottom_start(hs[i]);
         lmax = std::max(lmax, stop[i]);
     }
     auto sweeps = [&](int l, bool post, int first) -> int {
@@ -553,7 +547,7 @@ int multi_vcycle_f32(std::vector<mg_hierarchy*>& hs, Staging& S, hipStream_t st,
                 if (l >= stop[i] || k >= (post ? H->p.post_sweeps : H->p.pre_sweeps)) continue;
                 const Level& F = H->lev[l];
                 args.push_back(sweep_args_f32(H, l));
-                cfgs.push_back(sweep_config_for(F.nx, F.ny, F.nz, l == 0, false));
+                cfgs.push_back(sweep_config_for(F.nx, F.ny, F.nz, l == 0, false, false, true));
                 who.push_back(H);
             }
             if (args.empty()) continue;
@@ -572,7 +566,7 @@ int multi_vcycle_f32(std::vector<mg_hierarchy*>& hs, Staging& S, hipStream_t st,
             if (l >= stop[i]) continue;
             const Level& F = hs[i]->lev[l];
             args.push_back(sweep_args_f32(hs[i], l));
-            cfgs.push_back(sweep_config_for(F.nx, F.ny, F.nz, l == 0, false));
+            cfgs.push_back(sweep_config_for(F.nx, F.ny, F.nz, l == 0, false, false, true));
         }
         rc = launch_group<float>(args, cfgs, l == 0, kInPlain, kOpResidRestrict, S, st);
         if (rc) return rc;
@@ -650,16 +644,16 @@ bool batchable(const mg_hierarchy* H) {
     const Level& L0 = H->lev[0];
     if (H->outflow) return false;      // outflow sides: solved one by one (mac_project)
     if (H->boxes_on) return false;     // multi-box finest level: solved one by one
-    if (H->p.pre_sweeps < 1 || H->nlev < 2 || !sweep_fusable<double>(L0.nx, L0.ny, L0.nz)) return false;
+    if (H->p.pre_sweeps < 1 || H->nlev < 2 || !sweep_marchable(L0.nx, L0.ny, L0.nz)) return false;
     if (H->p.precision == MG_FP64) return true;
     // mixed precision: every FP32 level above the one-workgroup bottom is a
     // fused-sweep level (the batched FP32 cycle has no per-cell kernels), and
     // every prolongation is folded into a post-sweep
     if (H->p.post_sweeps < 1) return false;
-    const int b = bottom_start<float>(H);
+    const int b = bottom_start(H);
     if (b <= 0) return false;
     for (int l = 0; l < b; ++l)
-        if (!sweep_fusable<float>(H->lev[l].nx, H->lev[l].ny, H->lev[l].nz)) return false;
+        if (!sweep_fusable(H->lev[l].nx, H->lev[l].ny, H->lev[l].nz)) return false;
     return true;
 }
 

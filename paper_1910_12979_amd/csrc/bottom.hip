@@ -11,8 +11,7 @@
 // the coarsest solve), so a bottom launch gives the same bits as the
 // launches it replaces.  The batched form runs one workgroup per problem.
 //
-// Two forms.  k_bottom (first level of at most kBottomCells cells): every
-// thread owns the same cells throughout and holds their six face
+// Every thread owns the same cells throughout and holds their six face
 // coefficients, diagonal, its reciprocal, right-hand side and neighbour
 // offsets in registers, loaded once; only phi is in LDS, one array per colour
 // so that the reads of a wavefront are consecutive (a colour's cells alone
@@ -22,8 +21,6 @@
 // registers, which eight cells in FP64 take.  From 16^3 down, MI355X: 33 -> 21
 // us in FP64 and 36 -> 18 us in FP32, in the 256^3 solve (caches cold) 39 ->
 // 25 us, against 1024 threads with everything in LDS or global memory.
-// k_bottom_wide (up to 136 KB of phi and f): phi and f in LDS, coefficients
-// from global memory through the caches.
 #include <hip/hip_runtime.h>
 
 #include "dense.h"
@@ -32,105 +29,6 @@
 
 namespace mg {
 namespace {
-
-constexpr int kBottomThreads = 1024;
-
-__device__ inline int bidx(int i, int j, int k, int nx, int ny) { return (k * ny + j) * nx + i; }
-
-// One colour of red-black Gauss-Seidel on a bottom level (phi, f in LDS).
-template <typename T>
-__device__ void b_colour(const BottomLevel<T>& lv, T* P, const T* F, int colour) {
-    const int nx = lv.nx, ny = lv.ny, nz = lv.nz;
-    const int hx = (nx + 1) >> 1;
-    const int items = hx * ny * nz;
-    const T h2 = lv.h2;
-    for (int e = threadIdx.x; e < items; e += blockDim.x) {
-        int ih, r, j, k;
-        small_divmod(e, hx, r, ih);
-        small_divmod(r, ny, k, j);
-        const int i = 2 * ih + ((j + k + colour) & 1);
-        if (i >= nx) continue;
-        const int im = i > 0 ? i - 1 : nx - 1, ip = i < nx - 1 ? i + 1 : 0;
-        const int jm = j > 0 ? j - 1 : ny - 1, jp = j < ny - 1 ? j + 1 : 0;
-        const int km = k > 0 ? k - 1 : nz - 1, kp = k < nz - 1 ? k + 1 : 0;
-        const int c = bidx(i, j, k, nx, ny);
-        const T bxl = lv.bx[c], bxh = lv.bx[bidx(ip, j, k, nx, ny)];
-        const T byl = lv.by[c], byh = lv.by[bidx(i, jp, k, nx, ny)];
-        const T bzl = lv.bz[c], bzh = lv.bz[bidx(i, j, kp, nx, ny)];
-        T num = bxl * P[bidx(im, j, k, nx, ny)];
-        num = num + bxh * P[bidx(ip, j, k, nx, ny)];
-        num = num + byl * P[bidx(i, jm, k, nx, ny)];
-        num = num + byh * P[bidx(i, jp, k, nx, ny)];
-        num = num + bzl * P[bidx(i, j, km, nx, ny)];
-        num = num + bzh * P[bidx(i, j, kp, nx, ny)];
-        T den = bxl + bxh;
-        den = den + byl;
-        den = den + byh;
-        den = den + bzl;
-        den = den + bzh;
-        if (lv.has_bnd) den = den + bnd_diag(lv.bnd, i, j, k, nx, ny, nz);
-        P[c] = qdiv(num - h2 * F[c], den);
-    }
-    __syncthreads();
-}
-
-// (L phi)_c on a bottom level: faces in the fixed order, then times 1/h^2.
-template <typename T>
-__device__ inline T b_apply(const BottomLevel<T>& lv, const T* P, int i, int j, int k) {
-    const int nx = lv.nx, ny = lv.ny, nz = lv.nz;
-    const int im = i > 0 ? i - 1 : nx - 1, ip = i < nx - 1 ? i + 1 : 0;
-    const int jm = j > 0 ? j - 1 : ny - 1, jp = j < ny - 1 ? j + 1 : 0;
-    const int km = k > 0 ? k - 1 : nz - 1, kp = k < nz - 1 ? k + 1 : 0;
-    const int c = bidx(i, j, k, nx, ny);
-    const int cxp = bidx(ip, j, k, nx, ny), cyp = bidx(i, jp, k, nx, ny), czp = bidx(i, j, kp, nx, ny);
-    const T pc = P[c];
-    T s = lv.bx[c] * (P[bidx(im, j, k, nx, ny)] - pc);
-    s = s + lv.bx[cxp] * (P[cxp] - pc);
-    s = s + lv.by[c] * (P[bidx(i, jm, k, nx, ny)] - pc);
-    s = s + lv.by[cyp] * (P[cyp] - pc);
-    s = s + lv.bz[c] * (P[bidx(i, j, km, nx, ny)] - pc);
-    s = s + lv.bz[czp] * (P[czp] - pc);
-    if (lv.has_bnd) s = s - bnd_diag(lv.bnd, i, j, k, nx, ny, nz) * pc;
-    return s * (T(1) / lv.h2);
-}
-
-// f_c = (1/8) sum over the 8 children of (f - L phi), children x fastest,
-// then y, then z; phi_c = 0.
-template <typename T>
-__device__ void b_resid_restrict(const BottomLevel<T>& lv, const T* P, const T* F, T* cP, T* cF) {
-    const int cx = lv.nx >> 1, cy = lv.ny >> 1, cz = lv.nz >> 1;
-    const int items = cx * cy * cz;
-    for (int e = threadIdx.x; e < items; e += blockDim.x) {
-        int I, J, K, r;
-        small_divmod(e, cx, r, I);
-        small_divmod(r, cy, K, J);
-        T s = T(0);
-        for (int dk = 0; dk < 2; ++dk)
-            for (int dj = 0; dj < 2; ++dj)
-                for (int di = 0; di < 2; ++di) {
-                    const int i = 2 * I + di, j = 2 * J + dj, k = 2 * K + dk;
-                    const T r = F[bidx(i, j, k, lv.nx, lv.ny)] - b_apply(lv, P, i, j, k);
-                    s = s + r;
-                }
-        cF[e] = T(0.125) * s;
-        cP[e] = T(0);
-    }
-    __syncthreads();
-}
-
-// phi += P phi_coarse (piecewise constant).
-template <typename T>
-__device__ void b_prolong(const BottomLevel<T>& lv, T* P, const T* cP) {
-    const int nx = lv.nx, ny = lv.ny, nz = lv.nz;
-    const int items = nx * ny * nz;
-    for (int e = threadIdx.x; e < items; e += blockDim.x) {
-        int i, j, k, r;
-        small_divmod(e, nx, r, i);
-        small_divmod(r, ny, k, j);
-        P[e] = P[e] + cP[bidx(i >> 1, j >> 1, k >> 1, nx >> 1, ny >> 1)];
-    }
-    __syncthreads();
-}
 
 // Coarsest level (dense_solve): F in, P out, n values each.
 template <typename T, int NT>
@@ -143,68 +41,7 @@ __device__ void b_coarse(int n, int singular, const double* __restrict__ minv, c
     __syncthreads();
 }
 
-// Coarsest cells of k_bottom_wide: at least two levels below one of at most
-// kBottomLdsBytes / 8 cells.
-constexpr int kWideCoarse = 240;
-
-template <typename T>
-__device__ void bottom_wide_body(const BottomArgs<T>& A) {
-    __shared__ double lds_raw[kBottomLdsBytes / sizeof(double)];
-    __shared__ double rhs[kWideCoarse], x[kWideCoarse], part[kMatvecParts * kWideCoarse];
-    __shared__ double mean;
-    T* lds = reinterpret_cast<T*>(lds_raw);
-    const int nb = A.nlev;
-    auto Pof = [&](int b) { return lds + A.lev[b].off; };
-    auto Fof = [&](int b) { return lds + A.lev[b].off + A.lev[b].nx * A.lev[b].ny * A.lev[b].nz; };
-
-    {   // first bottom level: f from the level above's restriction, phi = 0
-        const int n0 = A.lev[0].nx * A.lev[0].ny * A.lev[0].nz;
-        T* P = Pof(0);
-        T* F = Fof(0);
-        for (int e = threadIdx.x; e < n0; e += blockDim.x) {
-            F[e] = A.f[e];
-            P[e] = T(0);
-        }
-        __syncthreads();
-    }
-    for (int b = 0; b + 1 < nb; ++b) {
-        for (int s = 0; s < A.pre; ++s) {
-            b_colour(A.lev[b], Pof(b), Fof(b), 0);
-            b_colour(A.lev[b], Pof(b), Fof(b), 1);
-        }
-        b_resid_restrict(A.lev[b], Pof(b), Fof(b), Pof(b + 1), Fof(b + 1));
-    }
-    {
-        const BottomLevel<T>& c = A.lev[nb - 1];
-        b_coarse<T, kBottomThreads>(c.nx * c.ny * c.nz, A.singular, A.minv, Fof(nb - 1), Pof(nb - 1), rhs, x, part,
-                                    &mean);
-    }
-    for (int b = nb - 2; b >= 0; --b) {
-        b_prolong(A.lev[b], Pof(b), Pof(b + 1));
-        for (int s = 0; s < A.post; ++s) {
-            b_colour(A.lev[b], Pof(b), Fof(b), 0);
-            b_colour(A.lev[b], Pof(b), Fof(b), 1);
-        }
-    }
-    const int n0 = A.lev[0].nx * A.lev[0].ny * A.lev[0].nz;
-    const T* P = Pof(0);
-    for (int e = threadIdx.x; e < n0; e += blockDim.x) A.phi[e] = P[e];
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBottomThreads) void k_bottom_wide(BottomArgs<T> a) {
-    bottom_wide_body<T>(a);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBottomThreads) void k_bottom_wide_multi(const BottomArgs<T>* __restrict__ descs) {
-    bottom_wide_body<T>(descs[blockIdx.x]);
-}
-
-// ---------------------------------------------------------------------------
-// first level of at most kBottomCells cells
-// ---------------------------------------------------------------------------
-constexpr int kNarrowThreads = 512;
+constexpr int kBottomThreads = 512;
 
 // A colour's cells of a level (every smoothed level has even sides) are
 // numbered ((k ny + j) nx/2 + ih), i = 2 ih + ((j + k + colour) & 1); phi of
@@ -290,7 +127,7 @@ __device__ __forceinline__ int own_thread() {
     return t;
 }
 
-// The first level's cells of a thread: e = threadIdx.x + m * kNarrowThreads
+// The first level's cells of a thread: e = threadIdx.x + m * kBottomThreads
 // of each colour, m < K.  In LDS: phi (P), the residual (R) and, with outflow
 // sides (kBnd), the boundary diagonal (G), each by colour.
 template <typename T, int K, bool kBnd>
@@ -309,7 +146,7 @@ struct Owned {
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int m = 0; m < K; ++m) {
-                const int e = threadIdx.x + m * kNarrowThreads;
+                const int e = threadIdx.x + m * kBottomThreads;
                 const CellAt q = cell_at(lv, c, min(e, half - 1));
                 cell_coeffs(lv, q, b[c][m]);
                 f[c][m] = F[q.row * lv.nx + q.i];
@@ -323,7 +160,7 @@ struct Owned {
 #pragma unroll
                 for (int m = 0; m < K; ++m) {
                     const T d = diagonal(c, m, G);
-                    rec[c][m] = lv.fused_div ? precip(d) : qrecip(d);
+                    rec[c][m] = lv.march_div ? precip(d) : qrecip(d);
                 }
         }
         __syncthreads();
@@ -332,7 +169,7 @@ struct Owned {
     // recomputed at each use: held, it would cost eight cells their registers
     __device__ __forceinline__ T diagonal(int c, int m, const T* G) const {
         T d = face_sum(b[c][m]);
-        if (kBnd) d = d + G[c * half + min((int)threadIdx.x + m * kNarrowThreads, half - 1)];
+        if (kBnd) d = d + G[c * half + min((int)threadIdx.x + m * kBottomThreads, half - 1)];
         return d;
     }
 
@@ -340,7 +177,7 @@ struct Owned {
     __device__ __forceinline__ void colour(T* P, const T* G, T h2) {
 #pragma unroll
         for (int m = 0; m < K; ++m) {
-            const int e = threadIdx.x + m * kNarrowThreads;
+            const int e = threadIdx.x + m * kBottomThreads;
             if (e >= half) continue;
             const T d = diagonal(c, m, G);
             T r;
@@ -370,7 +207,7 @@ struct Owned {
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int m = 0; m < K; ++m) {
-                const int e = threadIdx.x + m * kNarrowThreads;
+                const int e = threadIdx.x + m * kBottomThreads;
                 if (e < half)
                     R[c * half + e] = cell_residual<kBnd>(b[c][m], nb[c][m], P + (1 - c) * half, P[c * half + e],
                                                           f[c][m], kBnd ? G[c * half + e] : T(0), ih2);
@@ -386,7 +223,7 @@ struct Owned {
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int m = 0; m < K; ++m) {
-                const int e = t + m * kNarrowThreads;
+                const int e = t + m * kBottomThreads;
                 if (e >= half) continue;
                 int ih, j, k, r;
                 small_divmod(e, lv.nx >> 1, r, ih);
@@ -400,7 +237,7 @@ struct Owned {
         const int nx = lv.nx, hx = nx >> 1, t = own_thread();
 #pragma unroll
         for (int m = 0; m < K; ++m) {
-            const int e = t + m * kNarrowThreads;
+            const int e = t + m * kBottomThreads;
             if (e >= half) continue;
             int ih, j, k, r;
             small_divmod(e, hx, r, ih);
@@ -442,7 +279,7 @@ struct Second {
                 d = d + g;
             }
             for (int k = 0; k < 6; ++k) L.b[k][c * half + e] = b[k];
-            L.rec[c * half + e] = lv.fused_div ? precip(d) : qrecip(d);
+            L.rec[c * half + e] = lv.march_div ? precip(d) : qrecip(d);
             L.P[c * half + e] = T(0);
         }
     }
@@ -479,7 +316,7 @@ struct Second {
 // F_c = the mean of the 8 children's residuals (x fastest, then y, then z);
 // at most 512 coarse cells, one per thread, to at(I, J, K).
 template <typename T, typename At>
-__device__ __forceinline__ void narrow_restrict(const BottomLevel<T>& lv, const T* R, At at) {
+__device__ __forceinline__ void bottom_restrict(const BottomLevel<T>& lv, const T* R, At at) {
     const int cx = lv.nx >> 1, cy = lv.ny >> 1, cz = lv.nz >> 1, half = cx * lv.ny * lv.nz;
     const int e = threadIdx.x;
     if (e < cx * cy * cz) {
@@ -499,7 +336,7 @@ __device__ __forceinline__ void narrow_restrict(const BottomLevel<T>& lv, const 
 
 template <typename T, int K, bool kBnd>
 __device__ __forceinline__ void bottom_body(const BottomArgs<T>& A) {
-    constexpr int N0 = 2 * K * kNarrowThreads, Nc = kBottomCells / 8;
+    constexpr int N0 = 2 * K * kBottomThreads, Nc = kBottomCells / 8;
     __shared__ T P0[N0], G0[kBnd ? N0 : 1], Fc[Nc], Xc[Nc];
     __shared__ SecondLds<T> L;
     __shared__ double work[kMatvecParts * kCoarseMax];  // residuals of the first level, or the coarsest solve's sums
@@ -529,14 +366,14 @@ __device__ __forceinline__ void bottom_body(const BottomArgs<T>& A) {
         if (visit) break;
         a.residual(P0, G0, R0, T(1) / l0.h2);
         if (two) {
-            narrow_restrict(l0, R0, second(L.f));
+            bottom_restrict(l0, R0, second(L.f));
             o.sweeps(L, l1.h2, A.pre);
             o.residual(L, T(1) / l1.h2);
-            narrow_restrict(l1, L.R, coarse(Fc));
+            bottom_restrict(l1, L.R, coarse(Fc));
         } else {
-            narrow_restrict(l0, R0, coarse(Fc));
+            bottom_restrict(l0, R0, coarse(Fc));
         }
-        b_coarse<T, kNarrowThreads>(nc, A.singular, A.minv, Fc, Xc, rhs, x, work, &mean);
+        b_coarse<T, kBottomThreads>(nc, A.singular, A.minv, Fc, Xc, rhs, x, work, &mean);
         if (two) {
             const int e = threadIdx.x;
             if (e < half1) {
@@ -554,19 +391,19 @@ __device__ __forceinline__ void bottom_body(const BottomArgs<T>& A) {
 }
 
 template <typename T, int K, bool kBnd>
-__global__ __launch_bounds__(kNarrowThreads) void k_bottom(BottomArgs<T> a) {
+__global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a) {
     bottom_body<T, K, kBnd>(a);
 }
 
 template <typename T, int K>
-__global__ __launch_bounds__(kNarrowThreads) void k_bottom_multi(const BottomArgs<T>* __restrict__ descs) {
+__global__ __launch_bounds__(kBottomThreads) void k_bottom_multi(const BottomArgs<T>* __restrict__ descs) {
     bottom_body<T, K, false>(descs[blockIdx.x]);        // batches have no outflow sides
 }
 
 template <typename T, int K>
-void launch_narrow(const BottomArgs<T>& a, hipStream_t st) {
-    if (a.lev[0].has_bnd) hipLaunchKernelGGL((k_bottom<T, K, true>), dim3(1), dim3(kNarrowThreads), 0, st, a);
-    else hipLaunchKernelGGL((k_bottom<T, K, false>), dim3(1), dim3(kNarrowThreads), 0, st, a);
+void launch_form(const BottomArgs<T>& a, hipStream_t st) {
+    if (a.lev[0].has_bnd) hipLaunchKernelGGL((k_bottom<T, K, true>), dim3(1), dim3(kBottomThreads), 0, st, a);
+    else hipLaunchKernelGGL((k_bottom<T, K, false>), dim3(1), dim3(kBottomThreads), 0, st, a);
 }
 
 }  // namespace
@@ -574,21 +411,20 @@ void launch_narrow(const BottomArgs<T>& a, hipStream_t st) {
 template <typename T>
 hipError_t launch_bottom(const BottomArgs<T>& a, hipStream_t st) {
     const int n = bottom_cells(a);
-    if (n > kBottomCells) hipLaunchKernelGGL(k_bottom_wide<T>, dim3(1), dim3(kBottomThreads), 0, st, a);
-    else if (n > 4 * kNarrowThreads) launch_narrow<T, 4>(a, st);
-    else if (n > 2 * kNarrowThreads) launch_narrow<T, 2>(a, st);
-    else launch_narrow<T, 1>(a, st);
+    if (n > kBottomCells || a.nlev < 2 || a.nlev > kMaxBottomLevels) return hipErrorInvalidValue;
+    if (n > 4 * kBottomThreads) launch_form<T, 4>(a, st);
+    else if (n > 2 * kBottomThreads) launch_form<T, 2>(a, st);
+    else launch_form<T, 1>(a, st);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_bottom_multi(const BottomArgs<T>* d, int nprob, int cells, hipStream_t st) {
     if (nprob <= 0) return hipSuccess;
-    if (cells > kBottomCells) return hipErrorInvalidValue;
-    const dim3 nt(kNarrowThreads);
-    if (cells <= 0) hipLaunchKernelGGL(k_bottom_wide_multi<T>, dim3(nprob), dim3(kBottomThreads), 0, st, d);
-    else if (cells > 4 * kNarrowThreads) hipLaunchKernelGGL((k_bottom_multi<T, 4>), dim3(nprob), nt, 0, st, d);
-    else if (cells > 2 * kNarrowThreads) hipLaunchKernelGGL((k_bottom_multi<T, 2>), dim3(nprob), nt, 0, st, d);
+    if (cells < 1 || cells > kBottomCells) return hipErrorInvalidValue;
+    const dim3 nt(kBottomThreads);
+    if (cells > 4 * kBottomThreads) hipLaunchKernelGGL((k_bottom_multi<T, 4>), dim3(nprob), nt, 0, st, d);
+    else if (cells > 2 * kBottomThreads) hipLaunchKernelGGL((k_bottom_multi<T, 2>), dim3(nprob), nt, 0, st, d);
     else hipLaunchKernelGGL((k_bottom_multi<T, 1>), dim3(nprob), nt, 0, st, d);
     return hipGetLastError();
 }

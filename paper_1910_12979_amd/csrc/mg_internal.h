@@ -125,15 +125,16 @@ struct RhoArgs {
 // ---- bottom of the V-cycle in one workgroup (bottom.hip) -------------------
 // The coarse levels of the V-cycle from one of them (phi = 0, f given) down to
 // the coarsest and back.  Same per-cell arithmetic as the per-level kernels.
-constexpr int kMaxBottomLevels = 8;
-constexpr size_t kBottomLdsBytes = 136 * 1024;  // phi and f of every bottom level (k_bottom_wide)
-constexpr int kBottomCells = 4096;              // a first level of at most this many cells is held in registers
+// The first level has at most kBottomCells cells, so that it and the next (an
+// eighth) are the only ones smoothed: the third has at most 64 cells and is
+// the coarsest.
+constexpr int kMaxBottomLevels = 3;
+constexpr int kBottomCells = 4096;
 
 template <typename T>
 struct BottomLevel {
     int nx, ny, nz;
-    int off;            // k_bottom_wide: LDS offset (elements) of phi, then f
-    int fused_div;      // the per-level kernel divides as the fused sweep does (pdiv)
+    int march_div;      // FP32: the per-level sweep is the marching one's (pdiv)
     T h2;
     const T* bx;        // stored low-face coefficients (global)
     const T* by;
@@ -153,21 +154,14 @@ struct BottomArgs {
     BottomLevel<T> lev[kMaxBottomLevels];
 };
 
-// First level of at most kBottomCells cells: it and the next (an eighth) are
-// the only ones smoothed, the third has at most 64 cells and is the coarsest.
 template <typename T>
 inline int bottom_cells(const BottomArgs<T>& a) {
     return a.lev[0].nx * a.lev[0].ny * a.lev[0].nz;
 }
 template <typename T>
-inline bool bottom_narrow(const BottomArgs<T>& a) {
-    return bottom_cells(a) <= kBottomCells;
-}
-
-template <typename T>
 hipError_t launch_bottom(const BottomArgs<T>& a, hipStream_t st);
-// One workgroup per problem; d is device memory.  cells: the largest first
-// bottom level where every problem's is bottom_narrow, else 0.
+// One workgroup per problem; d is device memory, cells the largest first
+// bottom level of theirs.
 template <typename T>
 hipError_t launch_bottom_multi(const BottomArgs<T>* d, int nprob, int cells, hipStream_t st);
 

@@ -89,9 +89,7 @@ int project(mg_hierarchy* H, const double* rho, const double* b0c, const double*
             double* u, double* v, double* w, double* phi_out, mg_stats* stats, hipStream_t st,
             const double* w0 = nullptr, const Radial* rad = nullptr);
 double model_bytes(const mg_params& p, int cycles, int mixed);
-// First level run by the one-workgroup bottom solver (phi and f of it and of
-// every coarser level fit in its LDS), or -1.
-template <typename T>
+// First level run by the one-workgroup bottom solver, or -1.
 int bottom_start(const mg_hierarchy* H);
 // Mixed precision: the power of two nearest 1/rms of a residual of 2-norm
 // norm2_sqrt over n cells (1 for a zero or non-finite norm).

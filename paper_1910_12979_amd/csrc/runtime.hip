@@ -428,7 +428,7 @@ int build_coefficients(mg_hierarchy* H, const double* rho, const double* b0c, co
         // recomputes its FP32 coefficients from an FP32 copy of rho, so its
         // stored ones are not mirrored
         const bool fused0 = H->rho.rho != nullptr && H->p.pre_sweeps >= 1 && H->nlev > 1 &&
-                            sweep_fusable<double>(L0.nx, L0.ny, L0.nz);
+                            sweep_marchable(L0.nx, L0.ny, L0.nz);
         for (int l = 0; l < H->nlev; ++l) {
             Level& L = H->lev[l];
             if (l == 0 && !fused0) {
@@ -480,7 +480,7 @@ static int smooth(mg_hierarchy* H, int l, int nsweeps, int first, hipStream_t st
         HIPCHK(launch_prolong<T>(s, A->phi, phic, st));
         return MG_OK;
     }
-    if (!sweep_fusable<T>(F.nx, F.ny, F.nz)) {
+    if (!sweep_fusable(F.nx, F.ny, F.nz)) {
         if (first == kInProlong) HIPCHK(launch_prolong<T>(s, A->phi, phic, st));
         if (first == kInZero) HIPCHK(launch_fill<T>(A->phi, F.N, T(0), st));
         HIPCHK(launch_rbgs<T>(s, F.h, A->phi, A->f, A->bx, A->by, A->bz, nsweeps, st, &bnd));
@@ -513,6 +513,7 @@ static int smooth(mg_hierarchy* H, int l, int nsweeps, int first, hipStream_t st
         a.bnd = bnd;
         if constexpr (dbl) a.dg = F.dg_d;
         else a.dg = F.dg_s;
+        a.march_div = sweep_marchable(F.nx, F.ny, F.nz) ? 1 : 0;
         HIPCHK(launch_sweep<T>(a, use_rho, k == 0 ? first : (int)kInPlain,
                                sweep_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0), st));
         std::swap(A->phi, *alt);
@@ -530,8 +531,9 @@ static int resid_restrict(mg_hierarchy* H, int l, hipStream_t st) {
     const Bnd<float> b32 = F.bnd32();
     if constexpr (std::is_same<T, double>::value) {
         const bool rho0 = l == 0 && H->rho.rho;
-        if (l == 0 && sweep_fusable<double>(F.nx, F.ny, F.nz)) {
-            {   // finest level: the sweep's tiles, coefficients from rho or stored
+        if (sweep_fusable(F.nx, F.ny, F.nz)) {
+            const int cfg = restrict_config_for(F.nx, F.ny, F.nz, rho0, true, l > 0);
+            {   // the sweep's tiles, coefficients from rho or stored
                 SweepArgs<double> a{};
                 a.nx = F.nx;
                 a.ny = F.ny;
@@ -553,7 +555,7 @@ static int resid_restrict(mg_hierarchy* H, int l, hipStream_t st) {
                 a.has_bnd = F.has_bnd ? 1 : 0;
                 a.bnd = b64;
                 a.dg = F.dg_d;
-                HIPCHK(launch_resid_restrict_tiled(a, rho0, sweep_config_for(F.nx, F.ny, F.nz, rho0), st));
+                HIPCHK(launch_resid_restrict_tiled(a, rho0, cfg, st));
             }
             return MG_OK;
         }
@@ -564,7 +566,9 @@ static int resid_restrict(mg_hierarchy* H, int l, hipStream_t st) {
         HIPCHK(launch_resid_restrict<double>(s, F.h, F.d.phi, F.d.f, F.d.bx, F.d.by, F.d.bz, C.d.f, C.d.phi, st,
                                              &b64));
     } else {
-        if (l == 0 && H->rho32_on) {
+        const bool rho0 = l == 0 && H->rho32_on;
+        if (sweep_fusable(F.nx, F.ny, F.nz)) {
+            const int cfg = restrict_config_for(F.nx, F.ny, F.nz, rho0, false, l > 0);
             SweepArgs<float> a{};
             a.nx = F.nx;
             a.ny = F.ny;
@@ -583,7 +587,10 @@ static int resid_restrict(mg_hierarchy* H, int l, hipStream_t st) {
             a.has_bnd = F.has_bnd ? 1 : 0;
             a.bnd = b32;
             a.dg = F.dg_s;
-            HIPCHK(launch_resid_restrict_tiled<float>(a, true, sweep_config_for(F.nx, F.ny, F.nz, true, false), st));
+            a.bx = F.s.bx;
+            a.by = F.s.by;
+            a.bz = F.s.bz;
+            HIPCHK(launch_resid_restrict_tiled<float>(a, rho0, cfg, st));
             return MG_OK;
         }
         HIPCHK(launch_resid_restrict<float>(s, F.h, F.s.phi, F.s.f, F.s.bx, F.s.by, F.s.bz, C.s.f, C.s.phi, st,
@@ -592,30 +599,10 @@ static int resid_restrict(mg_hierarchy* H, int l, hipStream_t st) {
     return MG_OK;
 }
 
-template <typename T>
 int bottom_start(const mg_hierarchy* H) {
     if (!H->bottom_on) return -1;
-    int L = -1;
-    for (int l = 1; l + 1 < H->nlev; ++l) {
-        const Level& F = H->lev[l];
-        if (F.N <= (size_t)kBottomCells) return l;
-        if (!sweep_fusable<T>(F.nx, F.ny, F.nz)) {
-            L = l;
-            break;
-        }
-    }
-    if (L < 0) return -1;
-    // a wider level that the fused sweep does not take: the first level from
-    // there down whose phi and f, with every coarser level's, fit in the
-    // workgroup's LDS (a 24^3 level in FP64 does not: it keeps one launch per
-    // step, and the bottom takes 12^3 and below)
-    for (int b = L; b + 1 < H->nlev; ++b) {
-        if (H->lev[b].N <= (size_t)kBottomCells) return b;
-        if (H->nlev - b > kMaxBottomLevels) continue;
-        size_t bytes = 0;
-        for (int l = b; l < H->nlev; ++l) bytes += 2 * H->lev[l].N * sizeof(T);
-        if (bytes <= kBottomLdsBytes) return b;
-    }
+    for (int l = 1; l + 1 < H->nlev; ++l)
+        if (H->lev[l].N <= (size_t)kBottomCells) return l;
     return -1;
 }
 
@@ -628,7 +615,6 @@ void bottom_args(mg_hierarchy* H, int l, BottomArgs<T>& a) {
     a.post = H->p.post_sweeps;
     a.singular = H->singular ? 1 : 0;
     a.minv = H->minv;
-    int off = 0;
     for (int b = 0; b < a.nlev; ++b) {
         Level& F = H->lev[l + b];
         const LevelArrays<T>* A;
@@ -638,8 +624,7 @@ void bottom_args(mg_hierarchy* H, int l, BottomArgs<T>& a) {
         v.nx = F.nx;
         v.ny = F.ny;
         v.nz = F.nz;
-        v.off = off;
-        v.fused_div = sweep_fusable<T>(F.nx, F.ny, F.nz) ? 1 : 0;
+        v.march_div = sweep_marchable(F.nx, F.ny, F.nz) ? 1 : 0;
         v.h2 = (T)(F.h * F.h);
         v.bx = A->bx;
         v.by = A->by;
@@ -647,7 +632,6 @@ void bottom_args(mg_hierarchy* H, int l, BottomArgs<T>& a) {
         v.has_bnd = F.has_bnd ? 1 : 0;
         if constexpr (dbl) v.bnd = F.bnd64();
         else v.bnd = F.bnd32();
-        off += 2 * (int)F.N;
         if (b == 0) {
             a.f = A->f;
             a.phi = A->phi;
@@ -655,8 +639,6 @@ void bottom_args(mg_hierarchy* H, int l, BottomArgs<T>& a) {
     }
 }
 
-template int bottom_start<double>(const mg_hierarchy*);
-template int bottom_start<float>(const mg_hierarchy*);
 template void bottom_args<double>(mg_hierarchy*, int, BottomArgs<double>&);
 template void bottom_args<float>(mg_hierarchy*, int, BottomArgs<float>&);
 
@@ -666,7 +648,7 @@ template void bottom_args<float>(mg_hierarchy*, int, BottomArgs<float>&);
 template <typename T>
 static int vcycle(mg_hierarchy* H, int l, hipStream_t st, int pre_done = 0, bool zero_start = false) {
     Level& F = H->lev[l];
-    if (l > 0 && l == bottom_start<T>(H)) {          // this level and every coarser one in one launch
+    if (l > 0 && l == bottom_start(H)) {          // this level and every coarser one in one launch
         BottomArgs<T> a;
         bottom_args<T>(H, l, a);
         HIPCHK(launch_bottom<T>(a, st));
@@ -1132,7 +1114,10 @@ static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStrea
     };
     const bool mixed = H->p.precision == MG_MIXED;
     if (H->p.rtol >= 1.0) status = MG_OK;
-    const bool fused = H->p.pre_sweeps >= 1 && H->nlev > 1 && sweep_fusable<double>(L0.nx, L0.ny, L0.nz);
+    // mixed precision keeps the per-cell refinement (one FP32 V-cycle a step)
+    // on finest levels that the marching sweep does not take
+    const bool fused = H->p.pre_sweeps >= 1 && H->nlev > 1 &&
+                       (mixed ? sweep_marchable(L0.nx, L0.ny, L0.nz) : sweep_fusable(L0.nx, L0.ny, L0.nz));
     const bool fused_norm = !mixed && fused;
     if (mixed && fused && status == MG_ERR_NOT_CONVERGED) {
         auto rec = [&](int c, double r) {
@@ -1746,7 +1731,7 @@ int mg_autotune(mg_handle h, int32_t reps, void* stream) {
     int rc = MG_OK;
     for (int l = 0; l + 1 < h->nlev && rc == MG_OK; ++l) {
         Level& F = h->lev[l];
-        if (!sweep_fusable<double>(F.nx, F.ny, F.nz)) break;
+        if (!sweep_marchable(F.nx, F.ny, F.nz)) break;
         const bool rho = l == 0 && h->rho.rho != nullptr;
         float best = 1e30f;
         int best_cfg = -1;
@@ -1876,7 +1861,7 @@ int mg_sweep_config(mg_handle h, int32_t level, int32_t tile[4]) {
     tile[0] = tile[1] = tile[2] = tile[3] = -1;
     const Level& F = h->lev[level];
     const bool dbl = h->p.precision == MG_FP64;
-    const bool fusable = dbl ? sweep_fusable<double>(F.nx, F.ny, F.nz) : sweep_fusable<float>(F.nx, F.ny, F.nz);
+    const bool fusable = sweep_fusable(F.nx, F.ny, F.nz);
     if (level + 1 >= h->nlev || !fusable) return MG_OK;
     const int c = sweep_config_for(F.nx, F.ny, F.nz, level == 0, dbl, level > 0);
     tile[0] = kSweepCfgs[c].tx;

@@ -12,6 +12,8 @@ namespace mg {
 constexpr int kSweepTX = 32;     // smallest tile width (x) of any configuration
 constexpr int kSweepTY = 4;      // smallest tile height (y)
 constexpr int kSweepTZMax = 64;  // largest z-chunk
+constexpr double kTileSolo = 1.5e5;     // largest level (cells) of a single problem that kTileCfg sweeps by default
+constexpr double kTileRestrict = 6.0e5; // and whose residual it restricts
 constexpr int kMaxPartialRows = 2048;   // rows of a hierarchy's partial-sum buffer
 
 // Tile configurations of the fused sweep (TX x TY columns, TZ planes per
@@ -21,9 +23,11 @@ struct SweepCfg {
 };
 constexpr int kNumSweepCfg = 14;
 constexpr int kFirstCoarseCfg = 12;     // 4-plane chunks: coarse levels of a single problem
-constexpr SweepCfg kSweepCfgs[kNumSweepCfg] = {
+constexpr int kTileCfg = kNumSweepCfg;  // small levels: no march (tile.hip); never forced, tuned or saved
+constexpr SweepCfg kSweepCfgs[kNumSweepCfg + 1] = {
     {32, 8, 32}, {32, 8, 64}, {64, 8, 32}, {32, 16, 32}, {64, 4, 64},  {32, 4, 64}, {32, 8, 16},
-    {32, 8, 8},  {64, 8, 64}, {64, 16, 32}, {32, 32, 32}, {64, 16, 64}, {32, 8, 4}, {32, 4, 4}};
+    {32, 8, 8},  {64, 8, 64}, {64, 16, 32}, {32, 32, 32}, {64, 16, 64}, {32, 8, 4}, {32, 4, 4},
+    {16, 8, 4}};
 
 enum { kInZero = 0, kInPlain = 1, kInProlong = 2, kInCorrect = 3 };
 enum { kOpSweep = 0, kOpSweepNorm = 1, kOpResidRestrict = 2, kOpRefine = 3 };
@@ -54,14 +58,26 @@ struct SweepArgs {
     int has_bnd;               // outflow sides: their boundary faces add to the diagonal
     Bnd<T> bnd;                // which sides are outflow sides (non-null)
     const T* dg;               // per-cell boundary diagonal (bnd_diag of every cell)
+    int march_div;             // kTileCfg in FP32: divide as the marching sweep does (sweep_marchable)
     int ox, oy, oz;            // launch_sweep_boxes: first cell of a box interior
     int ex, ey, ez;            // launch_sweep_boxes: box cells
     int wlo[3], whi[3];        // launch_sweep_boxes with rho: wall faces (low faces of these cells), -1 none
     int go[3], gn[3], gp[3];   // launch_sweep_boxes with prolongation: box origin, domain cells, periodic
 };
 
-template <typename T>
+// Levels the marching sweep takes (in one of its configurations), levels that
+// kTileCfg takes, and either.
+bool sweep_marchable(int nx, int ny, int nz);
+bool sweep_tileable(int nx, int ny, int nz);
 bool sweep_fusable(int nx, int ny, int nz);
+
+// kTileCfg (tile.hip): one operation (in_mode, op as launch_sweep_multi) on a
+// small level, and its batched form.
+template <typename T>
+hipError_t launch_tile(const SweepArgs<T>& a, bool use_rho, int in_mode, int op, int* nparts, hipStream_t st);
+template <typename T>
+hipError_t launch_tile_multi(const SweepArgs<T>* d, const int2* tmap, int tiles, bool use_rho, int in_mode, int op,
+                             hipStream_t st);
 
 template <typename T>
 hipError_t launch_sweep(const SweepArgs<T>& a, bool use_rho, int in_mode, int cfg, hipStream_t st);
@@ -72,9 +88,9 @@ hipError_t launch_sweep(const SweepArgs<T>& a, bool use_rho, int in_mode, int cf
 // non-finite r makes the sum non-finite).  *nparts = rows written.
 hipError_t launch_sweep_norm(const SweepArgs<double>& a, bool use_rho, int cfg, int* nparts, hipStream_t st);
 
-// Finest level: f_c = R (f - L phi), phi_c = 0, using the sweep's tiles (each
-// face coefficient computed or read once per cell).  Needs even tile
-// origins, which every configuration has.
+// f_c = R (f - L phi), phi_c = 0, using the sweep's tiles (each face
+// coefficient computed or read once per cell).  Needs even tile origins,
+// which every configuration has.
 template <typename T>
 hipError_t launch_resid_restrict_tiled(const SweepArgs<T>& a, bool use_rho, int cfg, hipStream_t st);
 
@@ -139,17 +155,24 @@ template <typename T>
 hipError_t launch_sweep_boxes_mode(const SweepArgs<T>& a, const BoxGeom& g, int nbox, size_t bstride, int mode,
                                    int* nparts, hipStream_t st);
 
+// The configuration of the residual + restriction, which needs no ring of red
+// cells: kTileCfg up to kTileRestrict cells (64^3 FP64, stored coefficients:
+// 5.2 us against 6.7 with one thread per coarse cell), else the sweep's (128^3 24.0
+// -> 18.7 us).
+int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse);
+
 // Number of tiles (= partial rows) a sweep of this shape launches with cfg.
 int sweep_tiles(int nx, int ny, int nz, int cfg);
 
 // Configuration used for a level of shape nx x ny x nz whose coefficients come
 // from rho (finest level) or are stored, in FP64 (dbl) or FP32, as the
 // finest level of a problem or (coarse) a coarser level of a single-problem
-// V-cycle: forced, autotuned, else a measured default.  Configurations
-// kFirstCoarseCfg and up are only chosen for coarse levels.  A deterministic function of these, so
-// a problem's tiles (and the order of its per-tile norm rows) are the same in
-// solo and batched runs.
-int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl = true, bool coarse = false);
+// V-cycle: forced, autotuned, else a measured default.  A deterministic
+// function of these, so a problem's tiles are the same in every run.  batch:
+// for a launch over many problems, whose work fills the CUs (values do not
+// depend on the configuration; the operations that write norm rows take the
+// single problem's in a batch too, so that the rows' order is the same).
+int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl = true, bool coarse = false, bool batch = false);
 bool sweep_cfg_fits(int nx, int ny, int cfg);
 void sweep_record_tuned(int nx, int ny, int nz, bool rho, bool dbl, int cfg, bool coarse);
 int sweep_tuned_count();

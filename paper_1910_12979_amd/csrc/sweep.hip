@@ -678,44 +678,60 @@ bool sweep_cfg_fits(int nx, int ny, int cfg) {
     return cfg >= 0 && cfg < kNumSweepCfg && nx >= kSweepCfgs[cfg].tx && ny >= kSweepCfgs[cfg].ty;
 }
 
-int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
+int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, bool batch) {
+    if (!sweep_marchable(nx, ny, nz)) return kTileCfg;
     const int forced = tune_forced();
     if (forced >= 0 && sweep_cfg_fits(nx, ny, forced)) return forced;
     const int tuned = tune_find(nx, ny, nz, rho, dbl, coarse);
     if (tuned >= 0) return tuned;
-    // untuned shapes: choices measured on MI355X for cubic levels.  On the
-    // largest boxes 64x16-cell tiles (the halo share of the loads and of the
-    // redundant red updates is a third lower than with 64x8 tiles): FP64
-    // with 64-plane chunks (one 132 KB workgroup per CU), FP32 with 32-plane
-    // chunks; then 32x8 tiles with shallower z-chunks so small levels still
-    // fill the 256 CUs.  Coarse levels of a single-problem V-cycle go
-    // shallower still (a 64^3 level in 4-plane chunks, a 32^3 level in 32x4
-    // tiles of 4 planes: there the march through the planes, not the bytes,
-    // sets the time); batches, which fill the CUs with many problems, keep
-    // the deeper chunks.
+    // untuned shapes: choices measured on MI355X (us per FP64 sweep with the
+    // coefficients from rho).  Small levels of a single problem: kTileCfg,
+    // which has no march whose latency an idle chip would show (32^3 5.5
+    // against 6.7 in 32x4x4 tiles, 64x48x32 6.0 against 7.0; 64^3 9.1 against
+    // 7.7 in 32x8x4, so the line is at kTileSolo); then 32x8 tiles in as many
+    // planes a chunk as still fill the CUs (80^3 12.3 with 4, 14.9 with 8;
+    // 96^3 15.8 and 14.5; 160x96x112 22.9 with 8, 25.5 with 16; 128^3 23.1
+    // and 22.0).  From 4M cells on 64x16-cell tiles (the halo share of the
+    // loads and of the redundant red updates is a third lower than with 64x8
+    // tiles; 192^3 47.6 against 55.9), in FP64 from 8M on with 64-plane chunks
+    // (one 132 KB workgroup per CU).  Batches fill the CUs with many problems
+    // and keep the deeper chunks.
     const double cells = (double)nx * ny * nz;
-    if (nx >= 64 && ny >= 16 && cells >= 8.0e6) {
-        if (dbl && nz >= 64) return 11;
-        if (!dbl) return 9;
+    if (!batch && cells <= kTileSolo && sweep_tileable(nx, ny, nz)) return kTileCfg;
+    if (nx >= 64 && ny >= 16 && cells >= (batch ? 8.0e6 : 4.0e6)) {
+        if (dbl && nz >= 64 && cells >= 8.0e6) return 11;
+        if (!dbl || cells < 8.0e6) return 9;
     }
     if (nx >= 64 && cells >= 8.0e6) return 2;
     if (nx >= 32 && ny >= 8) {
-        if (cells >= 1.0e6) return 6;
-        if (!coarse) return 7;
-        if (cells >= 1.0e5) return 12;
+        if (batch) return cells >= 1.0e6 ? 6 : 7;
+        return cells >= 2.0e6 ? 6 : cells >= 7.0e5 ? 7 : 12;
     }
-    if (coarse && nx >= 32 && ny >= 4 && cells < 1.0e5) return 13;
-    return 5;
+    return batch ? 5 : 13;
 }
 
-template <typename T>
-bool sweep_fusable(int nx, int ny, int nz) {
+int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
+    const int cfg = sweep_config_for(nx, ny, nz, rho, dbl, coarse);
+    const bool chosen = cfg == tune_forced() || tune_find(nx, ny, nz, rho, dbl, coarse) >= 0;
+    return !chosen && (double)nx * ny * nz <= kTileRestrict && sweep_tileable(nx, ny, nz) ? kTileCfg : cfg;
+}
+
+bool sweep_marchable(int nx, int ny, int nz) {
     return nx >= kSweepTX && ny >= kSweepTY && nz >= 4 && nx % 2 == 0 && ny % 2 == 0 && nz % 2 == 0 &&
            (unsigned long long)nx * ny * nz < (1ull << 32);      // 32-bit element offsets
 }
 
+// At most the partial rows that every hierarchy has.
+bool sweep_tileable(int nx, int ny, int nz) {
+    return nx >= 2 && ny >= 2 && nz >= 2 && nx % 2 == 0 && ny % 2 == 0 && nz % 2 == 0 &&
+           (unsigned long long)nx * ny * nz <= (1ull << 20) && sweep_tiles(nx, ny, nz, kTileCfg) <= kMaxPartialRows;
+}
+
+bool sweep_fusable(int nx, int ny, int nz) { return sweep_marchable(nx, ny, nz) || sweep_tileable(nx, ny, nz); }
+
 template <typename T>
 hipError_t launch_sweep(const SweepArgs<T>& a, bool use_rho, int in_mode, int cfg, hipStream_t st) {
+    if (cfg == kTileCfg) return launch_tile<T>(a, use_rho, in_mode, kOpSweep, nullptr, st);
     const SweepCfg& c = kSweepCfgs[cfg];
     if (a.nx < c.tx || a.ny < c.ty) return hipErrorInvalidValue;
     switch (cfg) {
@@ -755,6 +771,7 @@ hipError_t launch_sweep_norm_t(const SweepArgs<double>& a, int cfg, int* nparts,
 }
 
 hipError_t launch_sweep_norm(const SweepArgs<double>& a, bool use_rho, int cfg, int* nparts, hipStream_t st) {
+    if (cfg == kTileCfg) return launch_tile<double>(a, use_rho, kInPlain, kOpSweepNorm, nparts, st);
     const SweepCfg& c = kSweepCfgs[cfg];
     if (a.nx < c.tx || a.ny < c.ty) return hipErrorInvalidValue;
     return use_rho ? launch_sweep_norm_t<true>(a, cfg, nparts, st) : launch_sweep_norm_t<false>(a, cfg, nparts, st);
@@ -782,6 +799,7 @@ hipError_t launch_resid_restrict_tiled_t(const SweepArgs<T>& a, int cfg, hipStre
 
 template <typename T>
 hipError_t launch_resid_restrict_tiled(const SweepArgs<T>& a, bool use_rho, int cfg, hipStream_t st) {
+    if (cfg == kTileCfg) return launch_tile<T>(a, use_rho, kInPlain, kOpResidRestrict, nullptr, st);
     const SweepCfg& c = kSweepCfgs[cfg];
     if (a.nx < c.tx || a.ny < c.ty) return hipErrorInvalidValue;
     return use_rho ? launch_resid_restrict_tiled_t<T, true>(a, cfg, st)
@@ -809,6 +827,7 @@ hipError_t launch_refine_t(const SweepArgs<double>& a, int cfg, int* nparts, hip
 }
 
 hipError_t launch_refine(const SweepArgs<double>& a, bool use_rho, int cfg, int* nparts, hipStream_t st) {
+    if (cfg == kTileCfg) return launch_tile<double>(a, use_rho, kInCorrect, kOpRefine, nparts, st);
     const SweepCfg& c = kSweepCfgs[cfg];
     if (a.nx < c.tx || a.ny < c.ty) return hipErrorInvalidValue;
     return use_rho ? launch_refine_t<true>(a, cfg, nparts, st) : launch_refine_t<false>(a, cfg, nparts, st);
@@ -847,6 +866,7 @@ template <typename T>
 hipError_t launch_sweep_multi(const SweepArgs<T>* d, const int2* tmap, int tiles, bool use_rho, int in_mode, int op,
                               int cfg, hipStream_t st) {
     if (tiles <= 0) return hipSuccess;
+    if (cfg == kTileCfg) return launch_tile_multi<T>(d, tmap, tiles, use_rho, in_mode, op, st);
     const SweepCfg& c = kSweepCfgs[cfg];
     if (c.tx == 32 && c.ty == 8) return launch_multi_mode<T, 32, 8>(d, tmap, tiles, use_rho, in_mode, op, st);
     if (c.tx == 64 && c.ty == 8) return launch_multi_mode<T, 64, 8>(d, tmap, tiles, use_rho, in_mode, op, st);
@@ -956,8 +976,6 @@ int sweep_tiles(int nx, int ny, int nz, int cfg) {
     return ((nx + c.tx - 1) / c.tx) * ((ny + c.ty - 1) / c.ty) * ((nz + c.tz - 1) / c.tz);
 }
 
-template bool sweep_fusable<double>(int, int, int);
-template bool sweep_fusable<float>(int, int, int);
 template hipError_t launch_sweep<double>(const SweepArgs<double>&, bool, int, int, hipStream_t);
 template hipError_t launch_sweep<float>(const SweepArgs<float>&, bool, int, int, hipStream_t);
 template hipError_t launch_resid_restrict_tiled<double>(const SweepArgs<double>&, bool, int, hipStream_t);
