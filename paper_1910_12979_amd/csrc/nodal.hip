@@ -15,13 +15,13 @@
 // contribute); in a periodic direction node n is node 0.
 //
 // Multigrid: four-colour Gauss-Seidel, colour (J mod 2) + 2 (K mod 2) in the
-// order 0..3 (one launch per colour: coupled nodes differ by one in at least
-// two coordinates, so in J or K, and their colours differ; each x-row has one
-// colour, so a launch reads and writes whole rows); residual, full-weighting
+// order 0..3 (coupled nodes differ by one in at least two coordinates, so in J
+// or K, and their colours differ; each x-row has one colour); residual, full-weighting
 // restriction 1/8 sum_d prod(1 - |d_i|/2) r_{2C+d}; trilinear prolongation;
 // coarse sigma the mean of the 8 fine cells; exact coarsest solve (at most
 // 512 nodes) by the dense inverse of -A + c 1 1^T.  Every per-node
-// expression is evaluated in one fixed order, without FMA contraction.
+// expression is evaluated in one fixed order, without FMA contraction beyond
+// the multiply-adds written out (nodal_march.h).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -37,30 +37,13 @@
 #include "dense.h"
 #include "devmath.h"
 #include "mg_internal.h"
+#include "nodal_march.h"
 #include "runtime.h"
 
 namespace mg {
 namespace {
 
 constexpr int kNodBlock = 256;
-
-// One level of the nodal hierarchy: cells (nx, ny, nz), nodes (Nx, Ny, Nz);
-// arrays in T (FP64, or FP32 for the inner cycle of a mixed-precision solve).
-template <typename T>
-struct NodLevelT {
-    int nx, ny, nz;
-    int Nx, Ny, Nz;
-    int px, py, pz;
-    double h;
-    T* sig;             // cells
-    T* phi;             // nodes
-    T* f;
-    T* r;
-    T* phi2;            // nodes: the other buffer of the out-of-place fused sweep
-    __host__ __device__ size_t nodes() const { return (size_t)Nx * Ny * Nz; }
-    __host__ __device__ size_t cells() const { return (size_t)nx * ny * nz; }
-};
-using NodLevel = NodLevelT<double>;
 
 __device__ inline int nod_cell(int I, int s, int n, int per) {
     int c = s ? I : I - 1;
@@ -283,440 +266,55 @@ __global__ void k_nod_gs(NodLevelT<T> L, int col) {
     L.phi[n] = pdiv(num - c12 * L.f[n], den);
 }
 
-// ---------------------------------------------------------------------------
-// Fused out-of-place sweep: out = the four-colour Gauss-Seidel sweep of
-// L.phi (colours 0..3 in order), one launch.
-//
-// Colour c of node (I, J, K) is (J mod 2) + 2 (K mod 2); every row of nodes
-// along x has one colour.  Coupled nodes differ in at least two coordinates,
-// so in an even plane colour 0 reads only old values and colour 1 the new
-// colour-0 values of its four in-plane diagonal neighbours (old values
-// above and below); in an odd plane colour 2 reads the new values of the
-// even planes above and below, colour 3 those and the new colour-2 values of
-// its in-plane diagonal neighbours.
-//
-// A workgroup owns a TX x TY tile of nodes and a chunk of planes and marches
-// up through it, one even plane and the odd plane below it per step:
-// colour 0 of the even plane on the tile plus a ring of 3, colour 1 on ring
-// 2, then colour 2 of the odd plane on ring 1 and colour 3 on the tile, so
-// every value a later colour reads was computed by the workgroup itself;
-// loads cover the tile plus a ring of 4.  New values overwrite old ones in
-// place in the LDS plane buffers (a colour reads only rows of the other
-// colour of its plane), so a plane needs one buffer: four rolling node
-// planes (even plane below, the odd plane, the even plane, the odd plane
-// above) and three rolling cell layers.  The even plane at the top of a
-// chunk is computed again by the next chunk (it reads only old values).
-// Cells beyond a wall carry sigma = 0 and nodes beyond it the value 0, so
-// their terms add exact zeros.  The per-node sums are the per-colour
-// kernel's, term by term, with the sigma products accumulated by fused
-// multiply-adds (the two kernels agree to rounding).
-//
-// Each thread owns one column x of the window and a pair of rows (even J,
-// odd J): one node per colour stage.
-// ---------------------------------------------------------------------------
-__device__ inline int nod_wrapi(int g, int n) {
-    g %= n;
-    return g < 0 ? g + n : g;
-}
-__device__ inline int nod_m3(int k) {
-    k %= 3;
-    return k < 0 ? k + 3 : k;
-}
-
-template <typename T, int TX, int TY>
-__global__ __launch_bounds__((TX + 8) * (TY + 8) / 2) void k_nod_sweep(NodLevelT<T> L, T* __restrict__ out, int tz,
-                                                                      int ntx, int nty, int etop) {
-    constexpr int WX = TX + 8, WY = TY + 8, WP = WY / 2;
-    __shared__ T sp[4][WY][WX];             // node planes, by plane & 3
-    __shared__ T ss[3][WY - 1][WX];         // cell layers, by layer mod 3; [jw][wx]: the cell whose low corner is
-                                            // node (wx, jw) (the window's last row of cells is never read)
-    const int tile = blockIdx.x;
-    const int tx = tile % ntx, ty = (tile / ntx) % nty, tc = tile / (ntx * nty);
-    const int ks = tc * tz;
-    const int ke = min(ks + tz, etop);
-    const int wx = threadIdx.x % WX, p = threadIdx.x / WX;
-    const int je = 2 * p, jo = 2 * p + 1;                  // window rows of the pair
-    const int gI = tx * TX - 4 + wx;                       // global node / low-corner cell coordinates
-    const int gJe = ty * TY - 4 + je, gJo = gJe + 1;
-    // existence along x and y (nodes and the cells whose low corner they are)
-    const bool xn = L.px || (gI >= 0 && gI < L.Nx), xc = L.px || (gI >= 0 && gI < L.nx);
-    const bool yne = L.py || (gJe >= 0 && gJe < L.Ny), yce = L.py || (gJe >= 0 && gJe < L.ny);
-    const bool yno = L.py || (gJo >= 0 && gJo < L.Ny), yco = L.py || (gJo >= 0 && gJo < L.ny);
-    const int Iw = L.px ? nod_wrapi(gI, L.Nx) : min(max(gI, 0), L.Nx - 1);
-    const int Jwe = L.py ? nod_wrapi(gJe, L.Ny) : min(max(gJe, 0), L.Ny - 1);
-    const int Jwo = L.py ? nod_wrapi(gJo, L.Ny) : min(max(gJo, 0), L.Ny - 1);
-    const int iw = L.px ? nod_wrapi(gI, L.nx) : min(max(gI, 0), L.nx - 1);
-    const int jwe = L.py ? nod_wrapi(gJe, L.ny) : min(max(gJe, 0), L.ny - 1);
-    const int jwo = L.py ? nod_wrapi(gJo, L.ny) : min(max(gJo, 0), L.ny - 1);
-    const size_t NxNy = (size_t)L.Nx * L.Ny, nxny = (size_t)L.nx * L.ny;
-    const size_t ne = (size_t)Jwe * L.Nx + Iw, no = (size_t)Jwo * L.Nx + Iw;
-    const size_t ce = (size_t)jwe * L.nx + iw, co = (size_t)jwo * L.nx + iw;
-    const T c12 = (T)(12.0 * (L.h * L.h));
-
-    auto plane_ok = [&](int K) { return L.pz || (K >= 0 && K < L.Nz); };
-    auto layer_ok = [&](int k) { return L.pz || (k >= 0 && k < L.nz); };
-    auto pw = [&](int K) { return L.pz ? nod_wrapi(K, L.Nz) : min(max(K, 0), L.Nz - 1); };
-    auto lw = [&](int k) { return L.pz ? nod_wrapi(k, L.nz) : min(max(k, 0), L.nz - 1); };
-    // Loads are always issued from valid (wrapped or clamped) addresses, so
-    // a set of them is plain load results the compiler never has to wait for
-    // early; the values of nodes and cells beyond a wall are replaced by 0
-    // when they are stored into LDS.
-    auto ld_phi = [&](int K, T& a, T& b) {
-        const size_t o = (size_t)pw(K) * NxNy;
-        a = L.phi[o + ne];
-        b = L.phi[o + no];
-    };
-    auto ld_sig = [&](int k, T& a, T& b) {
-        const size_t o = (size_t)lw(k) * nxny;
-        a = L.sig[o + ce];
-        b = L.sig[o + co];
-    };
-    auto ld_f = [&](int K, T& a, T& b) {
-        const size_t o = (size_t)pw(K) * NxNy;
-        a = L.f[o + ne];
-        b = L.f[o + no];
-    };
-    auto st_phi = [&](int K, T a, T b) {
-        const bool ok = plane_ok(K) && xn;
-        sp[K & 3][je][wx] = (ok && yne) ? a : T(0);
-        sp[K & 3][jo][wx] = (ok && yno) ? b : T(0);
-    };
-    auto st_sig = [&](int k, T a, T b) {
-        const bool ok = layer_ok(k) && xc;
-        ss[nod_m3(k)][je][wx] = (ok && yce) ? a : T(0);
-        if (jo < WY - 1) ss[nod_m3(k)][jo][wx] = (ok && yco) ? b : T(0);
-    };
-    // the update of window node (x, y) of plane slot pc with planes below
-    // (pm) and above (pp) and cell layers below (sm) and above (sq): the 20
-    // coupled neighbours and 8 cell coefficients are read from LDS first (all
-    // loads independent), then combined in the per-colour kernel's order:
-    // cells sz, sy, sx; far corners x+y, x+z, y+z, x+y+z
-    auto update = [&](int x, int y, int pm, int pc, int pp, int sm, int sq, T fv) -> T {
-        T v[3][3][3];
-        T sg[2][2][2];
-#pragma unroll
-        for (int dz = 0; dz < 3; ++dz) {
-            const int pl = dz == 0 ? pm : (dz == 1 ? pc : pp);
-#pragma unroll
-            for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
-                    v[dz][dy][dx] = ((dx != 1) + (dy != 1) + (dz != 1) >= 2) ? sp[pl][y - 1 + dy][x - 1 + dx] : T(0);
-        }
-#pragma unroll
-        for (int sz = 0; sz < 2; ++sz)
-#pragma unroll
-            for (int sy = 0; sy < 2; ++sy)
-#pragma unroll
-                for (int sx = 0; sx < 2; ++sx) sg[sz][sy][sx] = ss[sz ? sq : sm][y - 1 + sy][x - 1 + sx];
-        T num = T(0), den = T(0);
-#pragma unroll
-        for (int sz = 0; sz < 2; ++sz) {
-            const int oz = sz ? 2 : 0;
-#pragma unroll
-            for (int sy = 0; sy < 2; ++sy) {
-                const int oy = sy ? 2 : 0;
-#pragma unroll
-                for (int sx = 0; sx < 2; ++sx) {
-                    const int ox = sx ? 2 : 0;
-                    const T sig = sg[sz][sy][sx];
-                    T acc = v[1][oy][ox];
-                    acc += v[oz][1][ox];
-                    acc += v[oz][oy][1];
-                    acc += v[oz][oy][ox];
-                    num = fma(sig, acc, num);
-                    den = fma(T(4), sig, den);
-                }
-            }
-        }
-        return pdiv(num - c12 * fv, den);
-    };
-
-    // rings (window rows / columns) of the four colour stages
-    const bool colx3 = wx >= 1 && wx < WX - 1, colx2 = wx >= 2 && wx < WX - 2;
-    const bool colx1 = wx >= 3 && wx < WX - 3, colx0 = wx >= 4 && wx < WX - 4;
-    const bool st0 = colx3 && p >= 1 && p <= WP - 1 && xn && yne;        // colour 0 / 2 row: even
-    const bool st1 = colx2 && p >= 1 && p <= WP - 2 && xn && yno;        // colour 1 / 3 row: odd
-    const bool st2 = colx1 && p >= 2 && p <= WP - 2 && xn && yne;
-    const bool st3 = colx0 && p >= 2 && p <= WP - 3 && xn && yno;
-    const bool tile_pair = colx0 && p >= 2 && p <= WP - 3 && gI < L.Nx;   // output nodes (unwrapped inside the box)
-    const bool oute = tile_pair && gJe < L.Ny, outo = tile_pair && gJo < L.Ny;
-
-    // prologue: planes ks-1, ks, ks+1, layers ks-1, ks, f of plane ks
-    {
-        T a0, b0, a1, b1, a2, b2, a3, b3, a4, b4;
-        ld_phi(ks - 1, a0, b0);
-        ld_phi(ks, a1, b1);
-        ld_phi(ks + 1, a2, b2);
-        ld_sig(ks - 1, a3, b3);
-        ld_sig(ks, a4, b4);
-        st_phi(ks - 1, a0, b0);
-        st_phi(ks, a1, b1);
-        st_phi(ks + 1, a2, b2);
-        st_sig(ks - 1, a3, b3);
-        st_sig(ks, a4, b4);
-    }
-    T fe0, fo0, fe1 = T(0), fo1 = T(0);         // f of the even plane (e/o rows), of the odd plane below
-    ld_f(ks, fe0, fo0);
-    __syncthreads();
-
-    for (int E = ks; E <= ke; E += 2) {
-        // next step's loads in flight: planes E+2, E+3, layers E+1, E+2, f of planes E+2, E+1
-        const bool more = E + 2 <= ke;
-        T q0, q1, q2, q3, s0, s1, s2, s3, nfe, nfo, nfe1, nfo1;
-        ld_phi(E + 2, q0, q1);
-        ld_phi(E + 3, q2, q3);
-        ld_sig(E + 1, s0, s1);
-        ld_sig(E + 2, s2, s3);
-        ld_f(E + 2, nfe, nfo);
-        ld_f(E + 1, nfe1, nfo1);
-        const int pm = (E - 1) & 3, pc = E & 3, pp = (E + 1) & 3, pmm = (E - 2) & 3;
-        const int sm = nod_m3(E - 1), sq = nod_m3(E), smm = nod_m3(E - 2);
-        const bool even_ok = plane_ok(E);
-        // A: colour 0 of plane E (ring 3)
-        T ve = T(0), vo = T(0);
-        if (st0 && even_ok) {
-            ve = update(wx, je, pm, pc, pp, sm, sq, fe0);
-            sp[pc][je][wx] = ve;
-        }
-        __syncthreads();
-        // B: colour 1 of plane E (ring 2); plane E written where this chunk owns it
-        if (st1 && even_ok) {
-            vo = update(wx, jo, pm, pc, pp, sm, sq, fo0);
-            sp[pc][jo][wx] = vo;
-        }
-        const bool own_e = even_ok && (E < ke || (E == ke && !L.pz && ke == etop));
-        if (own_e) {
-            const size_t o = (size_t)pw(E) * NxNy;
-            if (oute) out[o + ne] = ve;
-            if (outo) out[o + no] = vo;
-        }
-        __syncthreads();
-        if (E > ks) {
-            // C: colour 2 of plane E-1 (ring 1)
-            T ve2 = T(0), vo2 = T(0);
-            if (st2) {
-                ve2 = update(wx, je, pmm, pm, pc, smm, sm, fe1);
-                sp[pm][je][wx] = ve2;
-            }
-            __syncthreads();
-            // D: colour 3 of plane E-1 (tile); plane E-1 written
-            if (st3) vo2 = update(wx, jo, pmm, pm, pc, smm, sm, fo1);
-            const size_t o = (size_t)pw(E - 1) * NxNy;
-            if (oute) out[o + ne] = ve2;
-            if (outo) out[o + no] = vo2;
-        }
-        if (!more) break;
-        __syncthreads();                 // every read of planes E-2, E-1 and layers E-2, E-1 done
-        st_phi(E + 2, q0, q1);
-        st_phi(E + 3, q2, q3);
-        st_sig(E + 1, s0, s1);
-        st_sig(E + 2, s2, s3);
-        fe0 = nfe;
-        fo0 = nfo;
-        fe1 = nfe1;
-        fo1 = nfo1;
-        __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Residual on tiles staged in LDS: a workgroup owns RTX x RTY x RTZ nodes,
-// loads phi on the tile plus one node around it and sigma on the cells
-// touching the tile once (instead of each node gathering its 20 neighbours
-// and 8 cells from the caches), then evaluates r = f - L phi per node with
-// (L phi)_n = 1/(12 h^2) sum_c sigma_c (far corners - 4 phi_n), cells in the
-// order sz, sy, sx and far corners x+y, x+z, y+z, x+y+z.  Nodes beyond a wall read 0 and cells beyond it
-// sigma = 0 (their terms add exact zeros).  kStore: r written to L.r; kNorm:
-// the workgroup's partial row {sum r^2, 0, max |r|, #non-finite} at row
-// blockIdx.x.
-// ---------------------------------------------------------------------------
-constexpr int kRTX = 32, kRTY = 8, kRTZ = 8;
-constexpr int kRWX = kRTX + 2, kRWY = kRTY + 2, kRWZ = kRTZ + 2;      // node window
-constexpr int kRCX = kRTX + 1, kRCY = kRTY + 1, kRCZ = kRTZ + 1;      // cell window
-
+// r = f - L phi at node (I, J, K): cells sz, sy, sx, far corners x+y, x+z,
+// y+z, x+y+z of each.
 template <typename T>
-inline int nod_resid_tiles(const NodLevelT<T>& L) {
-    return ((L.Nx + kRTX - 1) / kRTX) * ((L.Ny + kRTY - 1) / kRTY) * ((L.Nz + kRTZ - 1) / kRTZ);
+__device__ inline T nod_resid_at(const NodLevelT<T>& L, int I, int J, int K) {
+    const NodAxis ax = nod_axis(I, L.Nx, L.nx, L.px);
+    const NodAxis ay = nod_axis(J, L.Ny, L.ny, L.py);
+    const NodAxis az = nod_axis(K, L.Nz, L.nz, L.pz);
+    NodNbr<T> N;
+    nod_load_nbrs(L, L.phi, I, ax, ay, az, J, K, N);
+    const size_t n = nidx(L, I, J, K);
+    const T pn = L.phi[n];
+    T sum = T(0);
+    for (int sz = 0; sz < 2; ++sz)
+        for (int sy = 0; sy < 2; ++sy)
+            for (int sx = 0; sx < 2; ++sx) {
+                if (!az.e[sz] || !ay.e[sy] || !ax.e[sx]) continue;
+                const int oz = 2 * sz, oy = 2 * sy, ox = 2 * sx;
+                const T sig = L.sig[cidx3(L, ax.c[sx], ay.c[sy], az.c[sz])];
+                T acc = T(0);
+                acc += N.v[1][oy][ox];
+                acc += N.v[oz][1][ox];
+                acc += N.v[oz][oy][1];
+                acc += N.v[oz][oy][ox];
+                sum += sig * (acc - T(4) * pn);
+            }
+    return L.f[n] - pdiv(sum, (T)(12.0 * L.h * L.h));
 }
 
-// The refinement step of a mixed-precision solve in the same pass (kRefine):
-// the window's phi is phi + corr / s (corr the FP32 V-cycle's correction,
-// s = scales[0] the scale its residual carried, a power of two), written out
-// of place for the tile's own nodes (neighbouring tiles read the old phi of
-// their halos), and the residual of the updated phi is written in FP32 times
-// scales[1] (the scale of the previous residual: lagged by one step, as the
-// reduction advances the scales afterwards).
-struct NodRefine {
-    const float* corr;
-    const double* scales;
-    double* phi_out;
-    float* r32;
-};
-
-template <typename T, bool kStore, bool kNorm, bool kRefine = false>
-__global__ __launch_bounds__(kRTX * kRTY) void k_nod_resid_tile(NodLevelT<T> L, double* __restrict__ partials,
-                                                                NodRefine ra = NodRefine{}) {
-    __shared__ __align__(16) T sphi[kRWZ][kRWY][kRWX];
-    __shared__ T ssig[kRCZ][kRCY][kRCX];
-    const int ntx = (L.Nx + kRTX - 1) / kRTX, nty = (L.Ny + kRTY - 1) / kRTY;
-    const int b = blockIdx.x;
-    const int I0 = (b % ntx) * kRTX, J0 = ((b / ntx) % nty) * kRTY, K0 = (b / (ntx * nty)) * kRTZ;
-    const int tid = threadIdx.x;
-    const size_t NxNy = (size_t)L.Nx * L.Ny, nxny = (size_t)L.nx * L.ny;
-    // A window index g one beyond either end of [0, n): the periodic image
-    // (one wrap; a ragged tile's positions beyond n + 1 are clamped, their
-    // values are never read) or, beyond a wall, absent.
-    auto at = [](int g, int n, int per, bool& ok) {
-        if (per) {
-            if (g < 0) g += n;
-            else if (g >= n) g -= n;
-            return min(g, n - 1);
-        }
-        ok = ok && g >= 0 && g < n;
-        return min(max(g, 0), n - 1);
-    };
-    // node window (nodes I0-1 .. I0+RTX, etc.) and cell window (cells I0-1
-    // .. I0+RTX-1: those around the tile's nodes), x fastest across the
-    // threads: every load of the thread is issued before any is stored, so
-    // they are all in flight together
-    constexpr int kNT = kRTX * kRTY;
-    constexpr int kPN = (kRWX * kRWY * kRWZ + kNT - 1) / kNT, kPC = (kRCX * kRCY * kRCZ + kNT - 1) / kNT;
-    T vp[kPN], vs[kPC];
-    const double inv_s = kRefine ? 1.0 / ra.scales[0] : 0.0;     // exact: a power of two
-    const double r_s = kRefine ? ra.scales[1] : 0.0;
-#pragma unroll
-    for (int q = 0; q < kPN; ++q) {
-        const int e = min(tid + q * kNT, kRWX * kRWY * kRWZ - 1);
-        const int x = e % kRWX, yz = e / kRWX, y = yz % kRWY, z = yz / kRWY;
-        bool ok = true;
-        const int I = at(I0 - 1 + x, L.Nx, L.px, ok), J = at(J0 - 1 + y, L.Ny, L.py, ok);
-        const int K = at(K0 - 1 + z, L.Nz, L.pz, ok);
-        const size_t n = (size_t)K * NxNy + (size_t)J * L.Nx + I;
-        vp[q] = L.phi[n];
-        if (kRefine) vp[q] = vp[q] + (double)ra.corr[n] * inv_s;   // the correction add's expression
-        if (!ok) vp[q] = T(0);
-    }
-#pragma unroll
-    for (int q = 0; q < kPC; ++q) {
-        const int e = min(tid + q * kNT, kRCX * kRCY * kRCZ - 1);
-        const int x = e % kRCX, yz = e / kRCX, y = yz % kRCY, z = yz / kRCY;
-        bool ok = true;
-        const int i = at(I0 - 1 + x, L.nx, L.px, ok), j = at(J0 - 1 + y, L.ny, L.py, ok);
-        const int k = at(K0 - 1 + z, L.nz, L.pz, ok);
-        vs[q] = L.sig[(size_t)k * nxny + (size_t)j * L.nx + i];
-        if (!ok) vs[q] = T(0);
-    }
-#pragma unroll
-    for (int q = 0; q < kPN; ++q) {
-        const int e = tid + q * kNT;
-        if (e < kRWX * kRWY * kRWZ) (&sphi[0][0][0])[e] = vp[q];
-    }
-#pragma unroll
-    for (int q = 0; q < kPC; ++q) {
-        const int e = tid + q * kNT;
-        if (e < kRCX * kRCY * kRCZ) (&ssig[0][0][0])[e] = vs[q];
-    }
-    __syncthreads();
-    const int tx = tid % kRTX, ty = tid / kRTX;
-    const int I = I0 + tx, J = J0 + ty;
-    const T ih = (T)(12.0 * L.h * L.h);
-    double s2 = 0.0, mx = 0.0, nonfin = 0.0;
-    if (I < L.Nx && J < L.Ny) {
-        for (int tz = 0; tz < kRTZ; ++tz) {
-            const int K = K0 + tz;
-            if (K >= L.Nz) break;
-            const int x = tx + 1, y = ty + 1, z = tz + 1;        // the node in the windows
-            const T pn = sphi[z][y][x];
-            T sum = T(0);
-#pragma unroll
-            for (int sz = 0; sz < 2; ++sz) {
-                const int zo = sz ? z + 1 : z - 1;
-#pragma unroll
-                for (int sy = 0; sy < 2; ++sy) {
-                    const int yo = sy ? y + 1 : y - 1;
-#pragma unroll
-                    for (int sx = 0; sx < 2; ++sx) {
-                        const int xo = sx ? x + 1 : x - 1;
-                        // the cell on side (sx, sy, sz) of the node: cell window index node - 1 + s
-                        const T sig = ssig[z - 1 + sz][y - 1 + sy][x - 1 + sx];
-                        T acc = T(0);
-                        acc += sphi[z][yo][xo];
-                        acc += sphi[zo][y][xo];
-                        acc += sphi[zo][yo][x];
-                        acc += sphi[zo][yo][xo];
-                        sum += sig * (acc - T(4) * pn);
-                    }
-                }
-            }
-            const size_t n = (size_t)K * NxNy + (size_t)J * L.Nx + I;
-            const T r = L.f[n] - pdiv(sum, ih);
-            if (kStore) L.r[n] = r;
-            if (kRefine) {
-                ra.phi_out[n] = pn;
-                ra.r32[n] = (float)(r * r_s);
-            }
-            if (kNorm) {
-                const double rd = (double)r;
-                if (!isfinite(rd)) nonfin += 1.0;
-                s2 += rd * rd;
-                mx = fmax(mx, fabs(rd));
-            }
-        }
-    }
-    if (kNorm) {
-        // fixed-order tree over the workgroup, in the (now free) phi window
-        static_assert(sizeof(sphi) >= 3 * kRTX * kRTY * sizeof(double), "reduction buffer");
-        double* red = reinterpret_cast<double*>(&sphi[0][0][0]);
-        constexpr int nt = kRTX * kRTY;
-        __syncthreads();
-        red[tid] = s2;
-        red[nt + tid] = mx;
-        red[2 * nt + tid] = nonfin;
-        __syncthreads();
-        for (int w = nt / 2; w > 0; w >>= 1) {
-            if (tid < w) {
-                red[tid] = red[tid] + red[tid + w];
-                red[nt + tid] = fmax(red[nt + tid], red[nt + tid + w]);
-                red[2 * nt + tid] = red[2 * nt + tid] + red[2 * nt + tid + w];
-            }
-            __syncthreads();
-        }
-        if (tid == 0) {
-            double* row = partials + (size_t)b * kReduceWidth;
-            row[0] = red[0];
-            row[1] = 0.0;
-            row[2] = red[nt];
-            row[3] = red[2 * nt];
-        }
-    }
-}
-
-// coarse f = 1/8 sum_d w(d) r_{2C+d} (existing fine nodes), coarse phi = 0.
+// Restricted residual of a level of the bottom kernel launched by itself: the
+// bottom kernel's sums, each coarse node forming the residuals around it.
 template <typename T>
-__global__ void k_nod_restrict(NodLevelT<T> F, NodLevelT<T> C) {
-    const int I = blockIdx.x * blockDim.x + threadIdx.x;
-    const int J = blockIdx.y * blockDim.y + threadIdx.y;
-    const int K = blockIdx.z * blockDim.z + threadIdx.z;
-    if (I >= C.Nx || J >= C.Ny || K >= C.Nz) return;
-    const int X[3] = {2 * I, 2 * J, 2 * K};
+__global__ __launch_bounds__(64) void k_nod_restrict_each(NodLevelT<T> F, NodLevelT<T> C) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= (int)C.nodes()) return;
+    const int X[3] = {2 * (c % C.Nx), 2 * (c / C.Nx % C.Ny), 2 * (c / (C.Nx * C.Ny))};
     const int Nn[3] = {F.Nx, F.Ny, F.Nz}, per[3] = {F.px, F.py, F.pz};
     T s = T(0);
-    for (int dz = -1; dz <= 1; ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int D[3] = {dx, dy, dz};
-                int m[3];
-                bool ok = true;
-                T w = T(1);
-                for (int d = 0; d < 3; ++d) {
-                    m[d] = nod_node(X[d], D[d], Nn[d], per[d]);
-                    if (m[d] < 0) ok = false;
-                    if (D[d] != 0) w *= T(0.5);
-                }
-                if (ok) s += w * F.r[nidx(F, m[0], m[1], m[2])];
-            }
-    const size_t c = nidx(C, I, J, K);
+    for (int d = 0; d < 27; ++d) {
+        const int D[3] = {d % 3 - 1, d / 3 % 3 - 1, d / 9 - 1};
+        int m[3];
+        bool ok = true;
+        T w = T(1);
+        for (int i = 0; i < 3; ++i) {
+            m[i] = nod_node(X[i], D[i], Nn[i], per[i]);
+            if (m[i] < 0) ok = false;
+            if (D[i] != 0) w *= T(0.5);
+        }
+        if (ok) s += w * nod_resid_at(F, m[0], m[1], m[2]);
+    }
     C.f[c] = T(0.125) * s;
     C.phi[c] = T(0);
 }
@@ -1230,7 +828,7 @@ struct nodal_hierarchy {
     mg_params p{};
     int nlev = 0;
     NodLevel lev[kMaxLevels];
-    // mixed precision: FP32 mirrors of every level (sigma, phi, f, r, phi2),
+    // mixed precision: FP32 mirrors of every level (sigma, phi, f, phi2),
     // the inner V-cycle's arrays
     bool mixed = false;
     NodLevelT<float> lev32[kMaxLevels];
@@ -1272,12 +870,14 @@ int nod_count_levels(const mg_params* p) {
     return nodes <= kCoarseMax ? n : 0;
 }
 
-// Partial-sum rows of the finest level's residual norm.
-size_t nod_partial_rows(const NodLevel& L0) { return std::max<size_t>(2048, (size_t)nod_resid_tiles(L0)); }
+// Partial-sum rows: of the point loops, and of the finest level's residual norm.
+size_t nod_partial_rows(const NodLevel& L0) {
+    return std::max<size_t>(2048, (size_t)nod_resid_grid(L0, L0.Nz, false).blocks());
+}
 
 // Level shapes of a hierarchy of nl levels for p (into lev), and the device
-// bytes it needs: per level sigma on cells and phi, f, r, phi2 on nodes (in
-// mixed precision also FP32 copies of all five); the coarsest level's dense
+// bytes it needs: per level sigma on cells and phi, f, phi2 on nodes (in
+// mixed precision also FP32 copies of all four); the coarsest level's dense
 // inverse, the partial rows and the scalar block.
 size_t nod_layout(const mg_params* p, int nl, NodLevel* lev) {
     size_t bytes = 0;
@@ -1294,8 +894,8 @@ size_t nod_layout(const mg_params* p, int nl, NodLevel* lev) {
         L.Ny = L.ny + (L.py ? 0 : 1);
         L.Nz = L.nz + (L.pz ? 0 : 1);
         L.h = p->dx * (double)(1 << l);
-        bytes += al(L.cells() * 8) + 4 * al(L.nodes() * 8);
-        if (p->precision == MG_MIXED) bytes += al(L.cells() * 4) + 4 * al(L.nodes() * 4);
+        bytes += al(L.cells() * 8) + 3 * al(L.nodes() * 8);
+        if (p->precision == MG_MIXED) bytes += al(L.cells() * 4) + 3 * al(L.nodes() * 4);
     }
     const size_t nc = lev[nl - 1].nodes();
     bytes += al(nc * nc * 8) + al(nod_partial_rows(lev[0]) * kReduceWidth * 8) + al(64 * 8);
@@ -1316,42 +916,41 @@ int nod_reduce(nodal_hierarchy* H, int nparts, int slot, hipStream_t st) {
     return MG_OK;
 }
 
-// The fused sweep takes levels whose colouring is consistent across periodic
-// wraps (even node counts there), an even number of node planes to march
-// (the top plane of a walled z is even) and at least one 32 x 8 tile.
-template <typename T>
-bool nod_sweep_fits(const NodLevelT<T>& L) {
-    if (L.Nx < 32 || L.Ny < 16) return false;
-    if (L.py && L.Ny % 2 != 0) return false;
-    if (L.pz ? (L.Nz % 2 != 0) : (L.nz % 2 != 0)) return false;
-    return (L.pz ? L.Nz : L.Nz - 1) >= 2;
-}
-
-template <typename T, int TX, int TY>
-hipError_t launch_nod_sweep_t(const NodLevelT<T>& L, T* out, int tz, hipStream_t st) {
-    const int etop = L.pz ? L.Nz : L.Nz - 1;
-    const int ntx = (L.Nx + TX - 1) / TX, nty = (L.Ny + TY - 1) / TY, nch = (etop + tz - 1) / tz;
-    hipLaunchKernelGGL((k_nod_sweep<T, TX, TY>), dim3(ntx * nty * nch), dim3((TX + 8) * (TY + 8) / 2), 0, st, L,
-                       out, tz, ntx, nty, etop);
-    return hipGetLastError();
-}
-
-// Fused-sweep tiles (TX x TY nodes, tz planes per chunk).
+// Fused-sweep tiles: 56 x (2 pairs - 8) nodes, tz planes per chunk.
 struct NodSweepCfg {
-    int tx, ty, tz;
+    int pairs, tz;
 };
 constexpr int kNumNodSweepCfg = 8;
-constexpr NodSweepCfg kNodSweepCfgs[kNumNodSweepCfg] = {{64, 8, 32}, {32, 8, 32}, {32, 16, 32}, {64, 16, 32},
-                                                       {64, 8, 64}, {32, 8, 16}, {32, 16, 64}, {64, 8, 16}};
-std::atomic<int> g_nod_cfg{-1};                  // forced configuration (-1: the default below)
+constexpr NodSweepCfg kNodSweepCfgs[kNumNodSweepCfg] = {{8, 2},   {8, 4},   {8, 8},   {8, 16},
+                                                       {12, 16}, {12, 32}, {16, 32}, {16, 64}};
+std::atomic<int> g_nod_cfg{-1};                  // forced configuration (-1: the rule below)
+
+// Configuration of a level's sweep by its nodes.  Small levels are short of
+// workgroups and bound by the steps of one march, so they take few planes per
+// chunk; large ones are bound by instruction issue and HBM, where the halo
+// (rows and the repeated top plane) is what a bigger tile and longer chunk
+// save.  us per sweep in FP64, this choice / the next better one: 32^3 nodes
+// 7.0 / 8.9 (8 pairs x 4 planes), 64^3 9.4 / 10.4 (8 x 2), 128^3 26.4 / 28.1
+// (12 x 16; with the prolongation, whose 132 registers let 8-pair workgroups
+// no longer share a compute unit, 30.6 with 12 x 16 / 41 with 8 x 8), 192^3
+// 61 / 66 (8 x 16), 256^3 144 / 149 (16 x 32); in FP32 64^3 7.3, 128^3 18.2,
+// 192^3 40, 256^3 65 / 71 (12 x 32), 384 x 384 x 256 163.
+template <typename T>
+int nod_sweep_config(const NodLevelT<T>& L, bool prolong) {
+    const double n = (double)L.nodes();
+    if (n < 1e5) return 0;
+    if (n < 1e6) return 1;
+    if (sizeof(T) == 4) return n < 4e6 ? 2 : 4;
+    if (n < 4e6) return prolong ? 4 : 2;
+    return n < 12e6 ? 6 : 7;
+}
 
 template <typename T>
-hipError_t launch_nod_sweep(const NodLevelT<T>& L, T* out, int cfg, hipStream_t st) {
+hipError_t launch_nod_sweep(const NodLevelT<T>& L, T* out, int cfg, const NodLevelT<T>* coarse, hipStream_t st) {
     const NodSweepCfg& c = kNodSweepCfgs[cfg];
-    if (c.tx == 64 && c.ty == 8) return launch_nod_sweep_t<T, 64, 8>(L, out, c.tz, st);
-    if (c.tx == 32 && c.ty == 8) return launch_nod_sweep_t<T, 32, 8>(L, out, c.tz, st);
-    if (c.tx == 32 && c.ty == 16) return launch_nod_sweep_t<T, 32, 16>(L, out, c.tz, st);
-    return launch_nod_sweep_t<T, 64, 16>(L, out, c.tz, st);
+    if (c.pairs == 8) return launch_nod_sweep_t<T, 8>(L, out, c.tz, coarse, st);
+    if (c.pairs == 12) return launch_nod_sweep_t<T, 12>(L, out, c.tz, coarse, st);
+    return launch_nod_sweep_t<T, 16>(L, out, c.tz, coarse, st);
 }
 
 // The levels a V-cycle in T runs on: the FP64 hierarchy, or its FP32 mirrors.
@@ -1361,63 +960,6 @@ template <>
 NodLevelT<double>* nod_levels<double>(nodal_hierarchy* H) { return H->lev; }
 template <>
 NodLevelT<float>* nod_levels<float>(nodal_hierarchy* H) { return H->lev32; }
-
-// Sweeps on level l: the fused out-of-place sweep where it fits (the level's
-// two phi buffers swap), else one in-place launch per colour.
-template <typename T = double>
-int nod_smooth(nodal_hierarchy* H, int l, int nsweeps, hipStream_t st) {
-    NodLevelT<T>& L = nod_levels<T>(H)[l];
-    // default: the fused sweep on levels of 4M nodes or more, 32 x 16 tiles
-    // of 32-plane chunks (measured on MI355X: 215 us per 256^3 sweep against
-    // 346 us for four colour launches; on a 128^3 level the colour launches
-    // are faster); a forced configuration applies wherever it fits
-    int cfg = g_nod_cfg.load();
-    if (cfg >= 0 && (L.Nx < kNodSweepCfgs[cfg].tx || L.Ny < kNodSweepCfgs[cfg].ty)) cfg = -1;
-    const bool fused = nod_sweep_fits(L) && (cfg >= 0 || L.nodes() >= ((size_t)4 << 20));
-    if (fused) {
-        if (cfg < 0) cfg = 2;
-        for (int s = 0; s < nsweeps; ++s) {
-            NHIP(launch_nod_sweep(L, L.phi2, cfg, st));
-            std::swap(L.phi, L.phi2);
-        }
-        return MG_OK;
-    }
-    const dim3 block(64, 2, 2);
-    const dim3 grid = grid3(L.Nx, (L.Ny + 1) / 2, (L.Nz + 1) / 2, block);
-    for (int s = 0; s < nsweeps; ++s)
-        for (int col = 0; col < 4; ++col) hipLaunchKernelGGL(k_nod_gs<T>, grid, block, 0, st, L, col);
-    NHIP(hipGetLastError());
-    return MG_OK;
-}
-
-template <typename T = double>
-int nod_resid_restrict(nodal_hierarchy* H, int l, hipStream_t st) {
-    const NodLevelT<T>& F = nod_levels<T>(H)[l];
-    const NodLevelT<T>& C = nod_levels<T>(H)[l + 1];
-    hipLaunchKernelGGL((k_nod_resid_tile<T, true, false>), dim3(nod_resid_tiles(F)), dim3(kRTX * kRTY), 0, st, F,
-                       (double*)nullptr);
-    const dim3 block(32, 4, 2);
-    hipLaunchKernelGGL(k_nod_restrict<T>, grid3(C.Nx, C.Ny, C.Nz, block), block, 0, st, F, C);
-    NHIP(hipGetLastError());
-    return MG_OK;
-}
-
-template <typename T = double>
-int nod_prolong(nodal_hierarchy* H, int l, hipStream_t st) {
-    const NodLevelT<T>& F = nod_levels<T>(H)[l];
-    const NodLevelT<T>& C = nod_levels<T>(H)[l + 1];
-    const dim3 block(32, 4, 2);
-    hipLaunchKernelGGL(k_nod_prolong<T>, grid3(C.Nx, C.Ny, C.Nz, block), block, 0, st, F, C);
-    NHIP(hipGetLastError());
-    return MG_OK;
-}
-
-hipError_t nod_coarse_solve(int n, const double* minv, const double* f, double* phi, hipStream_t st) {
-    return launch_coarse_solve(n, minv, f, phi, st, 1);
-}
-hipError_t nod_coarse_solve(int n, const double* minv, const float* f, float* phi, hipStream_t st) {
-    return launch_coarse_solve_f32(n, minv, f, phi, st, 1);
-}
 
 // First level (>= 1, above the coarsest) that the bottom kernel takes with
 // every coarser one, or -1.
@@ -1438,6 +980,73 @@ int nod_bottom_start(const nodal_hierarchy* H) {
         return l;
     }
     return -1;
+}
+
+// Whether level l is one of the bottom kernel's: launched one by one (the
+// bottom off) these keep the per-node sums that it repeats bit for bit.
+template <typename T>
+bool nod_in_bottom(const nodal_hierarchy* H, int l) {
+    const int b = nod_bottom_start<T>(H);
+    return b >= 0 && l >= b;
+}
+
+// Whether level l takes the fused out-of-place sweep (its two phi buffers
+// swap): wherever the march fits above the bottom kernel's levels.
+template <typename T>
+bool nod_fused(const nodal_hierarchy* H, int l) {
+    return nod_sweep_fits(nod_levels<T>(const_cast<nodal_hierarchy*>(H))[l]) && !nod_in_bottom<T>(H, l);
+}
+
+// Sweeps on level l: fused, the first one of phi + P C.phi where coarse is
+// given, else one in-place launch per colour.
+template <typename T = double>
+int nod_smooth(nodal_hierarchy* H, int l, int nsweeps, hipStream_t st, const NodLevelT<T>* coarse = nullptr) {
+    NodLevelT<T>& L = nod_levels<T>(H)[l];
+    if (nod_fused<T>(H, l)) {
+        const int forced = g_nod_cfg.load();
+        for (int s = 0; s < nsweeps; ++s) {
+            const NodLevelT<T>* c = s == 0 ? coarse : nullptr;
+            NHIP(launch_nod_sweep(L, L.phi2, forced >= 0 ? forced : nod_sweep_config(L, c != nullptr), c, st));
+            std::swap(L.phi, L.phi2);
+        }
+        return MG_OK;
+    }
+    const dim3 block(64, 2, 2);
+    const dim3 grid = grid3(L.Nx, (L.Ny + 1) / 2, (L.Nz + 1) / 2, block);
+    for (int s = 0; s < nsweeps; ++s)
+        for (int col = 0; col < 4; ++col) hipLaunchKernelGGL(k_nod_gs<T>, grid, block, 0, st, L, col);
+    NHIP(hipGetLastError());
+    return MG_OK;
+}
+
+template <typename T = double>
+int nod_resid_restrict(nodal_hierarchy* H, int l, hipStream_t st) {
+    const NodLevelT<T>& F = nod_levels<T>(H)[l];
+    const NodLevelT<T>& C = nod_levels<T>(H)[l + 1];
+    if (nod_in_bottom<T>(H, l)) {
+        hipLaunchKernelGGL(k_nod_restrict_each<T>, dim3(((int)C.nodes() + 63) / 64), dim3(64), 0, st, F, C);
+        NHIP(hipGetLastError());
+        return MG_OK;
+    }
+    NHIP((launch_nod_resid<T, kNodRestrict>(F, C, nullptr, NodRefine{}, nullptr, st)));
+    return MG_OK;
+}
+
+template <typename T = double>
+int nod_prolong(nodal_hierarchy* H, int l, hipStream_t st) {
+    const NodLevelT<T>& F = nod_levels<T>(H)[l];
+    const NodLevelT<T>& C = nod_levels<T>(H)[l + 1];
+    const dim3 block(32, 4, 2);
+    hipLaunchKernelGGL(k_nod_prolong<T>, grid3(C.Nx, C.Ny, C.Nz, block), block, 0, st, F, C);
+    NHIP(hipGetLastError());
+    return MG_OK;
+}
+
+hipError_t nod_coarse_solve(int n, const double* minv, const double* f, double* phi, hipStream_t st) {
+    return launch_coarse_solve(n, minv, f, phi, st, 1);
+}
+hipError_t nod_coarse_solve(int n, const double* minv, const float* f, float* phi, hipStream_t st) {
+    return launch_coarse_solve_f32(n, minv, f, phi, st, 1);
 }
 
 // V-cycle from level l in T (the coarsest solve applies the FP64 inverse).
@@ -1465,6 +1074,8 @@ int nod_vcycle(nodal_hierarchy* H, int l, hipStream_t st) {
     if (rc) return rc;
     rc = nod_vcycle<T>(H, l + 1, st);
     if (rc) return rc;
+    if (H->p.post_sweeps > 0 && nod_fused<T>(H, l))
+        return nod_smooth<T>(H, l, H->p.post_sweeps, st, &nod_levels<T>(H)[l + 1]);
     rc = nod_prolong<T>(H, l, st);
     if (rc) return rc;
     return nod_smooth<T>(H, l, H->p.post_sweeps, st);
@@ -1519,7 +1130,7 @@ int nod_solve_mixed(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status_
     H->host[kSlotScale * kReduceWidth] = s0;
     H->host[kSlotScale * kReduceWidth + 1] = s0;
     NHIP(hipMemcpyAsync(scales, H->host + kSlotScale * kReduceWidth, 2 * sizeof(double), hipMemcpyHostToDevice, st));
-    const int nt = nod_resid_tiles(L0);
+    int nt = 0;
     int status = MG_ERR_NOT_CONVERGED, cycles = 0;
     double rel = 1.0;
     // nodal default one: its FP32 V-cycle costs several refinement passes
@@ -1535,9 +1146,7 @@ int nod_solve_mixed(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status_
         // next cycle, in one pass (phi out of place); the reduction then
         // advances the scales
         const NodRefine ra{M0.phi, scales, L0.phi2, M0.f};
-        hipLaunchKernelGGL((k_nod_resid_tile<double, false, true, true>), dim3(nt), dim3(kRTX * kRTY), 0, st, L0,
-                           H->partials, ra);
-        NHIP(hipGetLastError());
+        NHIP((launch_nod_resid<double, kNodRefine>(L0, L0, H->partials, ra, &nt, st)));
         std::swap(L0.phi, L0.phi2);
         NHIP(launch_reduce_scale(H->partials, nt, H->scal + kSlotRes * kReduceWidth, scales, NN, st));
         NHIP(hipMemcpyAsync(H->host + kSlotRes * kReduceWidth, H->scal + kSlotRes * kReduceWidth,
@@ -1619,10 +1228,9 @@ int nod_project(nodal_hierarchy* H, const double* rho, const double* b0c, const 
         auto cycle = [&](hipStream_t s) -> int {
             int r2 = nod_vcycle(H, 0, s);
             if (r2) return r2;
-            hipLaunchKernelGGL((k_nod_resid_tile<double, false, true>), dim3(nod_resid_tiles(L0)),
-                               dim3(kRTX * kRTY), 0, s, L0, H->partials);
-            NHIP(hipGetLastError());
-            NHIP(launch_reduce(H->partials, nod_resid_tiles(L0), H->scal + kSlotRes * kReduceWidth, s));
+            int nt = 0;
+            NHIP((launch_nod_resid<double, kNodNorm>(L0, L0, H->partials, NodRefine{}, &nt, s)));
+            NHIP(launch_reduce(H->partials, nt, H->scal + kSlotRes * kReduceWidth, s));
             NHIP(hipMemcpyAsync(H->host + kSlotRes * kReduceWidth, H->scal + kSlotRes * kReduceWidth,
                                 kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, s));
             return MG_OK;
@@ -1811,7 +1419,6 @@ int nodal_setup(const mg_params* p, nodal_handle* out) {
         L.sig = take(L.cells() * 8);
         L.phi = take(L.nodes() * 8);
         L.f = take(L.nodes() * 8);
-        L.r = take(L.nodes() * 8);
         L.phi2 = take(L.nodes() * 8);
     }
     H->mixed = p->precision == MG_MIXED;
@@ -1827,7 +1434,6 @@ int nodal_setup(const mg_params* p, nodal_handle* out) {
             M.sig = take32(L.cells());
             M.phi = take32(L.nodes());
             M.f = take32(L.nodes());
-            M.r = take32(L.nodes());
             M.phi2 = take32(L.nodes());
         }
     }
