@@ -300,9 +300,10 @@ int nodal_project(nodal_handle h, const double* rho, const double* beta0_cc, con
 int nodal_tune_sweep(int32_t cfg);
 /* Coefficients only (for the single steps below). */
 int nodal_set_coefficients(nodal_handle h, const double* rho, const double* beta0_cc, void* stream);
-/* enable = 1 (the default): the V-cycle and the residual norm after it run as
- * one captured hipGraph replayed every cycle (all buffers are fixed);
- * results are identical either way. */
+/* enable = 1: the V-cycle and the residual norm after it run as one captured
+ * hipGraph replayed every cycle (all buffers are fixed); 0 (the default, and
+ * faster): separate launches on the caller's stream.  Results are identical
+ * either way. */
 int nodal_set_graphs(nodal_handle h, int32_t enable);
 /* enable = 1 (the default): the coarse levels that fit in one workgroup's LDS
  * (phi, residual and sigma, with every coarser level's) run as one workgroup per V-cycle
@@ -430,13 +431,14 @@ int mg_tune_cache_clear(void);
 int mg_tune_record(const char* arch, const int32_t n[3], int32_t rho, int32_t fp64, int32_t coarse, int32_t cfg);
 int mg_tune_lookup(const char* arch, const int32_t n[3], int32_t rho, int32_t fp64, int32_t coarse);
 
-/* Replayable cycles: with enable = 1 (the default) an FP64 solve captures
+/* Replayable cycles: with enable = 1 a solve captures
  * one V-cycle plus the following residual-norm sweep as a hipGraph on the
  * hierarchy's own stream the first time it needs it, and replays it for the
  * later cycles and solves whose buffers, coefficient source, sweep counts
  * and tile choices match (at most two captures are kept per hierarchy).
- * Results are identical either way; 0 runs every cycle as separate launches
- * on the caller's stream. */
+ * Results are identical either way; 0 (the default, and faster: the host keeps
+ * ahead of the device) runs every cycle as separate launches on the caller's
+ * stream. */
 int mg_set_graphs(mg_handle h, int32_t enable);
 
 /* Bottom of the V-cycle: with enable = 1 (the default) the levels of at most

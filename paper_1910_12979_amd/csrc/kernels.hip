@@ -181,10 +181,11 @@ __global__ __launch_bounds__(kBlock) void k_coeff_rhs(CoeffDesc a) {
 __device__ void next_scale(const double* res, double* scales, double n);
 
 // Sum of the partial rows into out; with scales, also the next power-of-two
-// scale of the FP32 residual from out[0] (next_scale), in the same launch.
+// scale of the FP32 residual from out[0] (next_scale), in the same launch;
+// with a ring, also appended to it (restart: the ring emptied instead).
 __global__ __launch_bounds__(kBlock) void k_reduce(const double* __restrict__ partials, int nparts,
                                                    double* __restrict__ out, double* __restrict__ scales,
-                                                   double n) {
+                                                   double n, NormRing ring, int restart) {
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     for (int r = threadIdx.x; r < nparts; r += kBlock) {
         const double* p = partials + (size_t)r * kReduceWidth;
@@ -194,7 +195,15 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const double* __restrict__ pa
         a3 += p[3];
     }
     block_reduce_row(a0, a1, a2, a3, out);
-    if (scales && threadIdx.x == 0 && threadIdx.y == 0) next_scale(out, scales, n);   // out written by this thread
+    if (threadIdx.x == 0 && threadIdx.y == 0) {       // out written by this thread
+        if (scales) next_scale(out, scales, n);
+        if (ring.count) {
+            const int c = restart ? 0 : *ring.count;
+            if (!restart)
+                for (int q = 0; q < kReduceWidth; ++q) ring.rows[(c % kNormRing) * kReduceWidth + q] = out[q];
+            *ring.count = restart ? 0 : c + 1;
+        }
+    }
 }
 
 // Workgroup b of nb: f -= shift over its strided cells, partial row {sum f^2}.
@@ -216,9 +225,12 @@ __device__ void sum_body(size_t N, const double* __restrict__ a, double* __restr
     block_reduce_row(s, 0.0, 0.0, 0.0, partials + (size_t)b * kReduceWidth);
 }
 
+// shift: sum[0] / N with a sum on the device (the host's division, bit for
+// bit), else the given one.
 __global__ __launch_bounds__(kBlock) void k_shift_norm(size_t N, double* __restrict__ f, double shift,
+                                                       const double* __restrict__ sum,
                                                        double* __restrict__ partials) {
-    shift_norm_body(N, f, shift, partials, blockIdx.x, gridDim.x);
+    shift_norm_body(N, f, sum ? sum[0] / (double)N : shift, partials, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(kBlock) void k_sum(size_t N, const double* __restrict__ a,
@@ -1037,21 +1049,23 @@ hipError_t launch_coeff(const Shape& s, int px, int py, int pz, const double* rh
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double* partials, int nparts, double* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, st, partials, nparts, out, (double*)nullptr, 0.0);
+hipError_t launch_reduce(const double* partials, int nparts, double* out, hipStream_t st, NormRing ring,
+                         bool restart) {
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, st, partials, nparts, out, (double*)nullptr, 0.0, ring,
+                       restart ? 1 : 0);
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_scale(const double* partials, int nparts, double* out, double* scales, size_t n,
-                               hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, st, partials, nparts, out, scales, (double)n);
+                               hipStream_t st, NormRing ring) {
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, st, partials, nparts, out, scales, (double)n, ring, 0);
     return hipGetLastError();
 }
 
 hipError_t launch_shift_norm(const Shape& s, double* f, double shift, double* partials, int* nparts,
-                             hipStream_t st) {
+                             hipStream_t st, const double* sum) {
     int nb = partial_blocks(s.N());
-    hipLaunchKernelGGL(k_shift_norm, dim3(nb), dim3(kBlock), 0, st, s.N(), f, shift, partials);
+    hipLaunchKernelGGL(k_shift_norm, dim3(nb), dim3(kBlock), 0, st, s.N(), f, shift, sum, partials);
     *nparts = nb;
     return hipGetLastError();
 }

@@ -839,12 +839,14 @@ struct nodal_hierarchy {
     double* host = nullptr;
     bool coeffs_valid = false;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    // One V-cycle plus the finest residual norm (copied to host) as a
+    // One V-cycle plus the finest residual norm as a
     // replayable hipGraph on the hierarchy's own stream, keyed by the sweep
     // counts and every level's phi buffers at the start of the cycle (the
     // fused sweeps swap them; with an even number of sweeps a cycle they
     // come back, so one capture serves every cycle of every solve).
-    bool graphs_on = true;
+    // Off unless asked for: slower than separate launches enqueued ahead (64^3
+    // 1128 us a projection against 1074, 128^3 2011 against 1938).
+    bool graphs_on = false;
     bool bottom_on = true;      // the coarse levels that fit in LDS run in one workgroup (k_nod_bottom)
     hipStream_t gstream = nullptr;
     hipEvent_t gev = nullptr;
@@ -1111,6 +1113,51 @@ int nod_coefficients(nodal_hierarchy* H, const double* rho, const double* b0c, c
     return MG_OK;
 }
 
+// The iterations of a solve, `enqueue` putting one on the stream that `stream`
+// then names: as many at a time as norm_ahead allows.  *over: converged before
+// the last one enqueued, so that the solve has to be run again without looking
+// ahead.
+template <typename E, typename Q>
+int nod_cycles(nodal_hierarchy* H, double fnorm, mg_stats* S_, bool ahead, int* status, int* cycles, double* rel,
+               bool* over, E&& enqueue, Q&& stream) {
+    double best = 0.0;
+    *over = false;
+    *status = MG_ERR_NOT_CONVERGED;
+    while (*cycles < H->p.max_cycles) {
+        const int m = ahead ? norm_ahead(*rel, best, H->p.rtol, H->p.max_cycles - *cycles) : 1;
+        for (int i = 0; i < m; ++i) {
+            int rc = enqueue();
+            if (rc) return rc;
+        }
+        const hipStream_t st = stream();
+        NHIP(hipMemcpyAsync(H->host + kSlotRing * kReduceWidth, H->scal + kSlotRing * kReduceWidth,
+                            kNormRing * kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, st));
+        NHIP(hipStreamSynchronize(st));
+        for (int i = 0; i < m; ++i) {
+            const double* r = H->host + (kSlotRing + *cycles % kNormRing) * kReduceWidth;
+            const double was = *rel;
+            *rel = std::sqrt(r[0]) / fnorm;
+            ++*cycles;
+            if (*cycles < MG_HIST_MAX) {
+                S_->resid_hist[*cycles] = *rel;
+                S_->hist_len = *cycles + 1;
+            }
+            if (r[3] > 0.0 || !std::isfinite(*rel)) {
+                set_error("non-finite residual during the solve");
+                *status = MG_ERR_NONFINITE;
+                return MG_OK;
+            }
+            if (*rel <= H->p.rtol) {
+                *status = MG_OK;
+                *over = i + 1 < m;
+                return MG_OK;
+            }
+            best = *cycles == 1 ? *rel / was : std::min(best, *rel / was);
+        }
+    }
+    return MG_OK;
+}
+
 // Mixed-precision solve (iterative refinement with the multigrid of Sec. 3
 // as its inner solver): each iteration runs one FP32 V-cycle from zero on the
 // FP64 residual scaled by the power of two nearest 1/rms(r), adds the FP32
@@ -1118,7 +1165,7 @@ int nod_coefficients(nodal_hierarchy* H, const double* rho, const double* b0c, c
 // recomputes r = f - L phi and its norm in FP64; the stop test is the FP64
 // solve's.  Returns MG_OK or a launch error; *status is the solve's.
 int nod_solve_mixed(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status_out, int* cycles_out,
-                    double* rel_out, hipStream_t st) {
+                    double* rel_out, bool ahead, bool* over, hipStream_t st) {
     NodLevel& L0 = H->lev[0];
     NodLevelT<float>& M0 = H->lev32[0];
     const size_t NN = L0.nodes();
@@ -1136,7 +1183,7 @@ int nod_solve_mixed(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status_
     // nodal default one: its FP32 V-cycle costs several refinement passes
     // (256^3: two per step took 8.90 ms against 8.19 with one)
     const int inner = H->p.inner_cycles > 0 ? H->p.inner_cycles : 1;
-    while (cycles < H->p.max_cycles) {
+    auto cycle = [&]() -> int {
         NHIP(launch_fill<float>(M0.phi, NN, 0.0f, st));
         for (int c = 0; c < inner; ++c) {                 // the FP32 correction: V-cycles from zero
             int rc = nod_vcycle<float>(H, 0, st);
@@ -1148,32 +1195,83 @@ int nod_solve_mixed(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status_
         const NodRefine ra{M0.phi, scales, L0.phi2, M0.f};
         NHIP((launch_nod_resid<double, kNodRefine>(L0, L0, H->partials, ra, &nt, st)));
         std::swap(L0.phi, L0.phi2);
-        NHIP(launch_reduce_scale(H->partials, nt, H->scal + kSlotRes * kReduceWidth, scales, NN, st));
-        NHIP(hipMemcpyAsync(H->host + kSlotRes * kReduceWidth, H->scal + kSlotRes * kReduceWidth,
-                            kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, st));
-        NHIP(hipStreamSynchronize(st));
-        ++cycles;
-        const double* r = H->host + kSlotRes * kReduceWidth;
-        rel = std::sqrt(r[0]) / fnorm;
-        if (cycles < MG_HIST_MAX) {
-            S_->resid_hist[cycles] = rel;
-            S_->hist_len = cycles + 1;
-        }
-        if (r[3] > 0.0 || !std::isfinite(rel)) {
-            set_error("non-finite residual during the solve");
-            status = MG_ERR_NONFINITE;
-            break;
-        }
-        if (rel <= H->p.rtol) {
-            status = MG_OK;
-            break;
-        }
-        if (cycles >= H->p.max_cycles) break;
-    }
+        NHIP(launch_reduce_scale(H->partials, nt, H->scal + kSlotRes * kReduceWidth, scales, NN, st,
+                                 norm_ring(H->scal)));
+        return MG_OK;
+    };
+    int rc = nod_cycles(H, fnorm, S_, ahead, &status, &cycles, &rel, over, cycle, [&] { return st; });
+    if (rc) return rc;
     *status_out = status;
     *cycles_out = cycles;
     *rel_out = rel;
     return MG_OK;
+}
+
+// FP64 solve: V-cycles on phi, each with the finest residual norm after it,
+// from a captured graph where the levels' buffers come back.
+int nod_solve(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status, int* cycles, double* rel, bool ahead,
+              bool* over, hipStream_t st) {
+    NodLevel& L0 = H->lev[0];
+    bool on_graph = false;
+    auto cycle = [&](hipStream_t s) -> int {
+        int r2 = nod_vcycle(H, 0, s);
+        if (r2) return r2;
+        int nt = 0;
+        NHIP((launch_nod_resid<double, kNodNorm>(L0, L0, H->partials, NodRefine{}, &nt, s)));
+        NHIP(launch_reduce(H->partials, nt, H->scal + kSlotRes * kReduceWidth, s, norm_ring(H->scal)));
+        return MG_OK;
+    };
+    // a captured cycle bakes in the levels' phi buffers: replayable when
+    // every level's buffers come back (an even number of sweeps a cycle)
+    const bool graphs = H->graphs_on && (H->p.pre_sweeps + H->p.post_sweeps) % 2 == 0;
+    auto enqueue = [&]() -> int {
+        if (!graphs) return cycle(st);
+        if (!H->gstream) {
+            NHIP(hipStreamCreateWithFlags(&H->gstream, hipStreamNonBlocking));
+            NHIP(hipEventCreateWithFlags(&H->gev, hipEventDisableTiming));
+        }
+        if (!on_graph) {                    // after the caller's earlier work
+            NHIP(hipEventRecord(H->gev, st));
+            NHIP(hipStreamWaitEvent(H->gstream, H->gev, 0));
+            on_graph = true;
+        }
+        std::vector<void*> bufs;
+        for (int l = 0; l < H->nlev; ++l) {
+            bufs.push_back(H->lev[l].phi);
+            bufs.push_back(H->lev[l].phi2);
+        }
+        bufs.push_back((void*)(intptr_t)g_nod_cfg.load());      // the tiles the capture baked in
+        if (!H->cycle_exec || H->cycle_pre != H->p.pre_sweeps || H->cycle_post != H->p.post_sweeps ||
+            H->cycle_bufs != bufs) {
+            if (H->cycle_exec) {
+                NHIP(hipStreamSynchronize(H->gstream));      // a cycle enqueued ahead may still run it
+                hipGraphExecDestroy(H->cycle_exec);
+                H->cycle_exec = nullptr;
+            }
+            NHIP(hipStreamBeginCapture(H->gstream, hipStreamCaptureModeRelaxed));
+            int r2 = cycle(H->gstream);
+            hipGraph_t g = nullptr;
+            hipError_t e = hipStreamEndCapture(H->gstream, &g);
+            if (r2) {
+                if (g) hipGraphDestroy(g);
+                return r2;
+            }
+            if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture", __LINE__);
+            e = hipGraphInstantiate(&H->cycle_exec, g, nullptr, nullptr, 0);
+            hipGraphDestroy(g);
+            if (e != hipSuccess) {
+                H->cycle_exec = nullptr;
+                return hip_fail(e, "hipGraphInstantiate", __LINE__);
+            }
+            H->cycle_pre = H->p.pre_sweeps;
+            H->cycle_post = H->p.post_sweeps;
+            H->cycle_bufs = bufs;
+        }
+        NHIP(hipGraphLaunch(H->cycle_exec, H->gstream));
+        return MG_OK;
+    };
+    return nod_cycles(H, fnorm, S_, ahead, status, cycles, rel, over, enqueue,
+                      [&] { return on_graph ? H->gstream : st; });
 }
 
 int nod_project(nodal_hierarchy* H, const double* rho, const double* b0c, const double* S, double* u, double* v,
@@ -1210,100 +1308,29 @@ int nod_project(nodal_hierarchy* H, const double* rho, const double* b0c, const 
     if (rc) return S_->status = rc;
     const double fnorm = std::sqrt(H->host[kSlotNorm * kReduceWidth]);
     S_->norm_f = fnorm;
-    NHIP(launch_fill<double>(L0.phi, NN, 0.0, st));
     int status = MG_OK, cycles = 0;
     double rel = 0.0;
-    S_->resid_hist[0] = fnorm > 0.0 ? 1.0 : 0.0;
-    S_->rel_resid0 = S_->resid_hist[0];
-    S_->hist_len = 1;
-    // every cycle ends with a host synchronisation: the loop's wall time is
-    // the device time of the cycles
+    // the cycles' wall time, their last look at the norms included, is the
+    // device time of the cycles
     const auto t_s0 = std::chrono::steady_clock::now();
-    if (fnorm > 0.0 && H->p.rtol < 1.0 && H->mixed) {
-        rc = nod_solve_mixed(H, fnorm, S_, &status, &cycles, &rel, st);
-        if (rc) return S_->status = rc;
-    } else if (fnorm > 0.0 && H->p.rtol < 1.0) {
-        status = MG_ERR_NOT_CONVERGED;
-        bool on_graph = false;
-        auto cycle = [&](hipStream_t s) -> int {
-            int r2 = nod_vcycle(H, 0, s);
-            if (r2) return r2;
-            int nt = 0;
-            NHIP((launch_nod_resid<double, kNodNorm>(L0, L0, H->partials, NodRefine{}, &nt, s)));
-            NHIP(launch_reduce(H->partials, nt, H->scal + kSlotRes * kReduceWidth, s));
-            NHIP(hipMemcpyAsync(H->host + kSlotRes * kReduceWidth, H->scal + kSlotRes * kReduceWidth,
-                                kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, s));
-            return MG_OK;
-        };
-        // a captured cycle bakes in the levels' phi buffers: replayable when
-        // every level's buffers come back (an even number of sweeps a cycle)
-        const bool graphs = H->graphs_on && (H->p.pre_sweeps + H->p.post_sweeps) % 2 == 0;
-        while (cycles < H->p.max_cycles) {
-            if (graphs) {
-                if (!H->gstream) {
-                    NHIP(hipStreamCreateWithFlags(&H->gstream, hipStreamNonBlocking));
-                    NHIP(hipEventCreateWithFlags(&H->gev, hipEventDisableTiming));
-                }
-                if (!on_graph) {                    // after the caller's earlier work
-                    NHIP(hipEventRecord(H->gev, st));
-                    NHIP(hipStreamWaitEvent(H->gstream, H->gev, 0));
-                    on_graph = true;
-                }
-                std::vector<void*> bufs;
-                for (int l = 0; l < H->nlev; ++l) {
-                    bufs.push_back(H->lev[l].phi);
-                    bufs.push_back(H->lev[l].phi2);
-                }
-                bufs.push_back((void*)(intptr_t)g_nod_cfg.load());      // the tiles the capture baked in
-                if (!H->cycle_exec || H->cycle_pre != H->p.pre_sweeps || H->cycle_post != H->p.post_sweeps ||
-                    H->cycle_bufs != bufs) {
-                    if (H->cycle_exec) {
-                        hipGraphExecDestroy(H->cycle_exec);
-                        H->cycle_exec = nullptr;
-                    }
-                    NHIP(hipStreamBeginCapture(H->gstream, hipStreamCaptureModeRelaxed));
-                    int r2 = cycle(H->gstream);
-                    hipGraph_t g = nullptr;
-                    hipError_t e = hipStreamEndCapture(H->gstream, &g);
-                    if (r2) {
-                        if (g) hipGraphDestroy(g);
-                        return S_->status = r2;
-                    }
-                    if (e != hipSuccess) return S_->status = hip_fail(e, "hipStreamEndCapture", __LINE__);
-                    e = hipGraphInstantiate(&H->cycle_exec, g, nullptr, nullptr, 0);
-                    hipGraphDestroy(g);
-                    if (e != hipSuccess) {
-                        H->cycle_exec = nullptr;
-                        return S_->status = hip_fail(e, "hipGraphInstantiate", __LINE__);
-                    }
-                    H->cycle_pre = H->p.pre_sweeps;
-                    H->cycle_post = H->p.post_sweeps;
-                    H->cycle_bufs = bufs;
-                }
-                NHIP(hipGraphLaunch(H->cycle_exec, H->gstream));
-                NHIP(hipStreamSynchronize(H->gstream));
-            } else {
-                rc = cycle(st);
-                if (rc) return S_->status = rc;
-                NHIP(hipStreamSynchronize(st));
-            }
-            ++cycles;
-            const double* r = H->host + kSlotRes * kReduceWidth;
-            rel = std::sqrt(r[0]) / fnorm;
-            if (cycles < MG_HIST_MAX) {
-                S_->resid_hist[cycles] = rel;
-                S_->hist_len = cycles + 1;
-            }
-            if (r[3] > 0.0 || !std::isfinite(rel)) {
-                set_error("non-finite residual during the solve");
-                status = MG_ERR_NONFINITE;
-                break;
-            }
-            if (rel <= H->p.rtol) {
-                status = MG_OK;
-                break;
-            }
+    // looking ahead first; again without where that went beyond convergence
+    for (int pass = 0; pass < 2; ++pass) {
+        bool over = false;
+        cycles = 0;
+        rel = 0.0;
+        NHIP(launch_fill<double>(L0.phi, NN, 0.0, st));
+        NHIP(launch_reduce(H->partials, 0, H->scal + kSlotRes * kReduceWidth, st, norm_ring(H->scal), true));
+        S_->resid_hist[0] = fnorm > 0.0 ? 1.0 : 0.0;
+        S_->rel_resid0 = S_->resid_hist[0];
+        S_->hist_len = 1;
+        if (fnorm > 0.0 && H->p.rtol < 1.0) {
+            rel = 1.0;
+            rc = H->mixed ? nod_solve_mixed(H, fnorm, S_, &status, &cycles, &rel, pass == 0, &over, st)
+                          : nod_solve(H, fnorm, S_, &status, &cycles, &rel, pass == 0, &over, st);
+            if (rc) return S_->status = rc;
+            if (!H->mixed && cycles == 0) rel = 0.0;
         }
+        if (!over) break;
     }
     if (H->gstream) {                       // the caller's stream continues after the graph work
         NHIP(hipEventRecord(H->gev, H->gstream));

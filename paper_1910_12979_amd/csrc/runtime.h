@@ -17,6 +17,12 @@ constexpr int kSlotNorm = 1;   // {||f||^2 after mean removal, ...}
 constexpr int kSlotRes = 2;    // {||r||^2, -, max |r|, #non-finite}
 constexpr int kSlotPhi = 3;    // {sum phi, ...}
 constexpr int kSlotScale = 4;  // mixed precision: {scale of the FP32 residual, scale for the next}
+constexpr int kSlotCount = 5;  // norms in the ring (an int)
+constexpr int kSlotRing = 8;   // kNormRing rows: the residual norms of the last cycles
+// The ring in a hierarchy's block of 16 rows of device scalars.
+inline NormRing norm_ring(double* scal) {
+    return NormRing{scal + kSlotRing * kReduceWidth, reinterpret_cast<int*>(scal + kSlotCount * kReduceWidth)};
+}
 }  // namespace mg
 
 struct mg_hierarchy {
@@ -47,9 +53,14 @@ struct mg_hierarchy {
     mg::RhoArgs rho{};            // finest-level coefficient source of the current solve
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     hipEvent_t evs0 = nullptr, evs1 = nullptr;   // around the multigrid iterations of a solve
-    // Replayable V-cycles (FP64 solve): one cycle plus the next residual
-    // norm captured as a hipGraph, keyed by everything baked into it.
-    bool graphs_on = true;
+    // Replayable V-cycles (mg_set_graphs): one cycle plus the next residual
+    // norm captured as a hipGraph, keyed by everything baked into it.  Off
+    // unless asked for: with cycles enqueued ahead of the norms the separate
+    // launches keep up with the device, and a replay's own submission costs
+    // more (whole projections, separate / replayed: 32^3 627 / 682 us, 128^3
+    // 1986 / 2055; with inputs at new addresses, which need a new capture, 624
+    // / 738 and 1976 / 2160).
+    bool graphs_on = false;
     bool bottom_on = true;      // levels below the fused ones in one workgroup launch
     hipStream_t gstream = nullptr;
     hipEvent_t gev = nullptr;

@@ -706,8 +706,7 @@ double model_bytes(const mg_params& p, int cycles, int mixed) {
 // first pre-sweep: the sweep reads phi, f and rho anyway, so it also writes
 // per-tile partial sums of r = f - L phi(input).  The sweep is out of place
 // (into phi2); its output is taken (buffers swapped) only if another cycle
-// follows.  Enqueues the sweep, the reduction and the copy of the norm row to
-// pinned host memory; the caller synchronises.
+// follows.  Enqueues the sweep and the reduction into the ring of norms.
 static int enqueue_sweep_norm(mg_hierarchy* H, hipStream_t st) {
     Level& L0 = H->lev[0];
     SweepArgs<double> a{};
@@ -734,10 +733,58 @@ static int enqueue_sweep_norm(mg_hierarchy* H, hipStream_t st) {
     const bool rho0 = H->rho.rho != nullptr;
     int np = 0;
     HIPCHK(launch_sweep_norm(a, rho0, sweep_config_for(L0.nx, L0.ny, L0.nz, rho0), &np, st));
-    int rc = reduce_to(H, np, kSlotRes, st);
-    if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(H->host + kSlotRes * kReduceWidth, H->scal + kSlotRes * kReduceWidth,
-                          kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, st));
+    HIPCHK(launch_reduce(H->partials, np, H->scal + kSlotRes * kReduceWidth, st, norm_ring(H->scal)));
+    return MG_OK;
+}
+
+// The norms of the cycles enqueued since the last look, on the host when this
+// returns.
+static int read_ring(mg_hierarchy* H, hipStream_t st) {
+    return read_scalars(H, kSlotRing * kReduceWidth, kNormRing * kReduceWidth, st);
+}
+static hipError_t empty_ring(mg_hierarchy* H, hipStream_t st) {
+    return launch_reduce(H->partials, 0, H->scal + kSlotRes * kReduceWidth, st, norm_ring(H->scal), true);
+}
+static const double* ring_row(const mg_hierarchy* H, int cycle) {      // cycle: from 0
+    return H->host + (kSlotRing + cycle % kNormRing) * kReduceWidth;
+}
+
+// The iterations of a solve, `enqueue` putting one on the stream that `stream`
+// then names: as many at a time as norm_ahead allows.  *over: converged before
+// the last one enqueued, so that the solve has to be run again without looking
+// ahead.
+template <typename E, typename S, typename R>
+static int run_cycles(mg_hierarchy* H, double fnorm, bool ahead, int* status, int* cycles, double* rel, bool* over,
+                      E&& enqueue, S&& stream, R&& record) {
+    double best = 0.0;
+    *over = false;
+    while (*status == MG_ERR_NOT_CONVERGED && *cycles < H->p.max_cycles) {
+        const int m = ahead ? norm_ahead(*rel, best, H->p.rtol, H->p.max_cycles - *cycles) : 1;
+        for (int i = 0; i < m; ++i) {
+            int rc = enqueue(*cycles + i);
+            if (rc) return rc;
+        }
+        int rc = read_ring(H, stream());
+        if (rc) return rc;
+        for (int i = 0; i < m; ++i) {
+            const double* r = ring_row(H, *cycles);
+            const double was = *rel;
+            *rel = std::sqrt(r[0]) / fnorm;
+            ++*cycles;
+            record(*cycles, *rel);
+            if (r[3] > 0.0 || !std::isfinite(*rel)) {
+                *status = MG_ERR_NONFINITE;
+                set_error("non-finite residual during the solve");
+                return MG_OK;
+            }
+            if (*rel <= H->p.rtol) {
+                *status = MG_OK;
+                *over = i + 1 < m;
+                return MG_OK;
+            }
+            best = *cycles == 1 ? *rel / was : std::min(best, *rel / was);
+        }
+    }
     return MG_OK;
 }
 
@@ -774,8 +821,7 @@ static bool graphs_usable(const mg_hierarchy* H) {
 
 enum { kIterFp64 = 1, kIterMixed = 2 };
 
-// One solver iteration whose last step copies the norm row to pinned host
-// memory; the norm is on the host when this returns.  `enqueue` puts the
+// One solver iteration, enqueued.  `enqueue` puts the
 // iteration's work on a stream and makes the host-side buffer swaps.  Replays
 // a captured hipGraph of exactly this work when one matches the current
 // state, else captures one (or runs eagerly when graphs are off).  Graph
@@ -785,10 +831,7 @@ enum { kIterFp64 = 1, kIterMixed = 2 };
 template <typename F>
 static int run_iteration(mg_hierarchy* H, hipStream_t st, bool* on_graph, int kind, F&& enqueue) {
     if (!graphs_usable(H)) {
-        int rc = enqueue(st);
-        if (rc) return rc;
-        HIPCHK(hipStreamSynchronize(st));
-        return MG_OK;
+        return enqueue(st);
     }
     if (!H->gstream) {
         HIPCHK(hipStreamCreateWithFlags(&H->gstream, hipStreamNonBlocking));
@@ -808,6 +851,7 @@ static int run_iteration(mg_hierarchy* H, hipStream_t st, bool* on_graph, int ki
         g = &H->graph[H->graph_next];
         H->graph_next = (H->graph_next + 1) % 2;
         if (g->exec) {
+            HIPCHK(hipStreamSynchronize(gs));       // an iteration enqueued ahead may still run it
             hipGraphExecDestroy(g->exec);
             g->exec = nullptr;
         }
@@ -844,7 +888,6 @@ static int run_iteration(mg_hierarchy* H, hipStream_t st, bool* on_graph, int ki
         }
     }
     HIPCHK(hipGraphLaunch(g->exec, gs));
-    HIPCHK(hipStreamSynchronize(gs));
     return MG_OK;
 }
 
@@ -878,7 +921,8 @@ double residual_scale(double norm2_sqrt, size_t n) {
 // coefficients from an FP32 copy of rho (written by the coefficient kernel
 // when it could).  Iterations after the first replay a captured graph.
 static int solve_level0_mixed_fused(mg_hierarchy* H, double fnorm, int* cycles_out, double* rel_out,
-                                    const std::function<void(int, double)>& record, hipStream_t st) {
+                                    const std::function<void(int, double)>& record, bool ahead, bool* over,
+                                    hipStream_t st) {
     Level& L0 = H->lev[0];
     const bool rho0 = H->rho.rho != nullptr;      // else stored finest-level coefficients (radial beta0)
     if (rho0 && !H->rho32_fresh) HIPCHK(launch_coeff_to_f32(H->rho.rho, H->rho32, L0.N, st));
@@ -927,28 +971,18 @@ static int solve_level0_mixed_fused(mg_hierarchy* H, double fnorm, int* cycles_o
         int np = 0;
         HIPCHK(launch_refine(a, rho0, cfg, &np, s));
         std::swap(L0.d.phi, L0.phi2_d);
-        HIPCHK(launch_reduce_scale(H->partials, np, H->scal + kSlotRes * kReduceWidth, scales, L0.N, s));
-        HIPCHK(hipMemcpyAsync(H->host + kSlotRes * kReduceWidth, H->scal + kSlotRes * kReduceWidth,
-                              kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIPCHK(launch_reduce_scale(H->partials, np, H->scal + kSlotRes * kReduceWidth, scales, L0.N, s,
+                                   norm_ring(H->scal)));
         return (int)MG_OK;
     };
     int status = MG_ERR_NOT_CONVERGED, cycles = 0;
     double rel = 1.0;
     bool on_graph = false;
-    while (status == MG_ERR_NOT_CONVERGED && cycles < H->p.max_cycles) {
-        int rc = run_iteration(H, st, &on_graph, kIterMixed, iteration);
-        if (rc) return rc;
-        ++cycles;
-        const double* r = H->host + kSlotRes * kReduceWidth;
-        rel = std::sqrt(r[0]) / fnorm;
-        record(cycles, rel);
-        if (r[3] > 0.0 || !std::isfinite(rel)) {
-            status = MG_ERR_NONFINITE;
-            set_error("non-finite residual during the solve");
-            break;
-        }
-        if (rel <= H->p.rtol) status = MG_OK;
-    }
+    int rc = run_cycles(
+        H, fnorm, ahead, &status, &cycles, &rel, over,
+        [&](int) { return run_iteration(H, st, &on_graph, kIterMixed, iteration); },
+        [&] { return on_graph ? H->gstream : st; }, record);
+    if (rc) return rc;
     if (on_graph) {                                  // the caller's stream continues after the graph work
         HIPCHK(hipEventRecord(H->gev, H->gstream));
         HIPCHK(hipStreamWaitEvent(st, H->gev, 0));
@@ -963,9 +997,10 @@ static int solve_level0_mixed_fused(mg_hierarchy* H, double fnorm, int* cycles_o
 // box by box with a halo exchange after every colour and after the
 // prolongation, levels 1 and coarser are the single-box ones, and phi is
 // gathered back into level 0 at the end.
-static int solve_level0_boxes(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStream_t st) {
+static int solve_level0_boxes(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStream_t st, bool ahead) {
     Level& L0 = H->lev[0];
     Level& L1 = H->lev[1];
+    if (!ahead) HIPCHK(empty_ring(H, st));
     BoxSet& B = H->box;                          // the fused smoother swaps its phi buffers
     B.rho_on = H->rho.rho != nullptr;            // plane-parallel beta0: coefficients from rho
     const bool spec = H->p.pre_sweeps >= 1 && box_norm_sweep_fits(B);
@@ -976,47 +1011,40 @@ static int solve_level0_boxes(mg_hierarchy* H, double fnorm, mg_stats* stats, hi
     int status = H->p.rtol >= 1.0 ? MG_OK : MG_ERR_NOT_CONVERGED;
     int cycles = 0;
     double rel = 1.0;
+    bool over = false;
     if (stats) {
         stats->resid_hist[0] = 1.0;
         stats->hist_len = 1;
     }
+    auto record = [&](int c, double r) {
+        if (stats && c < MG_HIST_MAX) {
+            stats->resid_hist[c] = r;
+            stats->hist_len = c + 1;
+        }
+    };
     // fused box sweeps: the residual norm of each cycle's result comes from
     // the next cycle's first pre-sweep, run speculatively (its output is
     // taken only if another cycle follows), as on the single-box level
-    int pre_done = 0;
-    while (status == MG_ERR_NOT_CONVERGED && cycles < H->p.max_cycles) {
+    auto cycle = [&](int c) -> int {
+        const int pre_done = spec && c > 0 ? 1 : 0;
+        if (pre_done) {
+            std::swap(B.phi, B.phi2);                // keep the sweep: it is this cycle's first
+            HIPCHK(launch_box_exchange(B, -1, st));
+        }
         HIPCHK(launch_box_smooth(B, L0.h, H->p.pre_sweeps - pre_done, st));
         HIPCHK(launch_box_resid_restrict(B, L0.h, L1.d.f, L1.d.phi, st));
-        int rc = vcycle<double>(H, 1, st);
-        if (rc) return rc;
+        int r2 = vcycle<double>(H, 1, st);
+        if (r2) return r2;
         HIPCHK(launch_box_smooth(B, L0.h, H->p.post_sweeps, st, L1.d.phi));   // prolongation first
-        ++cycles;
         int np = 0;
         if (spec) HIPCHK(launch_box_sweep_norm(B, L0.h, H->partials, &np, st));
         else HIPCHK(launch_box_resid_norm(B, L0.h, H->partials, &np, st));
-        rc = reduce_to(H, np, kSlotRes, st);
-        if (rc) return rc;
-        rc = read_scalars(H, kSlotRes * kReduceWidth, kReduceWidth, st);
-        if (rc) return rc;
-        const double* r = H->host + kSlotRes * kReduceWidth;
-        rel = std::sqrt(r[0]) / fnorm;
-        if (stats && cycles < MG_HIST_MAX) {
-            stats->resid_hist[cycles] = rel;
-            stats->hist_len = cycles + 1;
-        }
-        if (r[3] > 0.0 || !std::isfinite(rel)) {
-            status = MG_ERR_NONFINITE;
-            set_error("non-finite residual during the solve");
-            break;
-        }
-        if (rel <= H->p.rtol) {
-            status = MG_OK;
-        } else if (spec && cycles < H->p.max_cycles) {
-            std::swap(B.phi, B.phi2);                // keep the sweep: it is the next cycle's first
-            HIPCHK(launch_box_exchange(B, -1, st));
-            pre_done = 1;
-        }
-    }
+        HIPCHK(launch_reduce(H->partials, np, H->scal + kSlotRes * kReduceWidth, st, norm_ring(H->scal)));
+        return MG_OK;
+    };
+    int rc = run_cycles(H, fnorm, ahead, &status, &cycles, &rel, &over, cycle, [&] { return st; }, record);
+    if (rc) return rc;
+    if (over) return solve_level0_boxes(H, fnorm, stats, st, false);
     HIPCHK(launch_box_gather(B, L0.d.phi, st));
     if (stats) {
         stats->cycles = cycles;
@@ -1031,9 +1059,10 @@ static int solve_level0_boxes(mg_hierarchy* H, double fnorm, mg_stats* stats, hi
 // sweeps, FP32 residual + restriction and the FP64 refinement run box by box
 // and the halo of phi32, phi and the scaled residual exchanged after each;
 // levels 1 and coarser are the single-box FP32 levels.
-static int solve_level0_boxes_mixed(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStream_t st) {
+static int solve_level0_boxes_mixed(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStream_t st, bool ahead) {
     Level& L0 = H->lev[0];
     Level& L1 = H->lev[1];
+    if (!ahead) HIPCHK(empty_ring(H, st));
     BoxSet& B = H->box;
     if (!B.phi32 || !B.fused || H->p.pre_sweeps < 1 || H->p.post_sweeps < 1) {
         set_error("mixed precision on boxes needs fused boxes and at least one pre- and one post-sweep");
@@ -1052,38 +1081,35 @@ static int solve_level0_boxes_mixed(mg_hierarchy* H, double fnorm, mg_stats* sta
     int status = H->p.rtol >= 1.0 ? MG_OK : MG_ERR_NOT_CONVERGED;
     int cycles = 0;
     double rel = 1.0;
+    bool over = false;
     if (stats) {
         stats->resid_hist[0] = 1.0;
         stats->hist_len = 1;
     }
+    auto record = [&](int c, double r) {
+        if (stats && c < MG_HIST_MAX) {
+            stats->resid_hist[c] = r;
+            stats->hist_len = c + 1;
+        }
+    };
     const int inner = inner_cycles_of(H->p);
-    while (status == MG_ERR_NOT_CONVERGED && cycles < H->p.max_cycles) {
+    auto cycle = [&](int) -> int {
         for (int c = 0; c < inner; ++c) {          // the FP32 correction: V-cycles, the first from zero
             HIPCHK(launch_box_smooth32(B, L0.h, H->p.pre_sweeps, c == 0, nullptr, st));
             HIPCHK(launch_box_resid_restrict32(B, L0.h, L1.s.f, L1.s.phi, st));
-            int rc = vcycle<float>(H, 1, st);
-            if (rc) return rc;
+            int r2 = vcycle<float>(H, 1, st);
+            if (r2) return r2;
             HIPCHK(launch_box_smooth32(B, L0.h, H->p.post_sweeps, false, L1.s.phi, st));   // prolongation first
         }
         int np = 0;
         HIPCHK(launch_box_refine(B, L0.h, scales, H->partials, &np, st));
-        HIPCHK(launch_reduce_scale(H->partials, np, H->scal + kSlotRes * kReduceWidth, scales, L0.N, st));
-        int rc = read_scalars(H, kSlotRes * kReduceWidth, kReduceWidth, st);
-        if (rc) return rc;
-        ++cycles;
-        const double* r = H->host + kSlotRes * kReduceWidth;
-        rel = std::sqrt(r[0]) / fnorm;
-        if (stats && cycles < MG_HIST_MAX) {
-            stats->resid_hist[cycles] = rel;
-            stats->hist_len = cycles + 1;
-        }
-        if (r[3] > 0.0 || !std::isfinite(rel)) {
-            status = MG_ERR_NONFINITE;
-            set_error("non-finite residual during the solve");
-            break;
-        }
-        if (rel <= H->p.rtol) status = MG_OK;
-    }
+        HIPCHK(launch_reduce_scale(H->partials, np, H->scal + kSlotRes * kReduceWidth, scales, L0.N, st,
+                                   norm_ring(H->scal)));
+        return MG_OK;
+    };
+    int rc = run_cycles(H, fnorm, ahead, &status, &cycles, &rel, &over, cycle, [&] { return st; }, record);
+    if (rc) return rc;
+    if (over) return solve_level0_boxes_mixed(H, fnorm, stats, st, false);
     HIPCHK(launch_box_gather(B, L0.d.phi, st));
     if (stats) {
         stats->cycles = cycles;
@@ -1093,12 +1119,13 @@ static int solve_level0_boxes_mixed(mg_hierarchy* H, double fnorm, mg_stats* sta
 }
 
 // Solve on level 0 after f (mean-removed) and the coefficients are in place.
-static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStream_t st) {
+// ahead: cycles may be enqueued before the norms of those before them are read.
+static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStream_t st, bool ahead = true) {
     if (H->boxes_on)
-        return H->p.precision == MG_MIXED ? solve_level0_boxes_mixed(H, fnorm, stats, st)
-                                          : solve_level0_boxes(H, fnorm, stats, st);
+        return H->p.precision == MG_MIXED ? solve_level0_boxes_mixed(H, fnorm, stats, st, ahead)
+                                          : solve_level0_boxes(H, fnorm, stats, st, ahead);
     Level& L0 = H->lev[0];
-    HIPCHK(launch_fill<double>(L0.d.phi, L0.N, 0.0, st));
+    if (!ahead) HIPCHK(empty_ring(H, st));         // run again
     int status = MG_ERR_NOT_CONVERGED;
     int cycles = 0;
     double rel = 1.0;
@@ -1106,10 +1133,10 @@ static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStrea
         stats->resid_hist[0] = 1.0;
         stats->hist_len = 1;
     }
-    auto record = [&](double r) {
-        if (stats && cycles < MG_HIST_MAX) {
-            stats->resid_hist[cycles] = r;
-            stats->hist_len = cycles + 1;
+    auto record = [&](int c, double r) {
+        if (stats && c < MG_HIST_MAX) {
+            stats->resid_hist[c] = r;
+            stats->hist_len = c + 1;
         }
     };
     const bool mixed = H->p.precision == MG_MIXED;
@@ -1119,44 +1146,28 @@ static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStrea
     const bool fused = H->p.pre_sweeps >= 1 && H->nlev > 1 &&
                        (mixed ? sweep_marchable(L0.nx, L0.ny, L0.nz) : sweep_fusable(L0.nx, L0.ny, L0.nz));
     const bool fused_norm = !mixed && fused;
+    // the FP64 fused solve's first sweep starts from zero without reading phi
+    if (!(fused_norm && status == MG_ERR_NOT_CONVERGED && H->p.max_cycles > 0) &&
+        !(mixed && fused && status == MG_ERR_NOT_CONVERGED))
+        HIPCHK(launch_fill<double>(L0.d.phi, L0.N, 0.0, st));
+    bool over = false;
     if (mixed && fused && status == MG_ERR_NOT_CONVERGED) {
-        auto rec = [&](int c, double r) {
-            if (stats && c < MG_HIST_MAX) {
-                stats->resid_hist[c] = r;
-                stats->hist_len = c + 1;
-            }
-        };
-        status = solve_level0_mixed_fused(H, fnorm, &cycles, &rel, rec, st);
+        status = solve_level0_mixed_fused(H, fnorm, &cycles, &rel, record, ahead, &over, st);
         if (status != MG_OK && status != MG_ERR_NOT_CONVERGED && status != MG_ERR_NONFINITE) return status;
     } else if (fused_norm) {
         bool on_graph = false;
-        while (status == MG_ERR_NOT_CONVERGED) {
-            int rc;
-            if (cycles == 0) {
-                if (H->p.max_cycles == 0) break;
-                rc = vcycle<double>(H, 0, st, 0);
-                if (rc == MG_OK) rc = enqueue_sweep_norm(H, st);
-                if (rc == MG_OK && hipStreamSynchronize(st) != hipSuccess) rc = MG_ERR_HIP;
-            } else {
+        int rc = run_cycles(
+            H, fnorm, ahead, &status, &cycles, &rel, &over,
+            [&](int c) -> int {
+                if (c == 0) {
+                    int r2 = vcycle<double>(H, 0, st, 0, true);
+                    return r2 ? r2 : enqueue_sweep_norm(H, st);
+                }
                 std::swap(L0.d.phi, L0.phi2_d);     // keep the sweep: it is this cycle's first
-                rc = cycle_and_norm(H, st, &on_graph);
-            }
-            if (rc) return rc;
-            ++cycles;
-            const double* r = H->host + kSlotRes * kReduceWidth;
-            rel = std::sqrt(r[0]) / fnorm;
-            record(rel);
-            if (r[3] > 0.0 || !std::isfinite(rel)) {
-                status = MG_ERR_NONFINITE;
-                set_error("non-finite residual during the solve");
-                break;
-            }
-            if (rel <= H->p.rtol) {
-                status = MG_OK;
-                break;
-            }
-            if (cycles >= H->p.max_cycles) break;
-        }
+                return cycle_and_norm(H, st, &on_graph);
+            },
+            [&] { return on_graph ? H->gstream : st; }, record);
+        if (rc) return rc;
         if (on_graph) {                              // the caller's stream continues after the graph work
             HIPCHK(hipEventRecord(H->gev, H->gstream));
             HIPCHK(hipStreamWaitEvent(st, H->gev, 0));
@@ -1186,7 +1197,7 @@ static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStrea
             if (rc) return rc;
             const double* r = H->host + kSlotRes * kReduceWidth;
             rel = std::sqrt(r[0]) / fnorm;
-            record(rel);
+            record(cycles, rel);
             if (r[3] > 0.0 || !std::isfinite(rel)) {
                 status = MG_ERR_NONFINITE;
                 set_error("non-finite residual during the solve");
@@ -1195,6 +1206,7 @@ static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStrea
             if (rel <= H->p.rtol) status = MG_OK;
         }
     }
+    if (over) return solve_level0(H, fnorm, stats, st, false);
     if (stats) {
         stats->cycles = cycles;
         stats->rel_resid = rel;
@@ -1231,7 +1243,13 @@ static int project_impl(mg_hierarchy* H, const double* rho, const double* b0c, c
     H->rho = radial ? RhoArgs{} : RhoArgs{rho_src, b0c, b0e, H->px, H->py, H->pz};
     int rc = build_coefficients(H, rho, b0c, b0e, S, u, v, w, st, w0, rad);
     if (rc) return rc;
-    rc = read_scalars(H, kSlotRhs * kReduceWidth, kReduceWidth, st);
+    // f's mean removed and its norm ahead of the checks: one look at both rows
+    int np = 0;
+    HIPCHK(launch_shift_norm(shape_of(L0), L0.d.f, 0.0, H->partials, &np, st,
+                             H->singular ? H->scal + kSlotRhs * kReduceWidth : nullptr));
+    HIPCHK(launch_reduce(H->partials, np, H->scal + kSlotNorm * kReduceWidth, st, norm_ring(H->scal), true));
+    static_assert(kSlotNorm == kSlotRhs + 1, "read together");
+    rc = read_scalars(H, kSlotRhs * kReduceWidth, 2 * kReduceWidth, st);
     if (rc) return rc;
     const double* q = H->host + kSlotRhs * kReduceWidth;
     double sf = q[0], saf = q[1], bad = q[2], nonfin = q[3];
@@ -1259,12 +1277,6 @@ static int project_impl(mg_hierarchy* H, const double* rho, const double* b0c, c
     } else {
         double mean = H->singular ? sf / (double)L0.N : 0.0;
         S_->mean_removed = mean;
-        int np = 0;
-        HIPCHK(launch_shift_norm(shape_of(L0), L0.d.f, mean, H->partials, &np, st));
-        rc = reduce_to(H, np, kSlotNorm, st);
-        if (rc) return rc;
-        rc = read_scalars(H, kSlotNorm * kReduceWidth, kReduceWidth, st);
-        if (rc) return rc;
         double fnorm = std::sqrt(H->host[kSlotNorm * kReduceWidth]);
         S_->norm_f = fnorm;
         if (fnorm == 0.0) {
@@ -1287,7 +1299,6 @@ static int project_impl(mg_hierarchy* H, const double* rho, const double* b0c, c
             }
         }
     }
-    int np = 0;
     if (H->singular) {
         HIPCHK(launch_sum(shape_of(L0), L0.d.phi, H->partials, &np, st));
         rc = reduce_to(H, np, kSlotPhi, st);
