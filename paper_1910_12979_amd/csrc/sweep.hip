@@ -105,7 +105,9 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
     __shared__ T sbx[3][WY][WX];                    // low x-face coefficients, planes t+1, t, t-1
     __shared__ T sby[3][WY][WX];
     __shared__ T srho[kRho ? 2 : 1][kRho ? WY : 1][kRho ? WX : 1];   // rho: t+1 (read), t+2 (staged)
-    __shared__ double sb0c[kRho ? NB : 1], sb0e[kRho ? NB : 1];
+    __shared__ T sb0c[kRho ? NB : 1], sb0e[kRho ? NB : 1];           // twice beta0: a face's coefficient is
+                                                                     // 2 beta0 / (rho + rho), the same bits as
+                                                                     // beta0 over half the sum
 
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int tx = tile % a.ntx;
@@ -139,7 +141,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
     auto base = [&](auto* p, int tw) { return p + (size_t)((unsigned)tw * plane); };
     const T h2 = a.h2;
     const T ih2 = T(1) / a.h2;
-    const T half = T(0.5);
     const T cscale = kIn == kInCorrect ? (T)(1.0 / a.scales[0]) : T(0);    // exact: a power of two
     // outflow sides (kBnd): the level's per-cell boundary diagonal a.dg (zero
     // away from the outflow sides) is read, like f, two plane steps ahead of
@@ -208,7 +209,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
     // low z-face coefficient of plane t from the queue values of planes t-1, t
     auto zface = [&](int t, T q_below, T q_here) -> T {
         if (!kRho) return q_here;
-        const T b = pdiv((T)sb0e[t - zb], half * (q_below + q_here));
+        const T b = pdiv(sb0e[t - zb], q_below + q_here);
         const bool wall = kBox ? (t == a.wlo[2] || t == a.whi[2]) : (wrap3(t, nz) == 0 && !a.pz);
         return wall ? T(0) : b;                              // solid wall: no flux
     };
@@ -217,8 +218,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
     if (kRho) {
         for (int q = threadIdx.x; q < NB && zb + q <= z1 + 3; q += blockDim.x) {
             int qw = wrap3(zb + q, nz);
-            sb0c[q] = a.b0c[qw];
-            sb0e[q] = a.b0e[qw];
+            sb0c[q] = (T)(2.0 * a.b0c[qw]);
+            sb0e[q] = (T)(2.0 * a.b0e[qw]);
         }
     }
     // Loads in flight: step s issues plane s+3 (phi, stored bx/by), s+4 (rho
@@ -269,15 +270,15 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
     // x/y low-face coefficients of plane t into LDS slot s from the staged rho
     // plane (buffer b); (r0, r1) is the thread's own pair of that plane
     auto rho_coeffs = [&](int t, int s, int b, T r0, T r1) {
-        const T b0 = (T)sb0c[t - zb];
+        const T b0 = sb0c[t - zb];
         const T rc[2] = {r0, r1};
         // the window's first row/column has no low neighbour and is never read
         const T rl[2] = {srho[b][ly][lx0 > 0 ? lx0 - 1 : 0], r0};
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const int lx = lx0 + c;
-            const T cx = pdiv(b0, half * (rl[c] + rc[c]));
-            const T cy = pdiv(b0, half * (srho[b][ly > 0 ? ly - 1 : 0][lx] + rc[c]));
+            const T cx = pdiv(b0, rl[c] + rc[c]);
+            const T cy = pdiv(b0, srho[b][ly > 0 ? ly - 1 : 0][lx] + rc[c]);
             const bool xwall = kBox ? (gxw + c == a.wlo[0] || gxw + c == a.whi[0]) : ((gxw + c == 0) && !a.px);
             const bool ywall = kBox ? (gyw == a.wlo[1] || gyw == a.whi[1]) : (gyw == 0 && !a.py);
             sbx[s][ly][lx] = xwall ? T(0) : cx;
