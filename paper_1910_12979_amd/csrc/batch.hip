@@ -1095,8 +1095,8 @@ int Engine::round(std::vector<Job*>& jobs, hipStream_t st) {
             sb += rb;
             rd.push_back(ReduceDesc{H->partials, rb, H->scal + kSlotPhi * kReduceWidth,
                                     gdev + (nrun + q) * kReduceWidth});
-            cd.push_back(CorrectDesc{L0.nx, L0.ny, L0.nz, H->px, H->py, H->pz, L0.h, p.beta0_cc, p.beta0_edge, L0.d.bx,
-                                     L0.d.by, L0.d.bz, L0.d.phi, H->scal + kSlotPhi * kReduceWidth, p.u, p.v, p.w,
+            cd.push_back(CorrectDesc{L0.nx, L0.ny, L0.nz, H->px, H->py, H->pz, L0.h, p.beta0_cc, p.beta0_edge, p.rho,
+                                     L0.d.phi, H->scal + kSlotPhi * kReduceWidth, p.u, p.v, p.w,
                                      p.phi, cb});
             cb += cell_blocks(L0.N);
         }

@@ -122,18 +122,20 @@ __device__ inline int box_global(const BoxSet& B, int d, int o, int L) {
     return g < 0 ? g + B.n[d] : g - B.n[d];
 }
 
-// phi = phi2 = 0; f and the face arrays of every ghosted cell.  One thread
-// per ghosted cell, patches over the ghosted planes.
+// phi = phi2 = 0; f, rho and (coeffs) the face arrays of every ghosted cell.
+// One thread per ghosted cell, 256 in a row of a plane's cells (64 x 4 patches
+// left half the lanes of a 68-cell row idle: 64 boxes of 64^3 453 us, now 189).
 __global__ __launch_bounds__(kBoxBlock) void k_box_scatter(BoxSet B, const double* __restrict__ f,
                                                            const double* __restrict__ bx,
                                                            const double* __restrict__ by,
                                                            const double* __restrict__ bz,
-                                                           const double* __restrict__ rho, int coeffs, int gx,
-                                                           int gy) {
-    const Patch q = patch_of(blockIdx.x, gx, gy, B.G[2], kCellTX, kCellTY);
-    const int i = q.x0 + (int)threadIdx.x, j = q.y0 + (int)threadIdx.y;
-    if (i >= B.G[0] || j >= B.G[1]) return;
-    const size_t e = (size_t)q.b * B.stride + ((size_t)q.k * B.G[1] + j) * B.G[0] + i;
+                                                           const double* __restrict__ rho, int coeffs,
+                                                           int gp) {
+    const Patch q = patch_of(blockIdx.x, gp, 1, B.G[2], kBoxBlock, 1);
+    const unsigned ij = (unsigned)q.x0 + threadIdx.x;
+    if (ij >= (unsigned)B.G[0] * (unsigned)B.G[1]) return;
+    const int i = (int)(ij % (unsigned)B.G[0]), j = (int)(ij / (unsigned)B.G[0]);
+    const size_t e = (size_t)q.b * B.stride + (size_t)q.k * B.G[0] * B.G[1] + ij;
     int c[3];
     box_coords(B, q.b, c);
     const int L[3] = {i - kG, j - kG, q.k - kG};
@@ -153,9 +155,11 @@ __global__ __launch_bounds__(kBoxBlock) void k_box_scatter(BoxSet B, const doubl
         const size_t gi = gidx(g[0], g[1], g[2], B.n[0], B.n[1]);
         fv = f[gi];
         if (rho) rv = rho[gi];
-        cv[0] = bx[gi];
-        cv[1] = by[gi];
-        cv[2] = bz[gi];
+        if (coeffs) {
+            cv[0] = bx[gi];
+            cv[1] = by[gi];
+            cv[2] = bz[gi];
+        }
     } else if (out == 1 && wall_d >= 0) {
         cv[wall_d] = 0.0;                     // the first cell past a high wall: its low face is the wall
     }
@@ -411,10 +415,9 @@ size_t boxset_cells(const BoxSet& B) { return (size_t)B.n[0] * B.n[1] * B.n[2]; 
 
 hipError_t launch_box_scatter(const BoxSet& B, const double* f, const double* bx, const double* by, const double* bz,
                               const double* rho, const double* b0c, const double* b0e, bool coeffs, hipStream_t st) {
-    const int gx = cdiv(B.G[0], kCellTX), gy = cdiv(B.G[1], kCellTY);
-    const unsigned blocks = (unsigned)gx * gy * B.G[2] * B.nbox;
-    hipLaunchKernelGGL(k_box_scatter, dim3(blocks), dim3(kCellTX, kCellTY), 0, st, B, f, bx, by, bz, rho,
-                       coeffs ? 1 : 0, gx, gy);
+    const int gp = cdiv(B.G[0] * B.G[1], kBoxBlock);
+    const unsigned blocks = (unsigned)gp * B.G[2] * B.nbox;
+    hipLaunchKernelGGL(k_box_scatter, dim3(blocks), dim3(kBoxBlock), 0, st, B, f, bx, by, bz, rho, coeffs ? 1 : 0, gp);
     if (rho)
         hipLaunchKernelGGL(k_box_beta0, dim3(cdiv(B.nbox * B.G[2], kBoxBlock)), dim3(kBoxBlock), 0, st, B, b0c, b0e);
     return hipGetLastError();

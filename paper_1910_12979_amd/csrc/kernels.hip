@@ -89,8 +89,10 @@ __device__ inline bool finite_d(double x) { return isfinite(x); }
 
 // ---------------------------------------------------------------------------
 // Level-0 face coefficients (+ optional right-hand side).  64 x 4 threads per
-// workgroup over (x, y); the workgroups stride over x, y and the planes so
-// the number of partial rows stays small, with no per-cell index division.
+// workgroup over (x, y); the workgroups stride over x and y and share out the
+// planes so the number of partial rows stays small, with no per-cell index
+// division.  HBM-bound: nine arrays (256^3 266 us, 4.5 TB/s; 304 us with the
+// planes dealt round-robin, each reading rho and w of its neighbour again).
 // ---------------------------------------------------------------------------
 constexpr int kPtX = 64, kPtY = 4;
 // Workgroup (bx, by, bz) of a (gx, gy, gz) grid over problem a.
@@ -112,9 +114,20 @@ __device__ void coeff_rhs_body(const CoeffDesc& a, int bxi, int byi, int bzi) {
     double* __restrict__ f = a.f;
     float* __restrict__ rho32 = a.rho32;
     double sf = 0.0, saf = 0.0, bad = 0.0, nonfin = 0.0;
-    for (int k = bzi; k < nz; k += a.gz)
+    const size_t plane = (size_t)nx * ny;
+    const int kper = (nz + a.gz - 1) / a.gz, k0 = bzi * kper, k1 = min(nz, k0 + kper);
     for (int j = byi * kPtY + threadIdx.y; j < ny; j += a.gy * kPtY)
     for (int i = bxi * kPtX + threadIdx.x; i < nx; i += a.gx * kPtX) {
+    // up through the workgroup's planes: rho below and w below are the ones
+    // read for the plane before
+    double rm = 0.0, wup = 0.0;
+    if (k0 < k1) {
+        const size_t wc = (size_t)j * nx + i;
+        if (k0 > 0) rm = rho[(size_t)(k0 - 1) * plane + wc];
+        else if (pz) rm = rho[(size_t)(nz - 1) * plane + wc];
+        if (kRhs) wup = w[(size_t)k0 * plane + wc];
+    }
+    for (int k = k0; k < k1; ++k) {
         const size_t c = cidx(i, j, k, nx, ny);
         double rc = rho[c];
         if (rho32) rho32[c] = (float)rc;
@@ -132,9 +145,9 @@ __device__ void coeff_rhs_body(const CoeffDesc& a, int bxi, int byi, int bzi) {
         else cy = py ? qdiv(bk, 0.5 * (rho[c + (size_t)(ny - 1) * nx] + rc)) : 0.0;
         // z-low face k (periodic: face 0 uses beta0_edge[0])
         double cz;
-        size_t plane = (size_t)nx * ny;
-        if (k > 0) cz = qdiv(bek, 0.5 * (rho[c - plane] + rc));
-        else cz = pz ? qdiv(b0e[0], 0.5 * (rho[c + (size_t)(nz - 1) * plane] + rc)) : 0.0;
+        if (k > 0) cz = qdiv(bek, 0.5 * (rm + rc));
+        else cz = pz ? qdiv(b0e[0], 0.5 * (rm + rc)) : 0.0;
+        rm = rc;
         bx[c] = cx;
         by[c] = cy;
         bz[c] = cz;
@@ -146,7 +159,7 @@ __device__ void coeff_rhs_body(const CoeffDesc& a, int bxi, int byi, int bzi) {
             double vl = v[vb + (size_t)j * nx];
             double vh = (j == ny - 1 && py) ? v[vb] : v[vb + (size_t)(j + 1) * nx];
             size_t wc = (size_t)j * nx + i;
-            double wl = w[(size_t)k * plane + wc];
+            double wl = wup;
             double bl = b0e[k];
             double wh, bh;
             if (k == nz - 1 && pz) {
@@ -156,6 +169,7 @@ __device__ void coeff_rhs_body(const CoeffDesc& a, int bxi, int byi, int bzi) {
                 wh = w[(size_t)(k + 1) * plane + wc];
                 bh = b0e[k + 1];
             }
+            wup = wh;
             if (k == 0 && pz) bl = b0e[0];
             double sc = S[c];
             if (w0) sc = sc - w0[k];         // the dp0/dt term of the constraint, per layer
@@ -168,6 +182,7 @@ __device__ void coeff_rhs_body(const CoeffDesc& a, int bxi, int byi, int bzi) {
             sf += fc;
             saf += fabs(fc);
         }
+    }
     }
     const int row = (bzi * a.gy + byi) * a.gx + bxi;
     block_reduce_row(sf, saf, bad, nonfin, a.partials + (size_t)row * kReduceWidth);
@@ -642,10 +657,12 @@ __global__ __launch_bounds__(kSolveThreads) void k_coarse_solve(int n, const dou
 // Velocity correction: U <- U - (b/beta0)_f (phi_c - phi_nb)/h on every
 // non-wall face (low faces of each cell), periodic duplicate faces refreshed.
 // ---------------------------------------------------------------------------
+// Correction of one cell's low faces.  HBM-bound: the face coefficients come
+// from rho, bit for bit the stored ones (256^3 249 us, nine arrays; 264 us
+// reading the three stored ones, eleven).
 __device__ inline void correct_cell(int i, int j, int k, int nx, int ny, int nz, int px, int py, int pz, double h,
                                     const double* __restrict__ b0c, const double* __restrict__ b0e,
-                                    const double* __restrict__ bx, const double* __restrict__ by,
-                                    const double* __restrict__ bz, const double* __restrict__ phi,
+                                    const double* __restrict__ rho, const double* __restrict__ phi,
                                     const double* __restrict__ phi_sum, double* __restrict__ u,
                                     double* __restrict__ v, double* __restrict__ w, double* __restrict__ phi_out) {
     const size_t N = (size_t)nx * ny * nz;
@@ -653,28 +670,29 @@ __device__ inline void correct_cell(int i, int j, int k, int nx, int ny, int nz,
     size_t c = cidx(i, j, k, nx, ny);
     double pc = phi[c] - m;
     if (phi_out) phi_out[c] = pc;
+    const double rc = rho[c];
     size_t plane = (size_t)nx * ny;
     if (px || i > 0) {
-        int im = i > 0 ? i - 1 : nx - 1;
-        double g = (pc - (phi[cidx(im, j, k, nx, ny)] - m)) / h;
+        const size_t cm = cidx(i > 0 ? i - 1 : nx - 1, j, k, nx, ny);
+        double g = (pc - (phi[cm] - m)) / h;
         size_t e = ((size_t)k * ny + j) * (nx + 1) + i;
-        double un = u[e] - (bx[c] / b0c[k]) * g;
+        double un = u[e] - (qdiv(b0c[k], 0.5 * (rho[cm] + rc)) / b0c[k]) * g;
         u[e] = un;
         if (px && i == 0) u[e + nx] = un;
     }
     if (py || j > 0) {
-        int jm = j > 0 ? j - 1 : ny - 1;
-        double g = (pc - (phi[cidx(i, jm, k, nx, ny)] - m)) / h;
+        const size_t cm = cidx(i, j > 0 ? j - 1 : ny - 1, k, nx, ny);
+        double g = (pc - (phi[cm] - m)) / h;
         size_t e = ((size_t)k * (ny + 1) + j) * nx + i;
-        double vn = v[e] - (by[c] / b0c[k]) * g;
+        double vn = v[e] - (qdiv(b0c[k], 0.5 * (rho[cm] + rc)) / b0c[k]) * g;
         v[e] = vn;
         if (py && j == 0) v[e + (size_t)ny * nx] = vn;
     }
     if (pz || k > 0) {
-        int km = k > 0 ? k - 1 : nz - 1;
-        double g = (pc - (phi[cidx(i, j, km, nx, ny)] - m)) / h;
+        const size_t cm = cidx(i, j, k > 0 ? k - 1 : nz - 1, nx, ny);
+        double g = (pc - (phi[cm] - m)) / h;
         size_t e = (size_t)k * plane + (size_t)j * nx + i;
-        double wn = w[e] - (bz[c] / b0e[k]) * g;
+        double wn = w[e] - (qdiv(b0e[k], 0.5 * (rho[cm] + rc)) / b0e[k]) * g;
         w[e] = wn;
         if (pz && k == 0) w[e + (size_t)nz * plane] = wn;
     }
@@ -682,15 +700,14 @@ __device__ inline void correct_cell(int i, int j, int k, int nx, int ny, int nz,
 
 __global__ void k_correct(int nx, int ny, int nz, int px, int py, int pz, double h,
                           const double* __restrict__ b0c, const double* __restrict__ b0e,
-                          const double* __restrict__ bx, const double* __restrict__ by,
-                          const double* __restrict__ bz, const double* __restrict__ phi,
+                          const double* __restrict__ rho, const double* __restrict__ phi,
                           const double* __restrict__ phi_sum, double* __restrict__ u,
                           double* __restrict__ v, double* __restrict__ w, double* __restrict__ phi_out) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     int j = blockIdx.y * blockDim.y + threadIdx.y;
     int k = blockIdx.z * blockDim.z + threadIdx.z;
     if (i >= nx || j >= ny || k >= nz) return;
-    correct_cell(i, j, k, nx, ny, nz, px, py, pz, h, b0c, b0e, bx, by, bz, phi, phi_sum, u, v, w, phi_out);
+    correct_cell(i, j, k, nx, ny, nz, px, py, pz, h, b0c, b0e, rho, phi, phi_sum, u, v, w, phi_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1263,12 +1280,11 @@ hipError_t launch_avg_bnd(const Shape& fine, const Bnd<T>& fb, T* const cb[6], h
 }
 
 hipError_t launch_correct(const Shape& s, int px, int py, int pz, double h, const double* b0c,
-                          const double* b0e, const double* bx, const double* by, const double* bz,
-                          const double* phi, const double* phi_sum, double* u, double* v, double* w,
-                          double* phi_out, hipStream_t st) {
+                          const double* b0e, const double* rho, const double* phi, const double* phi_sum, double* u,
+                          double* v, double* w, double* phi_out, hipStream_t st) {
     Launch3 L = cell_launch(s.nx, s.ny, s.nz);
-    hipLaunchKernelGGL(k_correct, L.grid, L.block, 0, st, s.nx, s.ny, s.nz, px, py, pz, h, b0c, b0e, bx, by, bz,
-                       phi, phi_sum, u, v, w, phi_out);
+    hipLaunchKernelGGL(k_correct, L.grid, L.block, 0, st, s.nx, s.ny, s.nz, px, py, pz, h, b0c, b0e, rho, phi,
+                       phi_sum, u, v, w, phi_out);
     return hipGetLastError();
 }
 
@@ -1518,8 +1534,8 @@ __global__ __launch_bounds__(256) void k_correct_multi(const CorrectDesc* __rest
     const long long t = (long long)(blockIdx.x - c.block0) * 256 + threadIdx.x;
     if (t >= (long long)c.nx * c.ny * c.nz) return;
     const int i = (int)(t % c.nx), j = (int)((t / c.nx) % c.ny), k = (int)(t / ((long long)c.nx * c.ny));
-    correct_cell(i, j, k, c.nx, c.ny, c.nz, c.px, c.py, c.pz, c.h, c.b0c, c.b0e, c.bx, c.by, c.bz, c.phi, c.phi_sum,
-                 c.u, c.v, c.w, c.phi_out);
+    correct_cell(i, j, k, c.nx, c.ny, c.nz, c.px, c.py, c.pz, c.h, c.b0c, c.b0e, c.rho, c.phi, c.phi_sum, c.u, c.v,
+                 c.w, c.phi_out);
 }
 
 }  // namespace

@@ -315,10 +315,11 @@ hipError_t launch_coarse_solve(int N, const double* minv, const double* f, doubl
 hipError_t launch_sum(const Shape& s, const double* a, double* partials, int* nparts,
                       hipStream_t st);
 // Velocity correction on non-wall faces with the zero-mean potential
-// phi - (*phi_sum)/N; writes phi_out (nullable) = phi - mean.
+// phi - (*phi_sum)/N; writes phi_out (nullable) = phi - mean.  The face
+// coefficients are formed from rho again, bit for bit the stored ones: one
+// array read for three.
 hipError_t launch_correct(const Shape& s, int px, int py, int pz, double h, const double* b0c,
-                          const double* b0e, const double* bx, const double* by,
-                          const double* bz, const double* phi, const double* phi_sum,
+                          const double* b0e, const double* rho, const double* phi, const double* phi_sum,
                           double* u, double* v, double* w, double* phi_out, hipStream_t st);
 // First coarse level's coefficients from level 0's recomputed from rho.
 hipError_t launch_avg_coeff_rho(const Shape& fine, int px, int py, int pz, const double* rho, const double* b0c,
@@ -446,9 +447,7 @@ struct CorrectDesc {
     double h;
     const double* b0c;
     const double* b0e;
-    const double* bx;
-    const double* by;
-    const double* bz;
+    const double* rho;
     const double* phi;
     const double* phi_sum;
     double* u;

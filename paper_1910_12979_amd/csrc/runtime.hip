@@ -1309,8 +1309,8 @@ static int project_impl(mg_hierarchy* H, const double* rho, const double* b0c, c
         HIPCHK(launch_correct_gen(g, L0.d.phi, H->singular ? H->scal + kSlotPhi * kReduceWidth : nullptr, u, v, w,
                                   phi_out, st));
     } else {
-        HIPCHK(launch_correct(shape_of(L0), H->px, H->py, H->pz, L0.h, b0c, b0e, L0.d.bx, L0.d.by, L0.d.bz,
-                              L0.d.phi, H->scal + kSlotPhi * kReduceWidth, u, v, w, phi_out, st));
+        HIPCHK(launch_correct(shape_of(L0), H->px, H->py, H->pz, L0.h, b0c, b0e, rho, L0.d.phi,
+                              H->scal + kSlotPhi * kReduceWidth, u, v, w, phi_out, st));
     }
     if (H->ev1) HIPCHK(hipEventRecord(H->ev1, st));
     if (H->singular) {
