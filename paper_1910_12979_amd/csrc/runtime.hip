@@ -514,8 +514,11 @@ static int smooth(mg_hierarchy* H, int l, int nsweeps, int first, hipStream_t st
         if constexpr (dbl) a.dg = F.dg_d;
         else a.dg = F.dg_s;
         a.march_div = sweep_marchable(F.nx, F.ny, F.nz) ? 1 : 0;
-        HIPCHK(launch_sweep<T>(a, use_rho, k == 0 ? first : (int)kInPlain,
-                               sweep_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0), st));
+        const int mode = k == 0 ? first : (int)kInPlain;
+        HIPCHK(launch_sweep<T>(a, use_rho, mode,
+                               mode == kInZero ? zero_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0)
+                                               : sweep_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0),
+                               st));
         std::swap(A->phi, *alt);
     }
     return MG_OK;

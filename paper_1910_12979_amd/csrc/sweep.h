@@ -158,8 +158,13 @@ hipError_t launch_sweep_boxes_mode(const SweepArgs<T>& a, const BoxGeom& g, int 
 // The configuration of the residual + restriction, which needs no ring of red
 // cells: kTileCfg up to kTileRestrict cells (64^3 FP64, stored coefficients:
 // 5.2 us against 6.7 with one thread per coarse cell), else the sweep's (128^3 24.0
-// -> 18.7 us).
+// -> 18.7 us); in FP32 32-plane chunks where the sweep takes 64, as two of its
+// workgroups share a CU (256^3 47.5 us against 54.8, 512^3 the same).
 int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse);
+// The configuration of a sweep from zero: the sweep's, but in FP32, where two of
+// its workgroups share a CU, 32-plane chunks while 64-plane ones are too few to
+// fill it (256^3 58.1 us against 68.9; 512^3 480 against 451).
+int zero_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse);
 
 // Number of tiles (= partial rows) a sweep of this shape launches with cfg.
 int sweep_tiles(int nx, int ny, int nz, int cfg);

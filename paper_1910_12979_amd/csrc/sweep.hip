@@ -694,13 +694,14 @@ int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, bo
     // 96^3 15.8 and 14.5; 160x96x112 22.9 with 8, 25.5 with 16; 128^3 23.1
     // and 22.0).  From 4M cells on 64x16-cell tiles (the halo share of the
     // loads and of the redundant red updates is a third lower than with 64x8
-    // tiles; 192^3 47.6 against 55.9), in FP64 from 8M on with 64-plane chunks
-    // (one 132 KB workgroup per CU).  Batches fill the CUs with many problems
-    // and keep the deeper chunks.
+    // tiles; 192^3 47.6 against 55.9), from 8M on with 64-plane chunks: one
+    // workgroup per CU in FP64 (132 KB) and, for its 92 registers, in FP32 (256^3
+    // 59.1 us against 63.5 with 32 planes, 512^3 533 against 565).  Batches fill
+    // the CUs with many problems and keep the deeper chunks, in FP32 32 planes.
     const double cells = (double)nx * ny * nz;
     if (!batch && cells <= kTileSolo && sweep_tileable(nx, ny, nz)) return kTileCfg;
     if (nx >= 64 && ny >= 16 && cells >= (batch ? 8.0e6 : 4.0e6)) {
-        if (dbl && nz >= 64 && cells >= 8.0e6) return 11;
+        if ((dbl || !batch) && nz >= 64 && cells >= 8.0e6) return 11;
         if (!dbl || cells < 8.0e6) return 9;
     }
     if (nx >= 64 && cells >= 8.0e6) return 2;
@@ -711,10 +712,21 @@ int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, bo
     return batch ? 5 : 13;
 }
 
+static bool config_chosen(int cfg, int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
+    return cfg == tune_forced() || tune_find(nx, ny, nz, rho, dbl, coarse) >= 0;
+}
+
 int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
     const int cfg = sweep_config_for(nx, ny, nz, rho, dbl, coarse);
-    const bool chosen = cfg == tune_forced() || tune_find(nx, ny, nz, rho, dbl, coarse) >= 0;
-    return !chosen && (double)nx * ny * nz <= kTileRestrict && sweep_tileable(nx, ny, nz) ? kTileCfg : cfg;
+    if (config_chosen(cfg, nx, ny, nz, rho, dbl, coarse)) return cfg;
+    if ((double)nx * ny * nz <= kTileRestrict && sweep_tileable(nx, ny, nz)) return kTileCfg;
+    return !dbl && cfg == 11 ? 9 : cfg;
+}
+
+int zero_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
+    const int cfg = sweep_config_for(nx, ny, nz, rho, dbl, coarse);
+    if (config_chosen(cfg, nx, ny, nz, rho, dbl, coarse)) return cfg;
+    return !dbl && cfg == 11 && (double)nx * ny * nz < 4.0e7 ? 9 : cfg;
 }
 
 bool sweep_marchable(int nx, int ny, int nz) {
