@@ -194,11 +194,10 @@ constexpr int kPtX = 64, kPtY = 4;
 __device__ inline int part_row() { return (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x; }
 
 // sigma = beta0 / rho per cell; partial rows {0, 0, bad, #non-finite} of
-// rho, beta0, S and the three velocity components.
+// rho and beta0 (256^3 nodes 155 us while it also read S and the velocities for
+// their checks, which the right-hand side now makes).
 __global__ __launch_bounds__(kNodBlock) void k_nod_sigma(NodLevel L, const double* __restrict__ rho,
                                                          const double* __restrict__ b0c,
-                                                         const double* __restrict__ S, const double* __restrict__ u,
-                                                         const double* __restrict__ v, const double* __restrict__ w,
                                                          double* __restrict__ partials) {
     double bad = 0.0, nonfin = 0.0;
     for (int k = blockIdx.z; k < L.nz; k += gridDim.z)
@@ -207,48 +206,99 @@ __global__ __launch_bounds__(kNodBlock) void k_nod_sigma(NodLevel L, const doubl
         const size_t c = cidx3(L, i, j, k);
         const double r = rho[c], b = b0c[k];
         if (!isfinite(r) || !isfinite(b)) nonfin += 1.0;
-        if (S && (!isfinite(S[c]) || !isfinite(u[c]) || !isfinite(v[c]) || !isfinite(w[c]))) nonfin += 1.0;
         if (!(r > 0.0) || !(b > 0.0)) bad = 1.0;
         L.sig[c] = b / r;
     }
     block_row(0.0, 0.0, bad, nonfin, partials + (size_t)part_row() * kReduceWidth);
 }
 
-// f_n and partial rows {sum f, sum |f|, 0, 0}.
-__global__ __launch_bounds__(kNodBlock) void k_nod_rhs(NodLevel L, const double* __restrict__ b0c,
-                                                       const double* __restrict__ u, const double* __restrict__ v,
-                                                       const double* __restrict__ w, const double* __restrict__ S,
-                                                       double* __restrict__ partials) {
-    const int nc[3] = {L.nx, L.ny, L.nz}, per[3] = {L.px, L.py, L.pz};
-    double sf = 0.0, saf = 0.0;
-    for (int K = blockIdx.z; K < L.Nz; K += gridDim.z)
-    for (int J = blockIdx.y * kPtY + threadIdx.y; J < L.Ny; J += gridDim.y * kPtY)
-    for (int I = blockIdx.x * kPtX + threadIdx.x; I < L.Nx; I += gridDim.x * kPtX) {
-        const size_t n = nidx(L, I, J, K);
-        const int X[3] = {I, J, K};
-        double div = 0.0, src = 0.0;
-        for (int sz = 0; sz < 2; ++sz)
-            for (int sy = 0; sy < 2; ++sy)
-                for (int sx = 0; sx < 2; ++sx) {
-                    const int S3[3] = {sx, sy, sz};
-                    int c[3];
-                    bool ok = true;
-                    for (int d = 0; d < 3; ++d) {
-                        c[d] = nod_cell(X[d], S3[d], nc[d], per[d]);
-                        if (c[d] < 0) ok = false;
-                    }
-                    if (!ok) continue;
-                    const size_t cc = cidx3(L, c[0], c[1], c[2]);
-                    const double b = b0c[c[2]];
-                    div += b * ((sx ? u[cc] : -u[cc]) + (sy ? v[cc] : -v[cc]) + (sz ? w[cc] : -w[cc]));
-                    src += b * S[cc];
-                }
-        const double fn = div / (4.0 * L.h) - 0.125 * src;
-        L.f[n] = fn;
-        sf += fn;
-        saf += fabs(fn);
+// f_n and partial rows {sum f, sum |f|, 0, #non-finite of u, v, w, S}.  A
+// wavefront marches up through a chunk of planes with 64 columns of four rows:
+// a cell layer's sums over the four cells around a node are formed once, from
+// the lane's own column and the one of the lane below, and serve the planes
+// below and above it.  Bound by reading u, v, w and S once: 256^3 nodes 177 us
+// (3.8 TB/s; 407 us with a node gathering its eight cells).
+constexpr int kRhsTX = 63;
+__global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_rhs(NodLevel L, const double* __restrict__ b0c,
+                                                                const double* __restrict__ u,
+                                                                const double* __restrict__ v,
+                                                                const double* __restrict__ w,
+                                                                const double* __restrict__ S, int tz, int ntx,
+                                                                int nty, double* __restrict__ partials) {
+    constexpr int R = kNodResidRows;
+    static_assert(64 * kNodResidWaves == kNodBlock, "block_row");
+    const int tile = nod_xcd_tile(blockIdx.x, gridDim.x);
+    const int tx = tile % ntx, ty = (tile / ntx) % nty, tc = tile / (ntx * nty);
+    const int wx = threadIdx.x;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int gI = tx * kRhsTX - 1 + wx, gJ = (ty * kNodResidWaves + p) * R;
+    const int Ka = tc * tz, Kb = min(Ka + tz, L.Nz);
+    auto in = [](int g, int n, int per) { return per || (g >= 0 && g < n); };
+    const bool xc = in(gI, L.nx, L.px);
+    const size_t nxny = (size_t)L.nx * L.ny;
+    size_t row[R + 1];                            // cell rows gJ - 1 .. gJ + 3
+    bool ok[R + 1];
+#pragma unroll
+    for (int j = 0; j <= R; ++j) {
+        row[j] = (size_t)nod_fold(gJ - 1 + j, L.ny, L.py) * L.nx + nod_fold(gI, L.nx, L.px);
+        ok[j] = xc && in(gJ - 1 + j, L.ny, L.py);
     }
-    block_row(sf, saf, 0.0, 0.0, partials + (size_t)part_row() * kReduceWidth);
+    double sf = 0.0, saf = 0.0, nonfin = 0.0;
+    const double h4 = 4.0 * L.h;
+    // beta0-weighted sums over a layer's cells around the nodes: of +-u +- v, of w, of S
+    struct Layer {
+        double a[R], w[R], s[R];
+    };
+    auto layer = [&](int k, Layer& y) {
+        const bool zk = in(k, L.nz, L.pz);
+        const int kf = nod_fold(k, L.nz, L.pz);
+        const size_t o = (size_t)kf * nxny;
+        double qu[R + 1], qv[R + 1], qw[R + 1], qs[R + 1];
+#pragma unroll
+        for (int j = 0; j <= R; ++j) {
+            qu[j] = u[o + row[j]];
+            qv[j] = v[o + row[j]];
+            qw[j] = w[o + row[j]];
+            qs[j] = S[o + row[j]];
+        }
+        const double b = b0c[kf];
+#pragma unroll
+        for (int j = 0; j <= R; ++j) {
+            const bool e = ok[j] && zk;
+            if (!isfinite(qu[j]) || !isfinite(qv[j]) || !isfinite(qw[j]) || !isfinite(qs[j])) nonfin += 1.0;
+            qu[j] = e ? qu[j] : 0.0;
+            qv[j] = e ? qv[j] : 0.0;
+            qw[j] = e ? qw[j] : 0.0;
+            qs[j] = e ? qs[j] : 0.0;
+            qu[j] = qu[j] - lane_lo(qu[j]);
+            qv[j] = qv[j] + lane_lo(qv[j]);
+            qw[j] = qw[j] + lane_lo(qw[j]);
+            qs[j] = qs[j] + lane_lo(qs[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            y.a[j] = b * ((qu[j] + qu[j + 1]) + (qv[j + 1] - qv[j]));
+            y.w[j] = b * (qw[j] + qw[j + 1]);
+            y.s[j] = b * (qs[j] + qs[j + 1]);
+        }
+    };
+    Layer lo, hi;
+    layer(Ka - 1, lo);
+    for (int K = Ka; K < Kb; ++K) {
+        layer(K, hi);
+        const bool own = wx >= 1 && gI < L.Nx;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if (own && gJ + j < L.Ny) {
+                const double fn = ((lo.a[j] + hi.a[j]) + (hi.w[j] - lo.w[j])) / h4 - 0.125 * (lo.s[j] + hi.s[j]);
+                L.f[nidx(L, gI, gJ + j, K)] = fn;
+                sf += fn;
+                saf += fabs(fn);
+            }
+        }
+        lo = hi;
+    }
+    block_row(sf, saf, 0.0, nonfin, partials + (size_t)blockIdx.x * kReduceWidth);
 }
 
 // One colour of the Gauss-Seidel sweep; thread (I, tj, tk) owns node
@@ -910,14 +960,6 @@ size_t nod_layout(const mg_params* p, int nl, NodLevel* lev) {
         if (e_ != hipSuccess) return hip_fail(e_, #expr, __LINE__);       \
     } while (0)
 
-int nod_reduce(nodal_hierarchy* H, int nparts, int slot, hipStream_t st) {
-    NHIP(launch_reduce(H->partials, nparts, H->scal + slot * kReduceWidth, st));
-    NHIP(hipMemcpyAsync(H->host + slot * kReduceWidth, H->scal + slot * kReduceWidth, kReduceWidth * sizeof(double),
-                        hipMemcpyDeviceToHost, st));
-    NHIP(hipStreamSynchronize(st));
-    return MG_OK;
-}
-
 // Fused-sweep tiles: 56 x (2 pairs - 8) nodes, tz planes per chunk.
 struct NodSweepCfg {
     int pairs, tz;
@@ -1084,24 +1126,27 @@ int nod_vcycle(nodal_hierarchy* H, int l, hipStream_t st) {
 }
 
 // sigma on every level from rho and beta0, coarsest inverse; partial rows
-// of the input checks reduced into slot kSlotRhs (bad, #non-finite).
-int nod_coefficients(nodal_hierarchy* H, const double* rho, const double* b0c, const double* S, const double* u,
-                     const double* v, const double* w, hipStream_t st) {
+// of the input checks reduced into slot kSlotRhs (bad, #non-finite), enqueued.
+int nod_build(nodal_hierarchy* H, const double* rho, const double* b0c, hipStream_t st) {
     const NodLevel& L0 = H->lev[0];
     const dim3 sg = point_grid(L0.nx, L0.ny, L0.nz);
-    const int nb = grid_blocks(sg);
-    hipLaunchKernelGGL(k_nod_sigma, sg, dim3(kPtX, kPtY), 0, st, L0, rho, b0c, S, u, v, w, H->partials);
+    hipLaunchKernelGGL(k_nod_sigma, sg, dim3(kPtX, kPtY), 0, st, L0, rho, b0c, H->partials);
     NHIP(hipGetLastError());
-    int rc = nod_reduce(H, nb, kSlotRhs, st);
-    if (rc) return rc;
+    NHIP(launch_reduce(H->partials, grid_blocks(sg), H->scal + kSlotRhs * kReduceWidth, st));
     const dim3 block(32, 4, 2);
     for (int l = 0; l + 1 < H->nlev; ++l) {
         const NodLevel& C = H->lev[l + 1];
         hipLaunchKernelGGL(k_nod_avg_sigma, grid3(C.nx, C.ny, C.nz, block), block, 0, st, H->lev[l], C);
     }
     NHIP(launch_nod_coarse_setup(H->lev[H->nlev - 1], H->minv, H->partials, st));
+    return MG_OK;
+}
+
+// The checks of rho and beta0 in slot kSlotRhs on the host, nonfin more
+// non-finite values among the other inputs.
+int nod_check(nodal_hierarchy* H, double nonfin) {
     const double* q = H->host + kSlotRhs * kReduceWidth;
-    if (q[3] > 0.0) {
+    if (q[3] > 0.0 || nonfin > 0.0) {
         set_error("non-finite value in rho, beta0, U or S");
         return MG_ERR_NONFINITE;
     }
@@ -1111,6 +1156,19 @@ int nod_coefficients(nodal_hierarchy* H, const double* rho, const double* b0c, c
     }
     H->coeffs_valid = true;
     return MG_OK;
+}
+
+int nod_read(nodal_hierarchy* H, int slot, int rows, hipStream_t st) {
+    NHIP(hipMemcpyAsync(H->host + slot * kReduceWidth, H->scal + slot * kReduceWidth,
+                        rows * kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, st));
+    NHIP(hipStreamSynchronize(st));
+    return MG_OK;
+}
+
+int nod_coefficients(nodal_hierarchy* H, const double* rho, const double* b0c, hipStream_t st) {
+    int rc = nod_build(H, rho, b0c, st);
+    if (!rc) rc = nod_read(H, kSlotRhs, 1, st);
+    return rc ? rc : nod_check(H, 0.0);
 }
 
 // The iterations of a solve, `enqueue` putting one on the stream that `stream`
@@ -1279,17 +1337,28 @@ int nod_project(nodal_hierarchy* H, const double* rho, const double* b0c, const 
     std::memset(S_, 0, sizeof *S_);
     S_->nlevels = H->nlev;
     NHIP(hipEventRecord(H->ev0, st));
-    int rc = nod_coefficients(H, rho, b0c, S, u, v, w, st);
+    int rc = nod_build(H, rho, b0c, st);
     if (rc) return S_->status = rc;
     NodLevel& L0 = H->lev[0];
     const size_t NN = L0.nodes();
-    const dim3 ng = point_grid(L0.Nx, L0.Ny, L0.Nz);
-    const int nb = grid_blocks(ng);
-    hipLaunchKernelGGL(k_nod_rhs, ng, dim3(kPtX, kPtY), 0, st, L0, b0c, u, v, w, S, H->partials);
+    // f, then its mean removed and its norm, and one look at all the rows
+    NodResidGrid g = nod_resid_grid(L0, L0.Nz, false);
+    g.ntx = (L0.Nx + kRhsTX - 1) / kRhsTX;        // no more rows than the residual's
+    hipLaunchKernelGGL(k_nod_rhs, dim3(g.blocks()), dim3(64, kNodResidWaves), 0, st, L0, b0c, u, v, w, S, g.tz, g.ntx,
+                       g.nty, H->partials);
     NHIP(hipGetLastError());
-    rc = nod_reduce(H, nb, kSlotNorm, st);
+    NHIP(launch_reduce(H->partials, g.blocks(), H->scal + kSlotNorm * kReduceWidth, st));
+    int np = 0;
+    NHIP(launch_shift_norm(Shape{L0.Nx, L0.Ny, L0.Nz}, L0.f, 0.0, H->partials, &np, st,
+                           H->scal + kSlotNorm * kReduceWidth));
+    NHIP(launch_reduce(H->partials, np, H->scal + kSlotRes * kReduceWidth, st));
+    static_assert(kSlotNorm == kSlotRhs + 1 && kSlotRes == kSlotRhs + 2, "read together");
+    rc = nod_read(H, kSlotRhs, 3, st);
     if (rc) return S_->status = rc;
-    const double sf = H->host[kSlotNorm * kReduceWidth], saf = H->host[kSlotNorm * kReduceWidth + 1];
+    const double* q = H->host + kSlotNorm * kReduceWidth;
+    rc = nod_check(H, q[3]);
+    if (rc) return S_->status = rc;
+    const double sf = q[0], saf = q[1];
     S_->sum_f = sf;
     S_->sum_abs_f = saf;
     if (!std::isfinite(sf) || !std::isfinite(saf)) {
@@ -1300,13 +1369,8 @@ int nod_project(nodal_hierarchy* H, const double* rho, const double* b0c, const 
         set_error("incompatible right-hand side: |sum f| > 1e-8 sum |f|");
         return S_->status = MG_ERR_INCOMPATIBLE_RHS;
     }
-    const double mean = sf / (double)NN;
-    S_->mean_removed = mean;
-    int np = 0;
-    NHIP(launch_shift_norm(Shape{L0.Nx, L0.Ny, L0.Nz}, L0.f, mean, H->partials, &np, st));
-    rc = nod_reduce(H, np, kSlotNorm, st);
-    if (rc) return S_->status = rc;
-    const double fnorm = std::sqrt(H->host[kSlotNorm * kReduceWidth]);
+    S_->mean_removed = sf / (double)NN;
+    const double fnorm = std::sqrt(H->host[kSlotRes * kReduceWidth]);
     S_->norm_f = fnorm;
     int status = MG_OK, cycles = 0;
     double rel = 0.0;
@@ -1512,7 +1576,7 @@ int nodal_set_coefficients(nodal_handle h, const double* rho, const double* beta
         set_error("null argument to nodal_set_coefficients");
         return MG_ERR_INVALID_ARG;
     }
-    return nod_coefficients(h, rho, beta0_cc, nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
+    return nod_coefficients(h, rho, beta0_cc, (hipStream_t)stream);
 }
 
 int nodal_set_graphs(nodal_handle h, int32_t enable) {
