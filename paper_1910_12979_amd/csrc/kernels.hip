@@ -24,7 +24,7 @@
 namespace mg {
 namespace {
 
-constexpr int kBlock = 256;          // threads per block for cell kernels
+constexpr int kBlock = 256;          // threads per block for cell kernels (and of reduce_row256)
 constexpr int kMaxPartialBlocks = 2048;
 
 struct Launch3 {
@@ -56,33 +56,6 @@ inline int partial_blocks(size_t N) {
 
 __device__ inline size_t cidx(int i, int j, int k, int nx, int ny) {
     return ((size_t)k * ny + j) * nx + i;
-}
-
-// Reduce a row of 4 values over a 1-D block of kBlock threads: [0],[1],[3]
-// summed, [2] max.  Fixed tree order.  Thread 0 writes the row.
-__device__ void block_reduce_row(double v0, double v1, double v2, double v3, double* out) {
-    __shared__ double sh[4][kBlock];
-    int t = threadIdx.y * blockDim.x + threadIdx.x;      // kBlock threads, 1-D or 2-D
-    sh[0][t] = v0;
-    sh[1][t] = v1;
-    sh[2][t] = v2;
-    sh[3][t] = v3;
-    __syncthreads();
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if (t < s) {
-            sh[0][t] = sh[0][t] + sh[0][t + s];
-            sh[1][t] = sh[1][t] + sh[1][t + s];
-            sh[2][t] = fmax(sh[2][t], sh[2][t + s]);
-            sh[3][t] = sh[3][t] + sh[3][t + s];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        out[0] = sh[0][0];
-        out[1] = sh[1][0];
-        out[2] = sh[2][0];
-        out[3] = sh[3][0];
-    }
 }
 
 __device__ inline bool finite_d(double x) { return isfinite(x); }
@@ -185,7 +158,7 @@ __device__ void coeff_rhs_body(const CoeffDesc& a, int bxi, int byi, int bzi) {
     }
     }
     const int row = (bzi * a.gy + byi) * a.gx + bxi;
-    block_reduce_row(sf, saf, bad, nonfin, a.partials + (size_t)row * kReduceWidth);
+    reduce_row256(sf, saf, bad, nonfin, a.partials + (size_t)row * kReduceWidth);
 }
 
 template <bool kRhs>
@@ -209,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const double* __restrict__ pa
         a2 = fmax(a2, p[2]);
         a3 += p[3];
     }
-    block_reduce_row(a0, a1, a2, a3, out);
+    reduce_row256(a0, a1, a2, a3, out);
     if (threadIdx.x == 0 && threadIdx.y == 0) {       // out written by this thread
         if (scales) next_scale(out, scales, n);
         if (ring.count) {
@@ -230,14 +203,14 @@ __device__ void shift_norm_body(size_t N, double* __restrict__ f, double shift, 
         f[c] = x;
         s += x * x;
     }
-    block_reduce_row(s, 0.0, 0.0, 0.0, partials + (size_t)b * kReduceWidth);
+    reduce_row256(s, 0.0, 0.0, 0.0, partials + (size_t)b * kReduceWidth);
 }
 
 __device__ void sum_body(size_t N, const double* __restrict__ a, double* __restrict__ partials, int b, int nb) {
     double s = 0.0;
     for (size_t c = (size_t)b * kBlock + threadIdx.x; c < N; c += (size_t)nb * kBlock)
         s += a[c];
-    block_reduce_row(s, 0.0, 0.0, 0.0, partials + (size_t)b * kReduceWidth);
+    reduce_row256(s, 0.0, 0.0, 0.0, partials + (size_t)b * kReduceWidth);
 }
 
 // shift: sum[0] / N with a sum on the device (the host's division, bit for
@@ -481,7 +454,7 @@ __global__ __launch_bounds__(kBlock) void k_resid_norm(int nx, int ny, int nz, T
         s += r * r;
         mx = fmax(mx, fabs(r));
     }
-    block_reduce_row(s, 0.0, mx, nonfin, partials + (size_t)blockIdx.x * kReduceWidth);
+    reduce_row256(s, 0.0, mx, nonfin, partials + (size_t)blockIdx.x * kReduceWidth);
 }
 
 // ---------------------------------------------------------------------------
@@ -816,7 +789,7 @@ __global__ __launch_bounds__(kBlock) void k_coeff_rhs_gen(GenArgs a) {
             saf += fabs(fc);
         }
     }
-    block_reduce_row(sf, saf, bad, nonfin, a.partials + (size_t)blockIdx.x * kReduceWidth);
+    reduce_row256(sf, saf, bad, nonfin, a.partials + (size_t)blockIdx.x * kReduceWidth);
 }
 
 __global__ __launch_bounds__(kBlock) void k_map_radial(GenArgs a, double* __restrict__ out) {
@@ -1470,7 +1443,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_multi(const ReduceDesc* __res
         a2 = fmax(a2, p[2]);
         a3 += p[3];
     }
-    block_reduce_row(a0, a1, a2, a3, r.out);
+    reduce_row256(a0, a1, a2, a3, r.out);
     if (threadIdx.x == 0 && r.copy)
         for (int q = 0; q < kReduceWidth; ++q) r.copy[q] = r.out[q];
 }

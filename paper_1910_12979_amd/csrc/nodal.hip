@@ -161,31 +161,6 @@ __device__ inline void nod_stencil_fast(const NodLevelT<T>& L, const T* __restri
     }
 }
 
-__device__ inline void block_row(double v0, double v1, double v2, double v3, double* out) {
-    __shared__ double sh[4][kNodBlock];
-    const int t = threadIdx.y * blockDim.x + threadIdx.x;
-    sh[0][t] = v0;
-    sh[1][t] = v1;
-    sh[2][t] = v2;
-    sh[3][t] = v3;
-    __syncthreads();
-    for (int s = kNodBlock / 2; s > 0; s >>= 1) {
-        if (t < s) {
-            sh[0][t] = sh[0][t] + sh[0][t + s];
-            sh[1][t] = sh[1][t] + sh[1][t + s];
-            sh[2][t] = fmax(sh[2][t], sh[2][t + s]);
-            sh[3][t] = sh[3][t] + sh[3][t + s];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        out[0] = sh[0][0];
-        out[1] = sh[1][0];
-        out[2] = sh[2][0];
-        out[3] = sh[3][0];
-    }
-}
-
 // Point loops of the reductions: 64 x 4 threads per workgroup over (x, y),
 // the workgroups of a launch striding over x, y and the planes; no
 // per-thread index division.  The partial row of a workgroup is its flat
@@ -209,7 +184,7 @@ __global__ __launch_bounds__(kNodBlock) void k_nod_sigma(NodLevel L, const doubl
         if (!(r > 0.0) || !(b > 0.0)) bad = 1.0;
         L.sig[c] = b / r;
     }
-    block_row(0.0, 0.0, bad, nonfin, partials + (size_t)part_row() * kReduceWidth);
+    reduce_row256(0.0, 0.0, bad, nonfin, partials + (size_t)part_row() * kReduceWidth);
 }
 
 // f_n and partial rows {sum f, sum |f|, 0, #non-finite of u, v, w, S}.  A
@@ -226,7 +201,7 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_rhs(NodLevel L, con
                                                                 const double* __restrict__ S, int tz, int ntx,
                                                                 int nty, double* __restrict__ partials) {
     constexpr int R = kNodResidRows;
-    static_assert(64 * kNodResidWaves == kNodBlock, "block_row");
+    static_assert(64 * kNodResidWaves == kNodBlock, "reduce_row256");
     const int tile = nod_xcd_tile(blockIdx.x, gridDim.x);
     const int tx = tile % ntx, ty = (tile / ntx) % nty, tc = tile / (ntx * nty);
     const int wx = threadIdx.x;
@@ -298,7 +273,7 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_rhs(NodLevel L, con
         }
         lo = hi;
     }
-    block_row(sf, saf, 0.0, nonfin, partials + (size_t)blockIdx.x * kReduceWidth);
+    reduce_row256(sf, saf, 0.0, nonfin, partials + (size_t)blockIdx.x * kReduceWidth);
 }
 
 // One colour of the Gauss-Seidel sweep; thread (I, tj, tk) owns node
