@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_rhs(NodLevel L, con
                                                                 int nty, double* __restrict__ partials) {
     constexpr int R = kNodResidRows;
     static_assert(64 * kNodResidWaves == kNodBlock, "reduce_row256");
-    const int tile = nod_xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_order(blockIdx.x, gridDim.x);
     const int tx = tile % ntx, ty = (tile / ntx) % nty, tc = tile / (ntx * nty);
     const int wx = threadIdx.x;
     const int p = __builtin_amdgcn_readfirstlane(threadIdx.y);
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_rhs(NodLevel L, con
     bool ok[R + 1];
 #pragma unroll
     for (int j = 0; j <= R; ++j) {
-        row[j] = (size_t)nod_fold(gJ - 1 + j, L.ny, L.py) * L.nx + nod_fold(gI, L.nx, L.px);
+        row[j] = (size_t)fold(gJ - 1 + j, L.ny, L.py) * L.nx + fold(gI, L.nx, L.px);
         ok[j] = xc && in(gJ - 1 + j, L.ny, L.py);
     }
     double sf = 0.0, saf = 0.0, nonfin = 0.0;
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_rhs(NodLevel L, con
     };
     auto layer = [&](int k, Layer& y) {
         const bool zk = in(k, L.nz, L.pz);
-        const int kf = nod_fold(k, L.nz, L.pz);
+        const int kf = fold(k, L.nz, L.pz);
         const size_t o = (size_t)kf * nxny;
         double qu[R + 1], qv[R + 1], qw[R + 1], qs[R + 1];
 #pragma unroll

@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "devmath.h"
+#include "lanes.h"
 #include "mg_internal.h"
 
 namespace mg {
@@ -28,68 +29,6 @@ struct NodLevelT {
     __host__ __device__ size_t cells() const { return (size_t)nx * ny * nz; }
 };
 using NodLevel = NodLevelT<double>;
-
-// Index k of a direction of n entries, a few beyond either end: the periodic
-// image, or the nearest entry there is (its value is then not used).
-__device__ __forceinline__ int nod_fold(int k, int n, int per) {
-    if (per) {
-        while (k < 0) k += n;
-        while (k >= n) k -= n;
-        return k;
-    }
-    return min(max(k, 0), n - 1);
-}
-
-// The value of x in the lane below / above (0 at the wavefront's ends): moves
-// within the vector registers, no LDS.  Every lane of the wavefront must be
-// active.
-__device__ __forceinline__ float lane_lo(float x) {
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lane_hi(float x) {
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xf, 0xf, true));
-}
-struct LaneHalves {
-    float a, b;
-};
-__device__ __forceinline__ double lane_lo(double x) {
-    const LaneHalves v = __builtin_bit_cast(LaneHalves, x);
-    return __builtin_bit_cast(double, LaneHalves{lane_lo(v.a), lane_lo(v.b)});
-}
-__device__ __forceinline__ double lane_hi(double x) {
-    const LaneHalves v = __builtin_bit_cast(LaneHalves, x);
-    return __builtin_bit_cast(double, LaneHalves{lane_hi(v.a), lane_hi(v.b)});
-}
-
-// Workgroup b of n runs on XCD b mod 8: tile of it such that an XCD's
-// workgroups have consecutive tiles, whose windows overlap in its L2.
-__device__ __forceinline__ int nod_xcd_tile(int b, int n) {
-    const int x = b % 8, q = n / 8, r = n % 8;
-    return x * q + min(x, r) + b / 8;
-}
-
-// Four loaded values, waited for together at this point.
-template <typename T>
-__device__ __forceinline__ void at_once(T& a, T& b, T& c, T& d) {
-    asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
-}
-
-// Element at byte offset o (32 bits: a plane's) of a plane that starts at
-// index k * n of a: the plane's address stays in scalar registers.
-template <typename T>
-__device__ __forceinline__ const T* nod_plane(const T* a, int k, size_t n) {
-    return a + (size_t)(unsigned)k * n;
-}
-template <typename T>
-__device__ __forceinline__ T at_byte(const T* a, unsigned o) {
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(a) + o);
-}
-template <typename T>
-__device__ __forceinline__ void put_byte(T* a, unsigned o, T v) {
-    *reinterpret_cast<T*>(reinterpret_cast<char*>(a) + o) = v;
-}
 
 // A cell coefficient as a node column uses it: of the cell on its high side
 // in x (the lane's own) and on its low side (the lane's below).
@@ -180,7 +119,7 @@ __global__ __launch_bounds__(64 * P) void k_nod_sweep(NodLevelT<T> L, T* __restr
     __shared__ T se[4][P][64];              // even rows of a plane, by (plane - ks) & 3
     __shared__ T so[4][P][64];              // odd rows
     __shared__ T sc[2][P][64];              // odd rows of the two newest cell layers
-    const int tile = nod_xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_order(blockIdx.x, gridDim.x);
     const int tx = tile % ntx, ty = (tile / ntx) % nty, tc = tile / (ntx * nty);
     const int ks = tc * tz, ke = min(ks + tz, etop);
     const int wx = threadIdx.x;
@@ -192,9 +131,9 @@ __global__ __launch_bounds__(64 * P) void k_nod_sweep(NodLevelT<T> L, T* __restr
     const bool xn = in(gI, L.Nx, L.px), xc = in(gI, L.nx, L.px);
     const bool yne = in(gJe, L.Ny, L.py), yce = in(gJe, L.ny, L.py);
     const bool yno = in(gJo, L.Ny, L.py), yco = in(gJo, L.ny, L.py);
-    const int Iw = nod_fold(gI, L.Nx, L.px), iw = nod_fold(gI, L.nx, L.px);
-    const int Je = nod_fold(gJe, L.Ny, L.py), Jo = nod_fold(gJo, L.Ny, L.py);
-    const int je = nod_fold(gJe, L.ny, L.py), jo = nod_fold(gJo, L.ny, L.py);
+    const int Iw = fold(gI, L.Nx, L.px), iw = fold(gI, L.nx, L.px);
+    const int Je = fold(gJe, L.Ny, L.py), Jo = fold(gJo, L.Ny, L.py);
+    const int je = fold(gJe, L.ny, L.py), jo = fold(gJo, L.ny, L.py);
     const size_t NxNy = (size_t)L.Nx * L.Ny, nxny = (size_t)L.nx * L.ny;
     constexpr unsigned kB = sizeof(T);            // byte offsets within a plane
     const unsigned ne = ((unsigned)Je * L.Nx + Iw) * kB, no = ((unsigned)Jo * L.Nx + Iw) * kB;
@@ -206,30 +145,30 @@ __global__ __launch_bounds__(64 * P) void k_nod_sweep(NodLevelT<T> L, T* __restr
     // beyond a wall become 0 when they are taken up (so the clamped values of
     // nodes beyond it, which are never updated, add exact zeros).
     auto ld_node = [&](const T* __restrict__ a, int K, T& e, T& o) {      // K, k: folded
-        const T* q = nod_plane(a, K, NxNy);
+        const T* q = plane_at(a, K, NxNy);
         e = at_byte(q, ne);
         o = at_byte(q, no);
     };
     auto ld_sig = [&](int k, T& e, T& o) {
-        const T* q = nod_plane(L.sig, k, nxny);
+        const T* q = plane_at(L.sig, k, nxny);
         e = at_byte(q, ce);
         o = at_byte(q, co);
     };
-    auto fn = [&](int K) { return nod_fold(K, L.Nz, L.pz); };
-    auto fc = [&](int k) { return nod_fold(k, L.nz, L.pz); };
+    auto fn = [&](int K) { return fold(K, L.Nz, L.pz); };
+    auto fc = [&](int k) { return fold(k, L.nz, L.pz); };
     // The coarse correction: an even column reads its parent, an odd one the
     // parent above it and takes the other from the lane below; in the coarse
     // rows at and above the even row.
     const bool oddx = wx & 1;
     unsigned c0 = 0, c1 = 0;
     if (kProlong) {
-        const int I1 = nod_fold((Iw + 1) >> 1, C.Nx, L.px);
-        const int J0 = Je >> 1, J1 = nod_fold((Jo + 1) >> 1, C.Ny, L.py);
+        const int I1 = fold((Iw + 1) >> 1, C.Nx, L.px);
+        const int J0 = Je >> 1, J1 = fold((Jo + 1) >> 1, C.Ny, L.py);
         c0 = ((unsigned)J0 * C.Nx + I1) * kB;
         c1 = ((unsigned)J1 * C.Nx + I1) * kB;
     }
     auto ld_coarse = [&](int K, T& a, T& b) {     // K: coarse plane, folded
-        const T* q = nod_plane(C.phi, K, (size_t)C.Nx * C.Ny);
+        const T* q = plane_at(C.phi, K, (size_t)C.Nx * C.Ny);
         a = at_byte(q, c0);
         b = at_byte(q, c1);
     };
@@ -261,9 +200,9 @@ __global__ __launch_bounds__(64 * P) void k_nod_sweep(NodLevelT<T> L, T* __restr
         ld_node(L.f, fn(ks), fe0, fo0);
         if (kProlong) {
             T ue, uo, ve, vo, we, wo;
-            ld_coarse(nod_fold((ks - 2) / 2, C.Nz, L.pz), ue, uo);
-            ld_coarse(nod_fold(ks / 2, C.Nz, L.pz), ve, vo);
-            ld_coarse(nod_fold((ks + 2) / 2, C.Nz, L.pz), we, wo);
+            ld_coarse(fold((ks - 2) / 2, C.Nz, L.pz), ue, uo);
+            ld_coarse(fold(ks / 2, C.Nz, L.pz), ve, vo);
+            ld_coarse(fold((ks + 2) / 2, C.Nz, L.pz), we, wo);
             interp(ue, uo, ue, uo);
             interp(ve, vo, ve, vo);
             interp(we, wo, we, wo);
@@ -296,7 +235,7 @@ __global__ __launch_bounds__(64 * P) void k_nod_sweep(NodLevelT<T> L, T* __restr
     // planes E+1, E+2, E+3 and layers E+1, E+2, folded; two on per step (at
     // least two planes and two layers in a periodic direction)
     int k1 = fn(ks + 1), k2 = fn(ks + 2), k3 = fn(ks + 3), l1 = fc(ks + 1), l2 = fc(ks + 2);
-    int kc = kProlong ? nod_fold(ks / 2 + 2, C.Nz, L.pz) : 0;
+    int kc = kProlong ? fold(ks / 2 + 2, C.Nz, L.pz) : 0;
     int ko0 = fn(ks), ko1 = fn(ks - 1);           // planes E and E-1
     auto on = [&](int& k, int step, int n) {
         k += step;
@@ -489,7 +428,7 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_resid(NodLevelT<T> 
     constexpr bool kRestrict = kMode == kNodRestrict, kRefine = kMode == kNodRefine;
     constexpr int R = kNodResidRows, P = kNodResidWaves;
     __shared__ double sh[kRestrict ? 2 * P * 64 : 3 * P];
-    const int tile = nod_xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_order(blockIdx.x, gridDim.x);
     const int tx = tile % ntx, ty = (tile / ntx) % nty, tc = tile / (ntx * nty);
     const int wx = threadIdx.x;
     const int p = __builtin_amdgcn_readfirstlane(threadIdx.y);
@@ -502,14 +441,14 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_resid(NodLevelT<T> 
     const size_t NxNy = (size_t)L.Nx * L.Ny, nxny = (size_t)L.nx * L.ny;
     const bool xn = in(gI, L.Nx, L.px), xc = in(gI, L.nx, L.px);
     constexpr unsigned kB = sizeof(T);
-    const unsigned xo = (unsigned)nod_fold(gI, L.Nx, L.px), co = (unsigned)nod_fold(gI, L.nx, L.px) * kB;
+    const unsigned xo = (unsigned)fold(gI, L.Nx, L.px), co = (unsigned)fold(gI, L.nx, L.px) * kB;
     size_t nrow[R + 2], crow[R + 1];              // rows gJ - 1 .. gJ + 4 of nodes, gJ - 1 .. gJ + 3 of cells
     bool cok[R + 1];
 #pragma unroll
-    for (int j = 0; j < R + 2; ++j) nrow[j] = (size_t)nod_fold(gJ - 1 + j, L.Ny, L.py) * L.Nx;
+    for (int j = 0; j < R + 2; ++j) nrow[j] = (size_t)fold(gJ - 1 + j, L.Ny, L.py) * L.Nx;
 #pragma unroll
     for (int j = 0; j < R + 1; ++j) {
-        crow[j] = (size_t)nod_fold(gJ - 1 + j, L.ny, L.py) * L.nx;
+        crow[j] = (size_t)fold(gJ - 1 + j, L.ny, L.py) * L.nx;
         cok[j] = xc && in(gJ - 1 + j, L.ny, L.py);
     }
     const double inv_s = kRefine ? 1.0 / ra.scales[0] : 0.0;     // exact: a power of two
@@ -517,22 +456,22 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_resid(NodLevelT<T> 
     const T ih = (T)(12.0 * L.h * L.h);
 
     auto ld_phi = [&](int K, T (&v)[R + 2], float (&c)[R + 2]) {
-        const T* q = nod_plane(L.phi, K, NxNy);
+        const T* q = plane_at(L.phi, K, NxNy);
 #pragma unroll
         for (int j = 0; j < R + 2; ++j) v[j] = at_byte(q + nrow[j], xo * kB);
         if (kRefine) {
-            const float* d = nod_plane(ra.corr, K, NxNy);
+            const float* d = plane_at(ra.corr, K, NxNy);
 #pragma unroll
             for (int j = 0; j < R + 2; ++j) c[j] = at_byte(d + nrow[j], xo * 4u);
         }
     };
     auto ld_sig = [&](int k, T (&v)[R + 1]) {
-        const T* q = nod_plane(L.sig, k, nxny);
+        const T* q = plane_at(L.sig, k, nxny);
 #pragma unroll
         for (int j = 0; j < R + 1; ++j) v[j] = at_byte(q + crow[j], co);
     };
     auto ld_f = [&](int K, T (&v)[R]) {
-        const T* q = nod_plane(L.f, K, NxNy);
+        const T* q = plane_at(L.f, K, NxNy);
 #pragma unroll
         for (int j = 0; j < R; ++j) v[j] = at_byte(q + nrow[j + 1], xo * kB);
     };
@@ -545,8 +484,8 @@ __global__ __launch_bounds__(64 * kNodResidWaves) void k_nod_resid(NodLevelT<T> 
 #pragma unroll
         for (int j = 0; j < R + 1; ++j) v[j] = sig_pair((ok && cok[j]) ? q[j] : T(0));
     };
-    auto fn = [&](int K) { return nod_fold(K, L.Nz, L.pz); };
-    auto fc = [&](int k) { return nod_fold(k, L.nz, L.pz); };
+    auto fn = [&](int K) { return fold(K, L.Nz, L.pz); };
+    auto fc = [&](int k) { return fold(k, L.nz, L.pz); };
 
     T pb[R + 2], pc[R + 2], pt[R + 2], f[R];      // planes K-1, K, K+1
     SigPair<T> sb[R + 1], st[R + 1];              // layers K-1, K

@@ -19,6 +19,7 @@
 #include "mg_internal.h"
 #include "runtime.h"
 #include "sweep.h"
+#include "sweep2.h"
 
 namespace mg {
 
@@ -488,7 +489,8 @@ static int smooth(mg_hierarchy* H, int l, int nsweeps, int first, hipStream_t st
     }
     // finest level: coefficients from rho (FP64) or its FP32 copy (mixed solve)
     const bool use_rho = l == 0 && (dbl ? H->rho.rho != nullptr : H->rho32_on);
-    for (int k = 0; k < nsweeps; ++k) {
+    const bool pairs = !dbl && use_rho && !F.has_bnd && sweep_paired(F.nx, F.ny, F.nz);
+    for (int k = 0, done = 1; k < nsweeps; k += done) {
         SweepArgs<T> a{};
         a.nx = F.nx;
         a.ny = F.ny;
@@ -515,10 +517,14 @@ static int smooth(mg_hierarchy* H, int l, int nsweeps, int first, hipStream_t st
         else a.dg = F.dg_s;
         a.march_div = sweep_marchable(F.nx, F.ny, F.nz) ? 1 : 0;
         const int mode = k == 0 ? first : (int)kInPlain;
-        HIPCHK(launch_sweep<T>(a, use_rho, mode,
-                               mode == kInZero ? zero_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0)
-                                               : sweep_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0),
-                               st));
+        done = pairs && nsweeps - k >= 2 ? 2 : 1;
+        if constexpr (!dbl)
+            if (done == 2) HIPCHK(launch_sweep2(a, mode, st));
+        if (done == 1)
+            HIPCHK(launch_sweep<T>(a, use_rho, mode,
+                                   mode == kInZero ? zero_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0)
+                                                   : sweep_config_for(F.nx, F.ny, F.nz, use_rho, dbl, l > 0),
+                                   st));
         std::swap(A->phi, *alt);
     }
     return MG_OK;
