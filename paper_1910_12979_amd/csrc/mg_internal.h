@@ -9,6 +9,7 @@
 #include <string>
 
 #include "../../include/macproj.h"
+#include "cycles.h"
 
 namespace mg {
 
@@ -237,28 +238,12 @@ hipError_t launch_dp0_term(int nz, const double* p0c, const double* g1c, const d
 hipError_t launch_coeff(const Shape& s, int px, int py, int pz, const double* rho,
                         const double* b0c, const double* b0e, double* bx, double* by,
                         double* bz, double* partials, int* nparts, hipStream_t st);
-// Residual norms of the cycles of a solve on the device, the c-th of them (from
-// 0) in row c mod kNormRing, so that several cycles can run before the host
-// looks (norm_ahead).  count: how many there are.
-constexpr int kNormRing = 8;
+// The ring of residual norms of a solve's cycles (cycles.h); count: how many
+// there are.
 struct NormRing {
     double* rows = nullptr;
     int* count = nullptr;
 };
-// How many cycles to enqueue before looking at the next residual norm: as many
-// as are sure to be needed, one if nothing is known yet (rel: the last relative
-// residual, best: the smallest ratio of two successive ones so far, room:
-// cycles allowed).  A cycle counts as needed if the residual ahead of it, at
-// ten times below what the best ratio predicts, is above rtol.  V-cycles reduce
-// the residual at a nearly constant rate, slower rather than faster as they go
-// on; a solve that is found to have converged ahead of the last cycle enqueued
-// all the same is run again without looking ahead.
-inline int norm_ahead(double rel, double best, double rtol, int room) {
-    int m = 1;
-    if (!(best > 0.0 && best < 1.0)) return m;
-    for (double p = rel * best; m < kNormRing && m < room && p > 10.0 * rtol; p *= best) ++m;
-    return m;
-}
 // Fixed-order reduction of nparts rows of kReduceWidth doubles into out[0..3];
 // appended to ring as well, or with restart the ring emptied.
 hipError_t launch_reduce(const double* partials, int nparts, double* out, hipStream_t st, NormRing ring = NormRing{},

@@ -1146,49 +1146,26 @@ int nod_coefficients(nodal_hierarchy* H, const double* rho, const double* b0c, h
     return rc ? rc : nod_check(H, 0.0);
 }
 
-// The iterations of a solve, `enqueue` putting one on the stream that `stream`
-// then names: as many at a time as norm_ahead allows.  *over: converged before
-// the last one enqueued, so that the solve has to be run again without looking
-// ahead.
+// The iterations of a solve (run_ahead), each of `step` V-cycles, `enqueue`
+// putting one on the stream that `stream` then names.
 template <typename E, typename Q>
-int nod_cycles(nodal_hierarchy* H, double fnorm, mg_stats* S_, bool ahead, int* status, int* cycles, double* rel,
-               bool* over, E&& enqueue, Q&& stream) {
-    double best = 0.0;
-    *over = false;
+int nod_cycles(nodal_hierarchy* H, double fnorm, mg_stats* S_, bool ahead, int step, int* status, int* cycles,
+               double* rel, bool* over, E&& enqueue, Q&& stream) {
     *status = MG_ERR_NOT_CONVERGED;
-    while (*cycles < H->p.max_cycles) {
-        const int m = ahead ? norm_ahead(*rel, best, H->p.rtol, H->p.max_cycles - *cycles) : 1;
-        for (int i = 0; i < m; ++i) {
-            int rc = enqueue();
-            if (rc) return rc;
-        }
+    auto rows = [&](const double** r) -> int {
         const hipStream_t st = stream();
-        NHIP(hipMemcpyAsync(H->host + kSlotRing * kReduceWidth, H->scal + kSlotRing * kReduceWidth,
-                            kNormRing * kReduceWidth * sizeof(double), hipMemcpyDeviceToHost, st));
-        NHIP(hipStreamSynchronize(st));
-        for (int i = 0; i < m; ++i) {
-            const double* r = H->host + (kSlotRing + *cycles % kNormRing) * kReduceWidth;
-            const double was = *rel;
-            *rel = std::sqrt(r[0]) / fnorm;
-            ++*cycles;
-            if (*cycles < MG_HIST_MAX) {
-                S_->resid_hist[*cycles] = *rel;
-                S_->hist_len = *cycles + 1;
-            }
-            if (r[3] > 0.0 || !std::isfinite(*rel)) {
-                set_error("non-finite residual during the solve");
-                *status = MG_ERR_NONFINITE;
-                return MG_OK;
-            }
-            if (*rel <= H->p.rtol) {
-                *status = MG_OK;
-                *over = i + 1 < m;
-                return MG_OK;
-            }
-            best = *cycles == 1 ? *rel / was : std::min(best, *rel / was);
-        }
-    }
-    return MG_OK;
+        *r = H->host + kSlotRing * kReduceWidth;
+        return nod_read(H, kSlotRing, kNormRing, st);
+    };
+    auto record = [&](int c, double r) {
+        if (c >= MG_HIST_MAX) return;
+        S_->resid_hist[c] = r;
+        S_->hist_len = c + 1;
+    };
+    int rc = run_ahead(fnorm, H->p.rtol, H->p.max_cycles, ahead, std::pow(kFirstGainNodal, step), kReduceWidth, status,
+                       cycles, rel, over, [&](int) { return enqueue(); }, rows, record);
+    if (rc == MG_OK && *status == MG_ERR_NONFINITE) set_error("non-finite residual during the solve");
+    return rc;
 }
 
 // Mixed-precision solve (iterative refinement with the multigrid of Sec. 3
@@ -1232,7 +1209,7 @@ int nod_solve_mixed(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status_
                                  norm_ring(H->scal)));
         return MG_OK;
     };
-    int rc = nod_cycles(H, fnorm, S_, ahead, &status, &cycles, &rel, over, cycle, [&] { return st; });
+    int rc = nod_cycles(H, fnorm, S_, ahead, inner, &status, &cycles, &rel, over, cycle, [&] { return st; });
     if (rc) return rc;
     *status_out = status;
     *cycles_out = cycles;
@@ -1303,7 +1280,7 @@ int nod_solve(nodal_hierarchy* H, double fnorm, mg_stats* S_, int* status, int* 
         NHIP(hipGraphLaunch(H->cycle_exec, H->gstream));
         return MG_OK;
     };
-    return nod_cycles(H, fnorm, S_, ahead, status, cycles, rel, over, enqueue,
+    return nod_cycles(H, fnorm, S_, ahead, 1, status, cycles, rel, over, enqueue,
                       [&] { return on_graph ? H->gstream : st; });
 }
 

@@ -746,55 +746,23 @@ static int enqueue_sweep_norm(mg_hierarchy* H, hipStream_t st) {
     return MG_OK;
 }
 
-// The norms of the cycles enqueued since the last look, on the host when this
-// returns.
-static int read_ring(mg_hierarchy* H, hipStream_t st) {
-    return read_scalars(H, kSlotRing * kReduceWidth, kNormRing * kReduceWidth, st);
-}
 static hipError_t empty_ring(mg_hierarchy* H, hipStream_t st) {
     return launch_reduce(H->partials, 0, H->scal + kSlotRes * kReduceWidth, st, norm_ring(H->scal), true);
 }
-static const double* ring_row(const mg_hierarchy* H, int cycle) {      // cycle: from 0
-    return H->host + (kSlotRing + cycle % kNormRing) * kReduceWidth;
-}
 
-// The iterations of a solve, `enqueue` putting one on the stream that `stream`
-// then names: as many at a time as norm_ahead allows.  *over: converged before
-// the last one enqueued, so that the solve has to be run again without looking
-// ahead.
+// The iterations of a solve (run_ahead), each of `step` V-cycles, `enqueue`
+// putting one on the stream that `stream` then names.
 template <typename E, typename S, typename R>
-static int run_cycles(mg_hierarchy* H, double fnorm, bool ahead, int* status, int* cycles, double* rel, bool* over,
-                      E&& enqueue, S&& stream, R&& record) {
-    double best = 0.0;
-    *over = false;
-    while (*status == MG_ERR_NOT_CONVERGED && *cycles < H->p.max_cycles) {
-        const int m = ahead ? norm_ahead(*rel, best, H->p.rtol, H->p.max_cycles - *cycles) : 1;
-        for (int i = 0; i < m; ++i) {
-            int rc = enqueue(*cycles + i);
-            if (rc) return rc;
-        }
-        int rc = read_ring(H, stream());
-        if (rc) return rc;
-        for (int i = 0; i < m; ++i) {
-            const double* r = ring_row(H, *cycles);
-            const double was = *rel;
-            *rel = std::sqrt(r[0]) / fnorm;
-            ++*cycles;
-            record(*cycles, *rel);
-            if (r[3] > 0.0 || !std::isfinite(*rel)) {
-                *status = MG_ERR_NONFINITE;
-                set_error("non-finite residual during the solve");
-                return MG_OK;
-            }
-            if (*rel <= H->p.rtol) {
-                *status = MG_OK;
-                *over = i + 1 < m;
-                return MG_OK;
-            }
-            best = *cycles == 1 ? *rel / was : std::min(best, *rel / was);
-        }
-    }
-    return MG_OK;
+static int run_cycles(mg_hierarchy* H, double fnorm, bool ahead, int step, int* status, int* cycles, double* rel,
+                      bool* over, E&& enqueue, S&& stream, R&& record) {
+    auto rows = [&](const double** r) {
+        *r = H->host + kSlotRing * kReduceWidth;
+        return read_scalars(H, kSlotRing * kReduceWidth, kNormRing * kReduceWidth, stream());
+    };
+    int rc = run_ahead(fnorm, H->p.rtol, H->p.max_cycles, ahead, std::pow(kFirstGainMac, step), kReduceWidth, status,
+                       cycles, rel, over, enqueue, rows, record);
+    if (rc == MG_OK && *status == MG_ERR_NONFINITE) set_error("non-finite residual during the solve");
+    return rc;
 }
 
 // Everything a captured iteration bakes in: coefficient source, sweep
@@ -988,7 +956,7 @@ static int solve_level0_mixed_fused(mg_hierarchy* H, double fnorm, int* cycles_o
     double rel = 1.0;
     bool on_graph = false;
     int rc = run_cycles(
-        H, fnorm, ahead, &status, &cycles, &rel, over,
+        H, fnorm, ahead, inner, &status, &cycles, &rel, over,
         [&](int) { return run_iteration(H, st, &on_graph, kIterMixed, iteration); },
         [&] { return on_graph ? H->gstream : st; }, record);
     if (rc) return rc;
@@ -1051,7 +1019,7 @@ static int solve_level0_boxes(mg_hierarchy* H, double fnorm, mg_stats* stats, hi
         HIPCHK(launch_reduce(H->partials, np, H->scal + kSlotRes * kReduceWidth, st, norm_ring(H->scal)));
         return MG_OK;
     };
-    int rc = run_cycles(H, fnorm, ahead, &status, &cycles, &rel, &over, cycle, [&] { return st; }, record);
+    int rc = run_cycles(H, fnorm, ahead, 1, &status, &cycles, &rel, &over, cycle, [&] { return st; }, record);
     if (rc) return rc;
     if (over) return solve_level0_boxes(H, fnorm, stats, st, false);
     HIPCHK(launch_box_gather(B, L0.d.phi, st));
@@ -1116,7 +1084,7 @@ static int solve_level0_boxes_mixed(mg_hierarchy* H, double fnorm, mg_stats* sta
                                    norm_ring(H->scal)));
         return MG_OK;
     };
-    int rc = run_cycles(H, fnorm, ahead, &status, &cycles, &rel, &over, cycle, [&] { return st; }, record);
+    int rc = run_cycles(H, fnorm, ahead, inner, &status, &cycles, &rel, &over, cycle, [&] { return st; }, record);
     if (rc) return rc;
     if (over) return solve_level0_boxes_mixed(H, fnorm, stats, st, false);
     HIPCHK(launch_box_gather(B, L0.d.phi, st));
@@ -1166,7 +1134,7 @@ static int solve_level0(mg_hierarchy* H, double fnorm, mg_stats* stats, hipStrea
     } else if (fused_norm) {
         bool on_graph = false;
         int rc = run_cycles(
-            H, fnorm, ahead, &status, &cycles, &rel, &over,
+            H, fnorm, ahead, 1, &status, &cycles, &rel, &over,
             [&](int c) -> int {
                 if (c == 0) {
                     int r2 = vcycle<double>(H, 0, st, 0, true);
