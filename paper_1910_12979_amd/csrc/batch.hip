@@ -809,7 +809,7 @@ int Engine::setup_new(std::vector<Job*>& fresh, hipStream_t st) {
         }
         const mg_problem& p = j->pr;
         const double* rho_src = p.rho;
-        if (((uintptr_t)p.rho & 15) != 0) {       // the fused sweeps read rho as 16-byte pairs
+        if (rho_copied(p.rho, p.phi, H->lev[0].N)) {
             BHIP(launch_copy(H->rho_own, p.rho, H->lev[0].N, st));
             rho_src = H->rho_own;
         }
@@ -1095,9 +1095,9 @@ int Engine::round(std::vector<Job*>& jobs, hipStream_t st) {
             sb += rb;
             rd.push_back(ReduceDesc{H->partials, rb, H->scal + kSlotPhi * kReduceWidth,
                                     gdev + (nrun + q) * kReduceWidth});
-            cd.push_back(CorrectDesc{L0.nx, L0.ny, L0.nz, H->px, H->py, H->pz, L0.h, p.beta0_cc, p.beta0_edge, p.rho,
-                                     L0.d.phi, H->scal + kSlotPhi * kReduceWidth, p.u, p.v, p.w,
-                                     p.phi, cb});
+            cd.push_back(CorrectDesc{L0.nx, L0.ny, L0.nz, H->px, H->py, H->pz, L0.h, p.beta0_cc, p.beta0_edge,
+                                     H->rho.rho, L0.d.phi, H->scal + kSlotPhi * kReduceWidth, p.u, p.v, p.w, p.phi,
+                                     cb});
             cb += cell_blocks(L0.N);
         }
         const RowDesc* dsd = nullptr;

@@ -99,6 +99,13 @@ int setup_static(const mg_params* p, void* ws, size_t ws_bytes, double* host, mg
 int project(mg_hierarchy* H, const double* rho, const double* b0c, const double* b0e, const double* S,
             double* u, double* v, double* w, double* phi_out, mg_stats* stats, hipStream_t st,
             const double* w0 = nullptr, const Radial* rad = nullptr);
+// Whether a projection works on a copy of rho: the fused finest-level sweeps
+// read it as 16-byte pairs, and the correction reads a cell's neighbours while
+// others write phi_out, which the caller may have laid over rho.
+inline bool rho_copied(const double* rho, const double* phi_out, size_t n) {
+    const uintptr_t a = (uintptr_t)rho, b = (uintptr_t)phi_out, bytes = n * sizeof(double);
+    return (a & 15) != 0 || (phi_out && a < b + bytes && b < a + bytes);
+}
 double model_bytes(const mg_params& p, int cycles, int mixed);
 // First level run by the one-workgroup bottom solver, or -1.
 int bottom_start(const mg_hierarchy* H);

@@ -1209,9 +1209,8 @@ static int project_impl(mg_hierarchy* H, const double* rho, const double* b0c, c
     const auto t_host0 = std::chrono::steady_clock::now();
     if (H->ev0) HIPCHK(hipEventRecord(H->ev0, st));
     Level& L0 = H->lev[0];
-    // the fused finest-level sweep reads rho as 16-byte pairs
     const double* rho_src = rho;
-    if (((uintptr_t)rho & 15) != 0) {
+    if (rho_copied(rho, phi_out, L0.N)) {
         HIPCHK(launch_copy(H->rho_own, rho, L0.N, st));
         rho_src = H->rho_own;
     }
@@ -1282,11 +1281,11 @@ static int project_impl(mg_hierarchy* H, const double* rho, const double* b0c, c
         if (rc) return rc;
     }
     if (H->outflow || radial) {
-        const GenArgs g = gen_args(H, rho, b0c, b0e, rad);
+        const GenArgs g = gen_args(H, rho_src, b0c, b0e, rad);
         HIPCHK(launch_correct_gen(g, L0.d.phi, H->singular ? H->scal + kSlotPhi * kReduceWidth : nullptr, u, v, w,
                                   phi_out, st));
     } else {
-        HIPCHK(launch_correct(shape_of(L0), H->px, H->py, H->pz, L0.h, b0c, b0e, rho, L0.d.phi,
+        HIPCHK(launch_correct(shape_of(L0), H->px, H->py, H->pz, L0.h, b0c, b0e, rho_src, L0.d.phi,
                               H->scal + kSlotPhi * kReduceWidth, u, v, w, phi_out, st));
     }
     if (H->ev1) HIPCHK(hipEventRecord(H->ev1, st));
