@@ -392,16 +392,20 @@ int serve_counters(void* server, double out[6]);
 /* Finish all tickets and release the server. */
 int serve_destroy(void* server);
 
-/* Tuning: force fused-sweep tile configuration cfg (0..11: 32x8x32, 32x8x64,
+/* Tuning: force fused-sweep tile configuration cfg (0..13: 32x8x32, 32x8x64,
  * 64x8x32, 32x16x32, 64x4x64, 32x4x64, 32x8x16, 32x8x8, 64x8x64, 64x16x32,
- * 32x32x32, 64x16x64 cells per workgroup tile x planes per chunk) on every
- * level that fits it; -1 restores the per-shape default.
+ * 32x32x32, 64x16x64, 32x8x4, 32x4x4 cells per workgroup tile x planes per
+ * chunk) on every level that fits it; -1 restores the per-shape default.
  * Process-wide; results do not depend on it (the sweep is exact per cell). */
 int mg_tune_sweep(int32_t cfg);
 
 /* Autotune: time every fused-sweep configuration that fits each level of h
- * (`reps` sweeps each, on `stream`) and keep the fastest per level shape in a
- * process-wide table used by every later solve of that shape.  Needs
+ * (`reps` sweeps each, on `stream`), the untuned choice among them, and keep
+ * the fastest per level shape in a process-wide table used by every later
+ * solve of that shape (in batches, whose work fills the chip, the 4-plane
+ * configurations 12 and 13 are passed over).  A level whose fastest form is
+ * the one without an index (mg_sweep_config) has no entry.  A table written by
+ * an earlier version keeps the tiles that were the fastest then.  Needs
  * coefficients (mg_set_coefficients or mac_project); overwrites the
  * hierarchy's own level arrays, never caller data.  Blocks until done.
  * With the environment variable MACPROJ_TUNE_CACHE naming a file, the table
@@ -477,9 +481,12 @@ int mg_set_bottom(mg_handle h, int32_t enable);
 int mg_set_boxes(mg_handle h, const int32_t box[3]);
 
 /* Fused-sweep tile used on level l of h: tile[0..2] = cells per workgroup
- * tile in x, y and planes per z-chunk, tile[3] = configuration index (as for
- * mg_tune_sweep).  All four are -1 for a level the fused sweep does not cover
- * (it then runs one kernel per colour). */
+ * tile in x, y and planes per z-chunk, tile[3] = configuration index, as for
+ * mg_tune_sweep, or 14, which that does not take: 16x8x4-cell tiles without a
+ * march, for small levels.  (On the largest finest levels two FP32 sweeps in a
+ * row run as one launch with tiles of its own; single ones take these.)  All
+ * four are -1 for a level the fused sweep does not cover (it then runs one
+ * kernel per colour). */
 int mg_sweep_config(mg_handle h, int32_t level, int32_t tile[4]);
 
 /* ---- allocation-free projection ------------------------------------------ */

@@ -1722,9 +1722,16 @@ int mg_autotune(mg_handle h, int32_t reps, void* stream) {
         const bool rho = l == 0 && h->rho.rho != nullptr;
         float best = 1e30f;
         int best_cfg = -1;
-        for (int c = 0; c < kNumSweepCfg && rc == MG_OK; ++c) {
-            if (!sweep_cfg_fits(F.nx, F.ny, c) || (l == 0 && c >= kFirstCoarseCfg)) continue;
-            sweep_force_config(c);
+        const int before = tune_find(F.nx, F.ny, F.nz, rho, true, l > 0);
+        tune_erase(F.nx, F.ny, F.nz, rho, true, l > 0);
+        for (int c = 0; c <= kNumSweepCfg && rc == MG_OK; ++c) {
+            if (c == kTileCfg) {        // timed where it is the untuned choice; kept by having no entry
+                sweep_force_config(-1);
+                if (sweep_config_for(F.nx, F.ny, F.nz, rho, true, l > 0) != kTileCfg) continue;
+            } else {
+                if (!sweep_cfg_fits(F.nx, F.ny, c)) continue;
+                sweep_force_config(c);
+            }
             rc = smooth<double>(h, l, 1, kInPlain, st);          // warm
             if (rc) break;
             hipEventRecord(e0, st);
@@ -1738,7 +1745,8 @@ int mg_autotune(mg_handle h, int32_t reps, void* stream) {
                 best_cfg = c;
             }
         }
-        if (best_cfg >= 0) sweep_record_tuned(F.nx, F.ny, F.nz, rho, true, best_cfg, l > 0);
+        const int keep = rc == MG_OK ? best_cfg : before;
+        if (keep >= 0 && keep != kTileCfg) sweep_record_tuned(F.nx, F.ny, F.nz, rho, true, keep, l > 0);
     }
     sweep_force_config(saved);
     hipEventDestroy(e0);

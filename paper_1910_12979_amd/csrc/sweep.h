@@ -22,7 +22,7 @@ struct SweepCfg {
     int tx, ty, tz;
 };
 constexpr int kNumSweepCfg = 14;
-constexpr int kFirstCoarseCfg = 12;     // 4-plane chunks: coarse levels of a single problem
+constexpr int kFirstCoarseCfg = 12;     // 4-plane chunks: levels that leave the chip idle (not in batches)
 constexpr int kTileCfg = kNumSweepCfg;  // small levels: no march (tile.hip); never forced, tuned or saved
 constexpr SweepCfg kSweepCfgs[kNumSweepCfg + 1] = {
     {32, 8, 32}, {32, 8, 64}, {64, 8, 32}, {32, 16, 32}, {64, 4, 64},  {32, 4, 64}, {32, 8, 16},
@@ -158,7 +158,7 @@ hipError_t launch_sweep_boxes_mode(const SweepArgs<T>& a, const BoxGeom& g, int 
 // The configuration of the residual + restriction, which needs no ring of red
 // cells: kTileCfg up to kTileRestrict cells (64^3 FP64, stored coefficients:
 // 5.2 us against 6.7 with one thread per coarse cell), else the sweep's (128^3 24.0
-// -> 18.7 us); in FP32 32-plane chunks where the sweep takes 64, as two of its
+// -> 18.7 us); tuned entries, timed on sweeps, say nothing about it.  In FP32 32-plane chunks where the sweep takes 64, as two of its
 // workgroups share a CU (256^3 47.5 us against 54.8, 512^3 the same).
 int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse);
 // The configuration of a sweep from zero: the sweep's, but in FP32, where two of
@@ -193,6 +193,7 @@ unsigned sweep_tune_epoch();
 // MACPROJ_TUNE_CACHE (read on first use, written by tune_save_env).
 int tune_find(int nx, int ny, int nz, bool rho, bool dbl, bool coarse);    // -1: none
 void tune_put(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, int cfg);
+void tune_erase(int nx, int ny, int nz, bool rho, bool dbl, bool coarse);
 int tune_count();
 unsigned tune_epoch();
 void tune_force(int cfg);          // -1: per-shape choice

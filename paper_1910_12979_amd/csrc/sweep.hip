@@ -684,8 +684,9 @@ int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, bo
     if (!sweep_marchable(nx, ny, nz)) return kTileCfg;
     const int forced = tune_forced();
     if (forced >= 0 && sweep_cfg_fits(nx, ny, forced)) return forced;
+    // 4-plane chunks are the tuner's answer for a problem alone on the chip
     const int tuned = tune_find(nx, ny, nz, rho, dbl, coarse);
-    if (tuned >= 0) return tuned;
+    if (tuned >= 0 && !(batch && tuned >= kFirstCoarseCfg)) return tuned;
     // untuned shapes: choices measured on MI355X (us per FP64 sweep with the
     // coefficients from rho).  Small levels of a single problem: kTileCfg,
     // which has no march whose latency an idle chip would show (32^3 5.5
@@ -713,20 +714,16 @@ int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, bo
     return batch ? 5 : 13;
 }
 
-static bool config_chosen(int cfg, int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
-    return cfg == tune_forced() || tune_find(nx, ny, nz, rho, dbl, coarse) >= 0;
-}
-
 int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
     const int cfg = sweep_config_for(nx, ny, nz, rho, dbl, coarse);
-    if (config_chosen(cfg, nx, ny, nz, rho, dbl, coarse)) return cfg;
+    if (cfg == tune_forced()) return cfg;
     if ((double)nx * ny * nz <= kTileRestrict && sweep_tileable(nx, ny, nz)) return kTileCfg;
     return !dbl && cfg == 11 ? 9 : cfg;
 }
 
 int zero_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
     const int cfg = sweep_config_for(nx, ny, nz, rho, dbl, coarse);
-    if (config_chosen(cfg, nx, ny, nz, rho, dbl, coarse)) return cfg;
+    if (cfg == tune_forced()) return cfg;
     return !dbl && cfg == 11 && (double)nx * ny * nz < 4.0e7 ? 9 : cfg;
 }
 

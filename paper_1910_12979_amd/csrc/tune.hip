@@ -1,7 +1,8 @@
 // Fused-sweep tuning table and its persistent JSON cache.
 //
 // The autotuner (mg_autotune) times every tile configuration on each level
-// shape of a hierarchy and records the fastest here, keyed by the GPU
+// shape of a hierarchy, the untuned choice among them, and records the fastest
+// here (no entry where the marchless tiles are), keyed by the GPU
 // architecture (the device's gcnArchName, e.g. "gfx950:sramecc+:xnack-"),
 // the level shape, the coefficient source (rho or stored), the precision and
 // whether the level is a coarse level.  With the environment variable
@@ -341,6 +342,12 @@ void tune_put(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, int cfg) 
     env_load_locked();
     g_table[TuneKey(current_arch(), nx, ny, nz, rho ? 1 : 0, dbl ? 1 : 0, coarse ? 1 : 0)] = cfg;
     ++g_epoch;
+}
+
+void tune_erase(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    env_load_locked();
+    if (g_table.erase(TuneKey(current_arch(), nx, ny, nz, rho ? 1 : 0, dbl ? 1 : 0, coarse ? 1 : 0))) ++g_epoch;
 }
 
 int tune_count() {

@@ -1,0 +1,64 @@
+"""mg_autotune does not lose to the untuned choice: its candidates hold that
+choice on every level, also where it is a 4-plane chunk or the form without a
+march, so a tuned level sweeps as fast (within the timer's noise), and the
+tuned solves, alone and in a batch, give the untuned bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1910_12979_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def sweep_us(H, level, sweeps=300):
+    """Time of one sweep on a level: the best of seven runs of `sweeps`."""
+    best = 1e30
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        H.level_step(level, "smooth", sweeps)
+        b.record()
+        b.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b) / sweeps)
+    return best
+
+
+def solves(mp, prob):
+    par = mp.params_of(prob)
+    out = []
+    d = mp.to_device(prob)
+    H = mp.Hierarchy(par)
+    H.mac_project(d.rho, d.beta0_cc, d.beta0_edge, d.S, d.u, d.v, d.w, d.phi)
+    H.close()
+    ds = [mp.to_device(prob) for _ in range(3)]
+    code, _ = mp.project_batch([par] * 3, ds)
+    assert code == 0
+    for t in [d] + ds:
+        out += [getattr(t, k).cpu().numpy() for k in ("phi", "u", "v", "w")]
+    return out
+
+
+@pytest.mark.parametrize("n", [(32, 32, 32),       # the form without a march on the finest level
+                               (64, 64, 64),       # 4-plane chunks there
+                               (128, 64, 64)])
+def test_autotune_keeps_up_with_the_default(mp, n):
+    prob = I.make_problem(n, H=0.2, rho_noise=0.05, seed=5, dx=1 / n[0])
+    d = mp.to_device(prob)
+    mp.tune_cache_clear()
+    H = mp.Hierarchy(mp.params_of(prob))
+    try:
+        ref = solves(mp, prob)
+        H.set_coefficients(d.rho, d.beta0_cc, d.beta0_edge)
+        levels = [l for l in range(H.nlevels - 1) if H.sweep_config(l)]
+        before = {l: (H.sweep_config(l), sweep_us(H, l)) for l in levels}
+        H.mg_autotune(reps=40)
+        after = {l: (H.sweep_config(l), sweep_us(H, l)) for l in levels}
+        print(before, after)
+        for l in levels:
+            assert after[l][1] <= 1.3 * before[l][1], (l, before[l], after[l])
+        for a, b in zip(ref, solves(mp, prob)):
+            assert np.array_equal(a, b)
+    finally:
+        H.close()
+        mp.tune_cache_clear()
