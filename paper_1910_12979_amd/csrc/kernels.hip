@@ -1188,6 +1188,7 @@ hipError_t launch_dense_blocks(double* M, int n, double* scratch, hipStream_t st
 
 hipError_t launch_coarse_setup(const Shape& s, double h, const double* bx, const double* by, const double* bz,
                                double* minv, double* scratch, hipStream_t st, const Bnd<double>* bnd, int singular) {
+    if (s.N() < 1 || s.N() > (size_t)kCoarseMax) return hipErrorInvalidValue;
     const CoarseRows R{s.nx, s.ny, s.nz, 1.0 / (h * h), bx, by, bz, bnd ? *bnd : Bnd<double>{}, bnd ? 1 : 0};
     const int n = (int)s.N();
     if (n <= kDenseReg) {

@@ -479,6 +479,7 @@ __global__ __launch_bounds__(256) void k_nod_coarse_build(NodCoarseRows R, doubl
 }
 
 hipError_t launch_nod_coarse_setup(const NodLevel& L, double* minv, double* scratch, hipStream_t st) {
+    if (L.nodes() < 1 || L.nodes() > (size_t)kCoarseMax) return hipErrorInvalidValue;
     const NodCoarseRows R{L, 1.0 / (12.0 * L.h * L.h)};
     const int n = (int)L.nodes();
     if (n <= kDenseReg) {
