@@ -162,7 +162,9 @@ int launch_fused(std::vector<Item>& grp, bool use_rho, int in_mode, int op, Stag
     std::map<int, std::vector<Item*>> by_cfg;
     for (auto& it : grp) {
         Level& F = it.H->lev[it.l];
-        by_cfg[sweep_config_for(F.nx, F.ny, F.nz, use_rho, true, false, op != kOpSweepNorm)].push_back(&it);
+        const int cfg = op == kOpSweepNorm ? norm_config_for(F.nx, F.ny, F.nz, use_rho)
+                                           : sweep_config_for(F.nx, F.ny, F.nz, use_rho, true, false, true);
+        by_cfg[cfg].push_back(&it);
     }
     for (auto& kv : by_cfg) {
         const int cfg = kv.first;
@@ -371,7 +373,8 @@ int multi_norm_sweep(std::vector<mg_hierarchy*>& hs, double* gather, Staging& S,
     for (size_t i = 0; i < hs.size(); ++i) {
         mg_hierarchy* H = hs[i];
         Level& L0 = H->lev[0];
-        rd.push_back(ReduceDesc{H->partials, sweep_tiles(L0.nx, L0.ny, L0.nz, sweep_config_for(L0.nx, L0.ny, L0.nz, true)),
+        const int cfg = norm_config_for(L0.nx, L0.ny, L0.nz, true);
+        rd.push_back(ReduceDesc{H->partials, sweep_tiles(L0.nx, L0.ny, L0.nz, cfg),
                                 H->scal + kSlotRes * kReduceWidth, gather + i * kReduceWidth});
     }
     void* dd = nullptr;

@@ -741,7 +741,7 @@ static int enqueue_sweep_norm(mg_hierarchy* H, hipStream_t st) {
     a.dg = L0.dg_d;
     const bool rho0 = H->rho.rho != nullptr;
     int np = 0;
-    HIPCHK(launch_sweep_norm(a, rho0, sweep_config_for(L0.nx, L0.ny, L0.nz, rho0), &np, st));
+    HIPCHK(launch_sweep_norm(a, rho0, norm_config_for(L0.nx, L0.ny, L0.nz, rho0), &np, st));
     HIPCHK(launch_reduce(H->partials, np, H->scal + kSlotRes * kReduceWidth, st, norm_ring(H->scal)));
     return MG_OK;
 }

@@ -714,6 +714,12 @@ int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, bo
     return batch ? 5 : 13;
 }
 
+int norm_config_for(int nx, int ny, int nz, bool rho) {
+    const int cfg = sweep_config_for(nx, ny, nz, rho);
+    if (cfg != kTileCfg || (double)nx * ny * nz <= kTileNorm || !sweep_marchable(nx, ny, nz)) return cfg;
+    return ny >= 8 ? 12 : 13;
+}
+
 int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
     const int cfg = sweep_config_for(nx, ny, nz, rho, dbl, coarse);
     if (cfg == tune_forced()) return cfg;
