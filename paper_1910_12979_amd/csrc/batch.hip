@@ -167,7 +167,7 @@ int launch_fused(std::vector<Item>& grp, bool use_rho, int in_mode, int op, Stag
         by_cfg[cfg].push_back(&it);
     }
     for (auto& kv : by_cfg) {
-        const int cfg = kv.first;
+        const int cfg = op == kOpSweepNorm ? batch_norm_config(kv.first) : kv.first;
         if (!multi_tile_shape(cfg)) {
             for (Item* it : kv.second) {
                 SweepArgs<double> a = sweep_args(it->H, it->l);
@@ -187,6 +187,7 @@ int launch_fused(std::vector<Item>& grp, bool use_rho, int in_mode, int op, Stag
         for (Item* it : kv.second) {
             SweepArgs<double> a = sweep_args(it->H, it->l);
             sweep_geometry(a, cfg);
+            a.half_rows = cfg != kv.first ? 1 : 0;
             const int nt = sweep_tiles(a.nx, a.ny, a.nz, cfg);
             for (int t = 0; t < nt; ++t) tmap.push_back(make_int2((int)descs.size(), t));
             descs.push_back(a);
@@ -618,9 +619,11 @@ int multi_refine(std::vector<mg_hierarchy*>& hs, double* gather, Staging& S, hip
         a.corr = L0.s.phi;
         a.r32 = L0.s.f;
         a.scales = H->scal + kSlotScale * kReduceWidth;
-        const int cfg = sweep_config_for(L0.nx, L0.ny, L0.nz, true);
+        const int cfg = norm_config_for(L0.nx, L0.ny, L0.nz, true);
+        const int deep = batch_norm_config(cfg);
+        a.half_rows = deep != cfg ? 1 : 0;
         args.push_back(a);
-        cfgs.push_back(cfg);
+        cfgs.push_back(deep);
         rd.push_back(ReduceDesc{H->partials, sweep_tiles(L0.nx, L0.ny, L0.nz, cfg), H->scal + kSlotRes * kReduceWidth,
                                 gather + i * kReduceWidth});
         sd.push_back(ScaleDesc{H->scal + kSlotRes * kReduceWidth, H->scal + kSlotScale * kReduceWidth, (double)L0.N});

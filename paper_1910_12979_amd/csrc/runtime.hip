@@ -913,7 +913,7 @@ static int solve_level0_mixed_fused(mg_hierarchy* H, double fnorm, int* cycles_o
     H->host[kSlotScale * kReduceWidth + 1] = s0;
     HIPCHK(hipMemcpyAsync(scales, H->host + kSlotScale * kReduceWidth, 2 * sizeof(double), hipMemcpyHostToDevice,
                           st));
-    const int cfg = sweep_config_for(L0.nx, L0.ny, L0.nz, rho0);
+    const int cfg = norm_config_for(L0.nx, L0.ny, L0.nz, rho0);
     const int inner = inner_cycles_of(H->p);
     auto iteration = [H, &L0, cfg, scales, rho0, inner](hipStream_t s) {
         // the FP32 correction: V-cycles on the scaled residual, from zero

@@ -14,7 +14,7 @@ constexpr int kSweepTY = 4;      // smallest tile height (y)
 constexpr int kSweepTZMax = 64;  // largest z-chunk
 constexpr double kTileSolo = 1.5e5;     // largest level (cells) of a single problem that kTileCfg sweeps by default
 constexpr double kTileRestrict = 6.0e5; // and whose residual it restricts
-constexpr double kTileNorm = 6.0e4;     // and whose sweep with the residual norm it takes (norm_config_for)
+constexpr double kTileNorm = 4.0e4;     // and whose sweep with the residual norm it takes (norm_config_for)
 constexpr int kMaxPartialRows = 2048;   // rows of a hierarchy's partial-sum buffer
 
 // Tile configurations of the fused sweep (TX x TY columns, TZ planes per
@@ -59,6 +59,7 @@ struct SweepArgs {
     int has_bnd;               // outflow sides: their boundary faces add to the diagonal
     Bnd<T> bnd;                // which sides are outflow sides (non-null)
     const T* dg;               // per-cell boundary diagonal (bnd_diag of every cell)
+    int half_rows;             // two norm rows a tile, each of half a chunk (batch_norm_config)
     int march_div;             // kTileCfg in FP32: divide as the marching sweep does (sweep_marchable)
     int ox, oy, oz;            // launch_sweep_boxes: first cell of a box interior
     int ex, ey, ez;            // launch_sweep_boxes: box cells
@@ -156,15 +157,18 @@ template <typename T>
 hipError_t launch_sweep_boxes_mode(const SweepArgs<T>& a, const BoxGeom& g, int nbox, size_t bstride, int mode,
                                    int* nparts, hipStream_t st);
 
-// The configuration of a finest level's sweep with the residual norm.  Its rows
-// are those of its tiles, so that a batch, to sum them in the same order, has to
-// take the single problem's; and there the marchless tiles, which fetch every
-// value several times, cost more than they save a problem alone.  Above
-// kTileNorm cells the level's 4-plane march therefore: 64 problems of 64x48x32
-// cells 5.17 ms for 5.56, of 48^3 6.69 for 7.06, while one of either takes 1 to
-// 2% longer (0.71 ms for 0.70); at 32^3 one would take 0.63 ms for 0.61, 64 of
-// them 2.67 for 2.84.
+// The configuration of a finest level's sweep with the residual norm and of the
+// refinement, which write a row per tile: the single problem's, so that a batch
+// sums the same rows.  The marchless tiles, which fetch every value several
+// times, cost a batch more than they save a problem alone; they are kept up to
+// kTileNorm cells and where no tile is ragged (64 problems of 32^3 cells 2.84
+// ms, 2.67 without, but one of them 0.61 for 0.63).
 int norm_config_for(int nx, int ny, int nz, bool rho);
+// A batch's configuration for these rows: in place of 32x8 tiles of 4 or 8
+// planes, which cost it a fifth more, ones twice as deep that write both rows
+// (SweepArgs::half_rows).  64 problems: sweep of 96x80x48 cells 364 us, now 299;
+// refinement of 48^3 125 without a march, now 105.  Else cfg.
+int batch_norm_config(int cfg);
 
 // The configuration of the residual + restriction, which needs no ring of red
 // cells: kTileCfg up to kTileRestrict cells (64^3 FP64, stored coefficients:
@@ -186,9 +190,8 @@ int sweep_tiles(int nx, int ny, int nz, int cfg);
 // V-cycle: forced, autotuned, else a measured default.  A deterministic
 // function of these, so a problem's tiles are the same in every run.  batch:
 // for a launch over many problems, whose work fills the CUs (values do not
-// depend on the configuration; the operations that write norm rows take the
-// single problem's in a batch too, so that the rows' order is the same:
-// norm_config_for, and this for the refinement).
+// depend on the configuration; the operations that write norm rows take
+// norm_config_for, for the same rows in both).
 int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl = true, bool coarse = false, bool batch = false);
 bool sweep_cfg_fits(int nx, int ny, int cfg);
 void sweep_record_tuned(int nx, int ny, int nz, bool rho, bool dbl, int cfg, bool coarse);

@@ -95,6 +95,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
     constexpr bool kRR = kOp == kOpResidRestrict;  // residual + restriction only (no sweep)
     constexpr bool kIR = kOp == kOpRefine;         // corrected phi + scaled residual + norm (no sweep)
     constexpr bool kGS = !kRR && !kIR;             // red/black updates
+    constexpr bool kHalf = (kNorm || kIR) && !kBox && TX == 32 && TY == 8;    // may write a row per half chunk
     constexpr int WX = TX + 4, WY = TY + 4, WP = WX / 2;   // ring-2 window, pairs per row
     constexpr int NB = kSweepTZMax + 6;                    // beta0 planes staged per chunk
     // Every LDS plane is double-buffered or tripled so that one barrier per
@@ -314,7 +315,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
     // residual of phi_in (kNorm, kRR) or of the corrected phi (kIR):
     // r = f - (sum_f b (phi_nb - phi_c)) / h^2 in the reference face order
     // only the sum of squares is kept: a non-finite residual makes it non-finite
-    double nrm2 = 0.0;
+    double nrm2 = 0.0, nfirst = 0.0;         // nfirst: of the chunk's first half (half_rows)
     const double rscale = kIR ? a.scales[1] : 0.0;
     auto resid_at = [&](int c, int t, int s_t, int b, T pm, T pc, T pp, T bzl, T bzh, T fc) -> T {
         const int lx = lx0 + c;
@@ -416,6 +417,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
             if (kNorm) rred = den * (pin - Rcur) * ih2;
         }
         if (kGS) sR[cur][ly][lxr] = Rcur;
+        if (kHalf && a.half_rows && t == z0 + (a.tz >> 1) && t < z1) {
+            nfirst = nrm2;
+            nrm2 = 0.0;
+        }
         if (kNorm && t >= z0 && t < z1 && writes) {
             accumulate(rred);
             const int cb = 1 - rsel;             // black cell of the pair: full evaluation
@@ -519,24 +524,31 @@ __device__ __forceinline__ void sweep_body(const SweepArgs<T>& a, const int tile
         // with twelve all wavefronts stayed until the end (256^3 119 us, now 115)
         double* red = reinterpret_cast<double*>(&sR[0][0][0]);
         const int nt = blockDim.x;
-        static_assert(sizeof(sR) >= (WP * WY) * sizeof(double), "reduction buffer");
-        red[threadIdx.x] = nrm2;
+        const bool two = kHalf && a.half_rows && z1 - z0 > (a.tz >> 1);
+        static_assert(sizeof(sR) >= (kHalf ? 2 : 1) * (WP * WY) * sizeof(double), "reduction buffer");
+        red[threadIdx.x] = two ? nfirst : nrm2;
+        if (two) red[nt + threadIdx.x] = nrm2;
         __syncthreads();
         if (threadIdx.x >= 64) return;
         // slot i of 256: the threads i, i + 256, ..; then the binary tree
         // whose first step adds slot i + 128 to slot i
-        double x[4] = {0.0, 0.0, 0.0, 0.0};
+        auto write_row = [&](const double* v, int at) {
+            double x[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            for (int i = threadIdx.x + 64 * q; i < nt; i += 256) x[q] += red[i];
-        const double sum = tree64((x[0] + x[2]) + (x[1] + x[3]), false);
-        if (threadIdx.x == 0) {
-            double* row = a.partials + (size_t)tile * kReduceWidth;
-            row[0] = sum;
-            row[1] = 0.0;
-            row[2] = 0.0;
-            row[3] = 0.0;
-        }
+            for (int q = 0; q < 4; ++q)
+                for (int i = threadIdx.x + 64 * q; i < nt; i += 256) x[q] += v[i];
+            const double sum = tree64((x[0] + x[2]) + (x[1] + x[3]), false);
+            if (threadIdx.x == 0) {
+                double* row = a.partials + (size_t)at * kReduceWidth;
+                row[0] = sum;
+                row[1] = 0.0;
+                row[2] = 0.0;
+                row[3] = 0.0;
+            }
+        };
+        const int at = kHalf && a.half_rows ? (2 * tz * a.nty + ty) * a.ntx + tx : tile;
+        write_row(red, at);
+        if (two) write_row(red + nt, at + a.nty * a.ntx);
     }
 }
 
@@ -716,8 +728,17 @@ int sweep_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse, bo
 
 int norm_config_for(int nx, int ny, int nz, bool rho) {
     const int cfg = sweep_config_for(nx, ny, nz, rho);
-    if (cfg != kTileCfg || (double)nx * ny * nz <= kTileNorm || !sweep_marchable(nx, ny, nz)) return cfg;
-    return ny >= 8 ? 12 : 13;
+    if (cfg != kTileCfg || !sweep_marchable(nx, ny, nz) || !sweep_cfg_fits(nx, ny, 12)) return cfg;
+    const SweepCfg& c = kSweepCfgs[kTileCfg];
+    const bool whole = nx % c.tx == 0 && ny % c.ty == 0 && nz % c.tz == 0;
+    return whole && (double)nx * ny * nz <= kTileNorm ? cfg : 12;
+}
+
+int batch_norm_config(int cfg) {
+    constexpr SweepCfg a = kSweepCfgs[12], b = kSweepCfgs[7], c = kSweepCfgs[6];
+    static_assert(a.tx == 32 && a.ty == 8 && b.tx == 32 && b.ty == 8 && c.tx == 32 && c.ty == 8, "kHalf's tiles");
+    static_assert(b.tz == 2 * a.tz && c.tz == 2 * b.tz, "two rows a tile");
+    return cfg == 12 ? 7 : cfg == 7 ? 6 : cfg;
 }
 
 int restrict_config_for(int nx, int ny, int nz, bool rho, bool dbl, bool coarse) {
