@@ -796,8 +796,9 @@ int Engine::setup_new(std::vector<Job*>& fresh, hipStream_t st) {
     if (rc) return rc;
     std::vector<CoeffDesc> cd;
     std::vector<ReduceDesc> rd;
-    std::vector<CoarseDesc> co;
-    std::vector<mg_hierarchy*> co_big;         // coarsest levels that take several launches each
+    std::vector<CoarseDesc> co, co_big;        // coarsest levels inverted by a workgroup each, and in blocks
+    std::vector<DenseDesc> big;
+    int big_n = 0;
     std::vector<EltDesc> f32;
     int cblocks = 0, f32blocks = 0, maxlev = 0;
     for (size_t q = 0; q < fresh.size(); ++q) {
@@ -831,10 +832,14 @@ int Engine::setup_new(std::vector<Job*>& fresh, hipStream_t st) {
         rd.push_back(ReduceDesc{H->partials, nb, H->scal + kSlotRhs * kReduceWidth, gdev + q * kReduceWidth});
         maxlev = std::max(maxlev, H->nlev);
         Level& Lc = H->lev[H->nlev - 1];
-        if (coarse_setup_batched(Lc.N))
-            co.push_back(CoarseDesc{Lc.nx, Lc.ny, Lc.nz, Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, H->singular ? 1 : 0});
-        else
-            co_big.push_back(H);
+        const CoarseDesc c{Lc.nx, Lc.ny, Lc.nz, Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, H->singular ? 1 : 0};
+        if (coarse_setup_batched(Lc.N)) {
+            co.push_back(c);
+        } else {
+            co_big.push_back(c);
+            big.push_back(DenseDesc{H->minv, (int)Lc.N, H->partials});   // its partial rows are reduced before
+            big_n = std::max(big_n, (int)Lc.N);
+        }
         if (H->p.precision == MG_MIXED) {
             // FP32 coefficient mirrors of the stored levels (the finest FP32
             // level recomputes its coefficients from an FP32 copy of rho)
@@ -875,10 +880,12 @@ int Engine::setup_new(std::vector<Job*>& fresh, hipStream_t st) {
         if ((rc = push_table(staging, co, st, &dco))) return rc;
         BHIP(launch_coarse_setup_multi(dco, (int)co.size(), st));
     }
-    for (mg_hierarchy* H : co_big) {            // its partial rows are reduced already: scratch
-        const Level& Lc = H->lev[H->nlev - 1];
-        BHIP(launch_coarse_setup(Shape{Lc.nx, Lc.ny, Lc.nz}, Lc.h, Lc.d.bx, Lc.d.by, Lc.d.bz, H->minv, H->partials,
-                                 st, nullptr, H->singular ? 1 : 0));
+    if (!co_big.empty()) {
+        const CoarseDesc* dco = nullptr;
+        const DenseDesc* dm = nullptr;
+        if ((rc = push_table(staging, co_big, st, &dco))) return rc;
+        if ((rc = push_table(staging, big, st, &dm))) return rc;
+        BHIP(launch_coarse_blocks_multi(dco, dm, (int)big.size(), big_n, st));
     }
     if (!f32.empty()) {
         const EltDesc* de = nullptr;

@@ -512,14 +512,28 @@ __global__ __launch_bounds__(256) void k_coarse_build(CoarseRows R, double* __re
     dense_build_row<6>(R.nx * R.ny * R.nz, singular, M, R, [&](int c) { return R.diag(c); });
 }
 
+// Problem blockIdx.y's row blockIdx.x (batches have no outflow sides).
+__global__ __launch_bounds__(256) void k_coarse_build_multi(const CoarseDesc* __restrict__ d) {
+    const CoarseDesc c = d[blockIdx.y];
+    if ((int)blockIdx.x >= c.nx * c.ny * c.nz) return;
+    const CoarseRows R{c.nx, c.ny, c.nz, 1.0 / (c.h * c.h), c.bx, c.by, c.bz, Bnd<double>{}, 0};
+    dense_build_row<6>(c.nx * c.ny * c.nz, c.singular, c.minv, R, [&](int i) { return R.diag(i); });
+}
+
 // One block step of the inversion above kDenseReg unknowns, pivots p0 ..
 // p0 + nb - 1 (nb <= kDenseNB; a last, smaller block is padded by the unit
-// matrix).  First W = P^-1 R into scratch, P the pivot block and R its rows
+// matrix), of one matrix or of many (each launch waits for the one before, so a
+// batch's matrices share them: 64 of 210 unknowns one after another 7.7 ms).  First W = P^-1 R into scratch, P the pivot block and R its rows
 // (with the unit columns in the block's own columns): thread j loads column j
 // of R while the first wavefront inverts P (its LDS traffic needs no barrier).
 constexpr int kPanelThreads = kCoarseMax;
-__global__ __launch_bounds__(kPanelThreads) void k_dense_panel(const double* __restrict__ M, int n, int p0, int nb,
-                                                               double* __restrict__ W) {
+__global__ __launch_bounds__(kPanelThreads) void k_dense_panel(DenseDesc one, const DenseDesc* __restrict__ many,
+                                                               int p0) {
+    const DenseDesc d = many ? many[blockIdx.x] : one;
+    const double* __restrict__ M = d.M;
+    double* __restrict__ W = d.scratch;
+    const int n = d.n, nb = min(kDenseNB, n - p0);
+    if (nb <= 0) return;
     constexpr int NB = kDenseNB, G = 64 / NB, E = NB / G;      // lane (g, tj): rows g E .., column tj
     __shared__ double prow[2][NB], pcol[2][NB];
     __shared__ __align__(16) double inv[NB][NB];
@@ -574,9 +588,14 @@ __global__ __launch_bounds__(kPanelThreads) void k_dense_panel(const double* __r
 // become W, every other row i subtracts sum_k M_i,p0+k W_k (its own block
 // columns counted as 0).  A strip reads and writes only its own rows of M.
 constexpr int kStripRows = 4;
-__global__ __launch_bounds__(kPanelThreads) void k_dense_update(double* __restrict__ M, int n, int p0, int nb,
-                                                                const double* __restrict__ W) {
+__global__ __launch_bounds__(kPanelThreads) void k_dense_update(DenseDesc one, const DenseDesc* __restrict__ many,
+                                                                int p0) {
     constexpr int NB = kDenseNB;
+    const DenseDesc d = many ? many[blockIdx.y] : one;
+    double* __restrict__ M = d.M;
+    const double* __restrict__ W = d.scratch;
+    const int n = d.n, nb = min(kDenseNB, n - p0);
+    if (nb <= 0 || (int)blockIdx.x * kStripRows >= n) return;
     __shared__ __align__(16) double C[kStripRows][NB];
     const int i0 = blockIdx.x * kStripRows, j = threadIdx.x;
     double w[NB], v[kStripRows];
@@ -1175,15 +1194,19 @@ hipError_t launch_resid_restrict_rho(const Shape& fine, double h, const RhoArgs&
     return hipGetLastError();
 }
 
-hipError_t launch_dense_blocks(double* M, int n, double* scratch, hipStream_t st) {
+// Block steps of nprob matrices (many: device; null: one), the largest n x n.
+static hipError_t dense_blocks(const DenseDesc& one, const DenseDesc* many, int nprob, int n, hipStream_t st) {
     if (n < 1 || n > kCoarseMax) return hipErrorInvalidValue;
     for (int p0 = 0; p0 < n; p0 += kDenseNB) {
-        const int nb = std::min(kDenseNB, n - p0);
-        hipLaunchKernelGGL(k_dense_panel, dim3(1), dim3(kPanelThreads), 0, st, M, n, p0, nb, scratch);
-        hipLaunchKernelGGL(k_dense_update, dim3((n + kStripRows - 1) / kStripRows), dim3(kPanelThreads), 0, st, M, n,
-                           p0, nb, (const double*)scratch);
+        hipLaunchKernelGGL(k_dense_panel, dim3(nprob), dim3(kPanelThreads), 0, st, one, many, p0);
+        hipLaunchKernelGGL(k_dense_update, dim3((n + kStripRows - 1) / kStripRows, nprob), dim3(kPanelThreads), 0, st,
+                           one, many, p0);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_dense_blocks(double* M, int n, double* scratch, hipStream_t st) {
+    return dense_blocks(DenseDesc{M, n, scratch}, nullptr, 1, n, st);
 }
 
 hipError_t launch_coarse_setup(const Shape& s, double h, const double* bx, const double* by, const double* bz,
@@ -1547,6 +1570,13 @@ hipError_t launch_coarse_setup_multi(const CoarseDesc* d, int nprob, hipStream_t
     if (nprob <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_coarse_setup_multi, dim3(nprob), dim3(kDenseThreads), 0, st, d);
     return hipGetLastError();
+}
+
+hipError_t launch_coarse_blocks_multi(const CoarseDesc* d, const DenseDesc* m, int nprob, int n, hipStream_t st) {
+    if (nprob <= 0) return hipSuccess;
+    if (n < 1 || n > kCoarseMax) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_coarse_build_multi, dim3(n, nprob), dim3(256), 0, st, d);
+    return dense_blocks(DenseDesc{}, m, nprob, n, st);
 }
 
 hipError_t launch_elt_multi(const EltDesc* d, int nprob, int blocks, hipStream_t st) {

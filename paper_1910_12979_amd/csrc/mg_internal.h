@@ -415,6 +415,12 @@ struct CoarseDesc {
     double* minv;
     int singular;
 };
+// A matrix of the blocked inversion: n x n, scratch 16 n doubles.
+struct DenseDesc {
+    double* M;
+    int n;
+    double* scratch;
+};
 // Elementwise operations over n values: kEltFill dst[e] = s (FP64),
 // kEltToF32 dst[e] = (float)src[e], kEltScaleToF32 dst[e] = (float)(src[e] * s).
 enum { kEltFill = 0, kEltToF32 = 1, kEltScaleToF32 = 2 };
@@ -461,6 +467,8 @@ hipError_t launch_avg_coeff_multi(const AvgDesc* d, int nprob, int blocks, hipSt
 // every problem's coarsest level small enough for one workgroup (coarse_setup_batched)
 hipError_t launch_coarse_setup_multi(const CoarseDesc* d, int nprob, hipStream_t st);
 bool coarse_setup_batched(size_t n);
+// the others, at most n unknowns each, block by block (m: their matrices)
+hipError_t launch_coarse_blocks_multi(const CoarseDesc* d, const DenseDesc* m, int nprob, int n, hipStream_t st);
 hipError_t launch_elt_multi(const EltDesc* d, int nprob, int blocks, hipStream_t st);
 hipError_t launch_correct_multi(const CorrectDesc* d, int nprob, int blocks, hipStream_t st);
 // Mixed precision: the scale update of launch_next_scale for many problems.
