@@ -527,13 +527,8 @@ __global__ __launch_bounds__(256) void k_coarse_build_multi(const CoarseDesc* __
 // (with the unit columns in the block's own columns): thread j loads column j
 // of R while the first wavefront inverts P (its LDS traffic needs no barrier).
 constexpr int kPanelThreads = kCoarseMax;
-__global__ __launch_bounds__(kPanelThreads) void k_dense_panel(DenseDesc one, const DenseDesc* __restrict__ many,
-                                                               int p0) {
-    const DenseDesc d = many ? many[blockIdx.x] : one;
-    const double* __restrict__ M = d.M;
-    double* __restrict__ W = d.scratch;
-    const int n = d.n, nb = min(kDenseNB, n - p0);
-    if (nb <= 0) return;
+__device__ __forceinline__ void dense_panel(const double* __restrict__ M, int n, int p0, int nb,
+                                            double* __restrict__ W) {
     constexpr int NB = kDenseNB, G = 64 / NB, E = NB / G;      // lane (g, tj): rows g E .., column tj
     __shared__ double prow[2][NB], pcol[2][NB];
     __shared__ __align__(16) double inv[NB][NB];
@@ -588,14 +583,9 @@ __global__ __launch_bounds__(kPanelThreads) void k_dense_panel(DenseDesc one, co
 // become W, every other row i subtracts sum_k M_i,p0+k W_k (its own block
 // columns counted as 0).  A strip reads and writes only its own rows of M.
 constexpr int kStripRows = 4;
-__global__ __launch_bounds__(kPanelThreads) void k_dense_update(DenseDesc one, const DenseDesc* __restrict__ many,
-                                                                int p0) {
+__device__ __forceinline__ void dense_update(double* __restrict__ M, int n, int p0, int nb,
+                                             const double* __restrict__ W) {
     constexpr int NB = kDenseNB;
-    const DenseDesc d = many ? many[blockIdx.y] : one;
-    double* __restrict__ M = d.M;
-    const double* __restrict__ W = d.scratch;
-    const int n = d.n, nb = min(kDenseNB, n - p0);
-    if (nb <= 0 || (int)blockIdx.x * kStripRows >= n) return;
     __shared__ __align__(16) double C[kStripRows][NB];
     const int i0 = blockIdx.x * kStripRows, j = threadIdx.x;
     double w[NB], v[kStripRows];
@@ -625,6 +615,24 @@ __global__ __launch_bounds__(kPanelThreads) void k_dense_update(DenseDesc one, c
         }
         M[(size_t)i * n + j] = x;
     }
+}
+
+__global__ __launch_bounds__(kPanelThreads) void k_dense_panel(const double* __restrict__ M, int n, int p0, int nb,
+                                                               double* __restrict__ W) {
+    dense_panel(M, n, p0, nb, W);
+}
+__global__ __launch_bounds__(kPanelThreads) void k_dense_update(double* __restrict__ M, int n, int p0, int nb,
+                                                                const double* __restrict__ W) {
+    dense_update(M, n, p0, nb, W);
+}
+// The block from p0 of every matrix that has one.
+__global__ __launch_bounds__(kPanelThreads) void k_dense_panel_multi(const DenseDesc* __restrict__ m, int p0) {
+    const DenseDesc d = m[blockIdx.x];
+    if (p0 < d.n) dense_panel(d.M, d.n, p0, min(kDenseNB, d.n - p0), d.scratch);
+}
+__global__ __launch_bounds__(kPanelThreads) void k_dense_update_multi(const DenseDesc* __restrict__ m, int p0) {
+    const DenseDesc d = m[blockIdx.y];
+    if (p0 < d.n && (int)blockIdx.x * kStripRows < d.n) dense_update(d.M, d.n, p0, min(kDenseNB, d.n - p0), d.scratch);
 }
 
 constexpr int kSolveThreads = 512;
@@ -1194,19 +1202,15 @@ hipError_t launch_resid_restrict_rho(const Shape& fine, double h, const RhoArgs&
     return hipGetLastError();
 }
 
-// Block steps of nprob matrices (many: device; null: one), the largest n x n.
-static hipError_t dense_blocks(const DenseDesc& one, const DenseDesc* many, int nprob, int n, hipStream_t st) {
+hipError_t launch_dense_blocks(double* M, int n, double* scratch, hipStream_t st) {
     if (n < 1 || n > kCoarseMax) return hipErrorInvalidValue;
     for (int p0 = 0; p0 < n; p0 += kDenseNB) {
-        hipLaunchKernelGGL(k_dense_panel, dim3(nprob), dim3(kPanelThreads), 0, st, one, many, p0);
-        hipLaunchKernelGGL(k_dense_update, dim3((n + kStripRows - 1) / kStripRows, nprob), dim3(kPanelThreads), 0, st,
-                           one, many, p0);
+        const int nb = std::min(kDenseNB, n - p0);
+        hipLaunchKernelGGL(k_dense_panel, dim3(1), dim3(kPanelThreads), 0, st, M, n, p0, nb, scratch);
+        hipLaunchKernelGGL(k_dense_update, dim3((n + kStripRows - 1) / kStripRows), dim3(kPanelThreads), 0, st, M, n,
+                           p0, nb, (const double*)scratch);
     }
     return hipGetLastError();
-}
-
-hipError_t launch_dense_blocks(double* M, int n, double* scratch, hipStream_t st) {
-    return dense_blocks(DenseDesc{M, n, scratch}, nullptr, 1, n, st);
 }
 
 hipError_t launch_coarse_setup(const Shape& s, double h, const double* bx, const double* by, const double* bz,
@@ -1576,7 +1580,12 @@ hipError_t launch_coarse_blocks_multi(const CoarseDesc* d, const DenseDesc* m, i
     if (nprob <= 0) return hipSuccess;
     if (n < 1 || n > kCoarseMax) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_coarse_build_multi, dim3(n, nprob), dim3(256), 0, st, d);
-    return dense_blocks(DenseDesc{}, m, nprob, n, st);
+    for (int p0 = 0; p0 < n; p0 += kDenseNB) {
+        hipLaunchKernelGGL(k_dense_panel_multi, dim3(nprob), dim3(kPanelThreads), 0, st, m, p0);
+        hipLaunchKernelGGL(k_dense_update_multi, dim3((n + kStripRows - 1) / kStripRows, nprob), dim3(kPanelThreads), 0,
+                           st, m, p0);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_elt_multi(const EltDesc* d, int nprob, int blocks, hipStream_t st) {
