@@ -446,9 +446,8 @@ int mg_tune_lookup(const char* arch, const int32_t n[3], int32_t rho, int32_t fp
 int mg_set_graphs(mg_handle h, int32_t enable);
 
 /* Bottom of the V-cycle: with enable = 1 (the default) the levels of at most
- * 4096 cells, and wider ones that the fused sweep does not cover (when their
- * phi and f fit in 136 KB of LDS), run as one workgroup per V-cycle instead
- * of one launch per step and level.  Results are identical either way. */
+ * 4096 cells run as one workgroup per V-cycle instead of one launch per step
+ * and level.  Results are identical either way. */
 int mg_set_bottom(mg_handle h, int32_t enable);
 
 /* Multi-box finest level: the block-structured box layout whose boxes the

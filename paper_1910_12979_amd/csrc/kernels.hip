@@ -523,7 +523,8 @@ __global__ __launch_bounds__(256) void k_coarse_build_multi(const CoarseDesc* __
 // One block step of the inversion above kDenseReg unknowns, pivots p0 ..
 // p0 + nb - 1 (nb <= kDenseNB; a last, smaller block is padded by the unit
 // matrix), of one matrix or of many (each launch waits for the one before, so a
-// batch's matrices share them: 64 of 210 unknowns one after another 7.7 ms).  First W = P^-1 R into scratch, P the pivot block and R its rows
+// batch's matrices share them: 64 boxes with 210 unknowns 7.0 ms a batch, 17.2
+// with one matrix after another).  First W = P^-1 R into scratch, P the pivot block and R its rows
 // (with the unit columns in the block's own columns): thread j loads column j
 // of R while the first wavefront inverts P (its LDS traffic needs no barrier).
 constexpr int kPanelThreads = kCoarseMax;

@@ -982,7 +982,11 @@ template <>
 NodLevelT<float>* nod_levels<float>(nodal_hierarchy* H) { return H->lev32; }
 
 // First level (>= 1, above the coarsest) that the bottom kernel takes with
-// every coarser one, or -1.
+// every coarser one, or -1: the first that fits.  One level lower, with the
+// march above it, is slower for first levels of 16 x 16 x 17 nodes (32^3 cells
+// 0.79 ms for 0.76, 64^3 1.05 for 1.02) and 12 x 12 x 13 (48^3 0.98 for 0.89,
+// mixed 0.93 for 0.85), faster only for the largest that FP32 takes (24 x 16 x
+// 21, 96x64x80 mixed 1.11 for 1.21).
 template <typename T>
 int nod_bottom_start(const nodal_hierarchy* H) {
     using Cap = NodBottomCap<T>;

@@ -452,9 +452,10 @@ int build_coefficients(mg_hierarchy* H, const double* rho, const double* b0c, co
 
 // Sweeps on level l.  `first` selects what the first sweep reads as its
 // input: kInPlain (phi as stored), kInZero (phi = 0, nothing read) or
-// kInProlong (phi + P phi_{l+1}).  Levels large enough for the fused
-// out-of-place sweep ping-pong between the two phi buffers; smaller levels
-// use the per-colour kernels in place.
+// kInProlong (phi + P phi_{l+1}).  Levels that the fused out-of-place sweep
+// covers ping-pong between the two phi buffers; the others (thin ones, too
+// narrow to march and too large for the marchless tiles) use the per-colour
+// kernels in place.
 template <typename T>
 static int smooth(mg_hierarchy* H, int l, int nsweeps, int first, hipStream_t st) {
     constexpr bool dbl = std::is_same<T, double>::value;
@@ -896,7 +897,7 @@ double residual_scale(double norm2_sqrt, size_t n) {
 // device-side scales (the residual's, and the power of two nearest
 // 1/rms(r) for the next).  The FP32 finest-level sweeps recompute their
 // coefficients from an FP32 copy of rho (written by the coefficient kernel
-// when it could).  Iterations after the first replay a captured graph.
+// when it could).  With mg_set_graphs the iterations are captured and replayed.
 static int solve_level0_mixed_fused(mg_hierarchy* H, double fnorm, int* cycles_out, double* rel_out,
                                     const std::function<void(int, double)>& record, bool ahead, bool* over,
                                     hipStream_t st) {
@@ -1269,7 +1270,7 @@ static int project_impl(mg_hierarchy* H, const double* rho, const double* b0c, c
                 float ms = 0.f;
                 hipEventElapsedTime(&ms, H->evs0, H->evs1);
                 S_->ms_smooth = ms;
-            } else {       // every iteration ends with a host synchronisation: wall time of the loop
+            } else {       // the last look at the norms ends the loop: its wall time
                 S_->ms_smooth =
                     std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_s0).count();
             }

@@ -224,7 +224,7 @@ def make_params(n, dx, periodic=(True, True, False), pre_sweeps=2, post_sweeps=2
     """``outflow``: None or six booleans (x low, x high, ..., z high) marking
     sides of non-periodic directions as outflow sides (phi = 0).
     ``inner_cycles``: FP32 V-cycles per refinement step in mixed precision
-    (0: one)."""
+    (0: two, in the nodal projection one)."""
     p = Params()
     nx, ny, nz = n
     lib().mg_default_params(ctypes.byref(p), nx, ny, nz, float(dx))
@@ -360,7 +360,7 @@ class Hierarchy:
         _check(lib().mg_autotune(self._h, int(reps), _stream(stream)))
 
     def set_graphs(self, enable: bool):
-        """Replay captured V-cycles (default on) or launch every cycle eagerly."""
+        """Replay captured V-cycles, or (the default) launch every cycle separately."""
         _check(lib().mg_set_graphs(self._h, 1 if enable else 0))
 
     def set_bottom(self, enable: bool):
